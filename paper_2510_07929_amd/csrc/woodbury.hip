@@ -28,19 +28,13 @@
 namespace kqr {
 
 namespace {
-constexpr int kT = 64;        // SYRK / update / GEMM tile edge
-constexpr int kSubRows = 32;  // rows staged per LDS step of the SYRK
+constexpr int kT = 64;        // SYRK tile edge
+constexpr int kSubRows = 32;  // a SYRK chunk is a multiple of this many rows
 constexpr int kNb = 64;       // Cholesky panel width = inverse leaf block
 constexpr int kLt = 32;       // output tile edge of the Cholesky update and the doubling GEMMs
 constexpr int kGtBlocks = 512;
 constexpr int kGtStage = 256;
 }  // namespace
-
-// U(i, a) = F(i, a) for a < r, 1 for a == r, 0 beyond.
-__device__ __forceinline__ double u_at(const float* __restrict__ F, int64_t ldf, int r, int64_t i, int a) {
-  if (a < r) return double(F[i * ldf + a]);
-  return a == r ? 1.0 : 0.0;
-}
 
 __device__ __forceinline__ void tile_coords(int t, int& ta, int& tb) {
   int a = int((sqrtf(8.f * t + 1.f) - 1.f) * 0.5f);
@@ -59,101 +53,196 @@ __device__ __forceinline__ double load_or_zero(const double* p, bool ok) {
 }
 
 // part[s][tile][64x64] = sum over rows of chunk s of w_i U_ia U_ib, where the
-// rows are idx[k] (or k itself when idx is null) and w_i = 1/L_i (or 1).
-__global__ __launch_bounds__(256) void syrk_kernel(const float* __restrict__ F, int64_t nrows, int r,
-                                                   int64_t ldf, const double* __restrict__ L,
-                                                   const int* __restrict__ idx, int ntile, int64_t chunk,
-                                                   double* __restrict__ part) {
-  __shared__ double A[kSubRows][kT + 1];
-  __shared__ double B[kSubRows][kT + 1];
-  __shared__ int64_t rows[kSubRows];
-  __shared__ double wts[kSubRows];
+// rows are idx[k] (LISTED) or k itself and w_i (WEIGHTED) or 1 is the weight.
+//
+// The product runs on v_mfma_f64_16x16x4f64, which adds its four products in
+// order with one rounding each: an entry is the chain of FMAs over the chunk's
+// rows, the same bits as a scalar loop.  A wave owns 2 x 2 of the tile's 4 x 4
+// blocks and loads both operands straight from F in the MFMA layout (lane =
+// row of a group of four x column: 64 contiguous bytes per row and block), four
+// groups at a time with the next four in flight while these are multiplied, so
+// there is no LDS traffic and no barrier; the waves of a workgroup read the
+// same rows from L1.  The block row above a diagonal tile's diagonal is skipped.
+// (One block per wave and sixteen waves per tile measured the same: 72-81 us
+// for 32 to 192 workgroups, 152 against 136 us for 320.)
+// Bound by the FP64 matrix rate (66 TFLOP/s in a large library product here):
+// n = 50,000, r = 500, general L: 811 us as VALU FMAs from LDS tiles with
+// barriers every 32 rows, 299 us now; r = 224, no L: 368 us, 136 us now.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+// w = 1 / L, once per launch of the weighted SYRK: its waves read a row's weight
+// for every block they own, and a division there cost 50 us of 357.
+__global__ __launch_bounds__(256) void reciprocal_kernel(int64_t n, const double* __restrict__ L,
+                                                         double* __restrict__ w) {
+  const int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
+  if (i < n) w[i] = 1.0 / L[i];
+}
+
+template <bool WEIGHTED, bool LISTED>
+__global__ __launch_bounds__(256, 4) void syrk_kernel(const float* __restrict__ F, int64_t nrows, int r,
+                                                                    int64_t ldf, const double* __restrict__ w,
+                                                                    const int* __restrict__ idx, int ntile,
+                                                                    int nsplit, int64_t chunk, double* __restrict__ part) {
+  constexpr int BS = 2;       // a wave's 16 x 16 blocks per side
+  constexpr int NW = 4 / BS;  // waves per tile side
+  constexpr int G = 4;        // groups of four rows in flight
   int ta, tb;
-  tile_coords(blockIdx.x, ta, tb);
-  const int s = blockIdx.y;
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  double acc[4][4];
+  // Workgroups go round the eight XCDs in turn: each XCD gets a run of whole
+  // chunks (all tiles of one before the next), so a chunk's rows of F are
+  // fetched into one L2.
+  const int per = (ntile * nsplit + 7) / 8;
+  const int item = int(blockIdx.x % 8) * per + int(blockIdx.x / 8);
+  if (item >= ntile * nsplit) return;
+  const int split = item / ntile, tile = item % ntile;
+  tile_coords(tile, ta, tb);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int li = lane & 15, lg = lane >> 4;
+  const int wr = wave / NW, wc = wave % NW;  // this wave's blocks: rows BS wr .., columns BS wc ..
+  if (ta == tb && wc > wr) return;           // above the diagonal (no barrier follows)
+  const int64_t k0 = int64_t(split) * chunk, k1 = min(nrows, k0 + chunk);
+  // columns of the two sides: F's clamped ones; U's column r is 1, those beyond 0
+  int ca[BS], cb[BS];
+  float oa[BS], ob[BS];
+  bool fa_ok[BS], fb_ok[BS];
 #pragma unroll
-  for (int p = 0; p < 4; ++p)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) acc[p][q] = 0.0;
-  const int64_t k0 = int64_t(s) * chunk;
-  const int64_t k1 = min(nrows, k0 + chunk);
-  for (int64_t kb = k0; kb < k1; kb += kSubRows) {
-    // the stage's rows and weights first (one lane per row), then every
-    // element load issued unconditionally at a clamped address
-    if (threadIdx.x < kSubRows) {
-      const int64_t kk = kb + threadIdx.x;
-      const int64_t i = kk < k1 ? (idx ? int64_t(idx[kk]) : kk) : -1;
-      rows[threadIdx.x] = i;
-      wts[threadIdx.x] = i < 0 ? 0.0 : (L ? 1.0 / L[i] : 1.0);
-    }
-    __syncthreads();
-    double fa[kSubRows * kT / 256], fb[kSubRows * kT / 256];
-    if (r > 0) {  // the same in every lane; an empty factor (r = 0, F may be null) is never read
-#pragma unroll
-      for (int t = 0; t < kSubRows * kT / 256; ++t) {
-        const int e = int(threadIdx.x) + 256 * t;
-        const int ii = e / kT, k = e % kT;
-        const int64_t ic = rows[ii] < 0 ? 0 : rows[ii];
-        fa[t] = double(F[ic * ldf + min(ta * kT + k, r - 1)]);
-        fb[t] = double(F[ic * ldf + min(tb * kT + k, r - 1)]);
-      }
-    } else {
-#pragma unroll
-      for (int t = 0; t < kSubRows * kT / 256; ++t) fa[t] = fb[t] = 0.0;
-    }
-#pragma unroll
-    for (int t = 0; t < kSubRows * kT / 256; ++t) {
-      const int e = int(threadIdx.x) + 256 * t;
-      const int ii = e / kT, k = e % kT;
-      const int64_t i = rows[ii];
-      const int ca = ta * kT + k, cb = tb * kT + k;
-      const double ua = ca < r ? fa[t] : (ca == r ? 1.0 : 0.0);
-      const double ub = cb < r ? fb[t] : (cb == r ? 1.0 : 0.0);
-      A[ii][k] = i < 0 ? 0.0 : ua * wts[ii];
-      B[ii][k] = i < 0 ? 0.0 : ub;
-    }
-    __syncthreads();
-#pragma unroll 4
-    for (int ii = 0; ii < kSubRows; ++ii) {
-      double av[4], bv[4];
-#pragma unroll
-      for (int p = 0; p < 4; ++p) av[p] = A[ii][ty * 4 + p];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) bv[q] = B[ii][tx * 4 + q];
-#pragma unroll
-      for (int p = 0; p < 4; ++p)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) acc[p][q] = fma(av[p], bv[q], acc[p][q]);
-    }
-    __syncthreads();
+  for (int p = 0; p < BS; ++p) {
+    const int a = ta * kT + 16 * (BS * wr + p) + li, b = tb * kT + 16 * (BS * wc + p) + li;
+    ca[p] = min(a, max(r - 1, 0));
+    cb[p] = min(b, max(r - 1, 0));
+    oa[p] = a == r ? 1.f : 0.f;
+    ob[p] = b == r ? 1.f : 0.f;
+    fa_ok[p] = a < r;
+    fb_ok[p] = b < r;
   }
-  double* out = part + (int64_t(s) * ntile + blockIdx.x) * (kT * kT);
+  f64x4 acc[BS][BS];
 #pragma unroll
-  for (int p = 0; p < 4; ++p)
+  for (int p = 0; p < BS; ++p)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) out[(ty * 4 + p) * kT + tx * 4 + q] = acc[p][q];
+    for (int q = 0; q < BS; ++q) acc[p][q] = f64x4{0.0, 0.0, 0.0, 0.0};
+  float fa[G][BS], fb[G][BS];
+  double wt[G];
+  // offsets of the lane inside a group of four consecutive rows
+  uint32_t oca[BS], ocb[BS];
+#pragma unroll
+  for (int p = 0; p < BS; ++p) {
+    oca[p] = uint32_t(lg) * uint32_t(ldf) + uint32_t(ca[p]);
+    ocb[p] = uint32_t(lg) * uint32_t(ldf) + uint32_t(cb[p]);
+  }
+  int irow[G];  // LISTED: the rows of the next step to load
+  auto list = [&](int64_t kb) {
+#pragma unroll
+    for (int g = 0; g < G; ++g) irow[g] = idx[min(kb + 4 * g + lg, k1 - 1)];
+  };
+  // the step at kb, all of its rows inside the chunk and consecutive: a scalar
+  // base per group and a fixed 32-bit offset per lane (64-bit multiplies per
+  // row took more issue time than the products)
+  auto load_run = [&](int64_t kb) {
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const float* base = F + (kb + 4 * g) * ldf;
+#pragma unroll
+      for (int p = 0; p < BS; ++p) {
+        fa[g][p] = base[oca[p]];
+        fb[g][p] = base[ocb[p]];
+      }
+      if (WEIGHTED) wt[g] = (w + kb + 4 * g)[uint32_t(lg)];
+    }
+  };
+  // the step at kb row by row: listed rows, or the chunk's last step (clamped)
+  auto load_rows = [&](int64_t kb) {
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const uint64_t row = LISTED ? uint64_t(uint32_t(irow[g])) : uint64_t(min(kb + 4 * g + lg, k1 - 1));
+      const float* base = F + row * uint32_t(ldf);
+#pragma unroll
+      for (int p = 0; p < BS; ++p) {
+        fa[g][p] = base[ca[p]];
+        fb[g][p] = base[cb[p]];
+      }
+      if (WEIGHTED) wt[g] = w[row];
+    }
+    if (LISTED) list(kb + 4 * G);
+  };
+  double av[G][BS], bv[G][BS];
+  // the loaded step as FP64 operands; FULL: all of its rows are inside the chunk
+  auto convert = [&](int64_t kb, auto full_c) {
+    constexpr bool FULL = decltype(full_c)::value;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const bool ok = FULL || kb + 4 * g + lg < k1;
+#pragma unroll
+      for (int p = 0; p < BS; ++p) {
+        const float ua = fa_ok[p] ? fa[g][p] : oa[p], ub = fb_ok[p] ? fb[g][p] : ob[p];
+        av[g][p] = ok ? (WEIGHTED ? double(ua) * wt[g] : double(ua)) : 0.0;
+        bv[g][p] = ok ? double(ub) : 0.0;
+      }
+    }
+  };
+  auto multiply = [&]() {
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+      for (int p = 0; p < BS; ++p)
+#pragma unroll
+        for (int q = 0; q < BS; ++q)
+          acc[p][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[g][p], bv[g][q], acc[p][q], 0, 0, 0);
+  };
+  const int64_t kfull = k0 + (k1 - k0) / (4 * G) * (4 * G);  // whole steps
+  int64_t kb = k0;
+  if (LISTED) list(k0);
+  if (!LISTED && kfull > k0) load_run(k0);
+  else load_rows(k0);
+  for (; kb + 4 * G < kfull; kb += 4 * G) {
+    convert(kb, std::true_type{});
+    if (LISTED) load_rows(kb + 4 * G);
+    else load_run(kb + 4 * G);
+    multiply();
+  }
+  if (kb < kfull) {  // the last whole step
+    convert(kb, std::true_type{});
+    kb += 4 * G;
+    if (kb < k1) load_rows(kb);
+    multiply();
+  }
+  if (kb < k1) {
+    convert(kb, std::false_type{});
+    multiply();
+  }
+  // D of the MFMA: element v of a lane is row 4 v + lane / 16, column lane % 16
+  double* out = part + (int64_t(split) * ntile + tile) * (kT * kT);
+#pragma unroll
+  for (int p = 0; p < BS; ++p)
+#pragma unroll
+    for (int q = 0; q < BS; ++q)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        out[(16 * (BS * wr + p) + 4 * v + lg) * kT + 16 * (BS * wc + q) + li] = acc[p][q][v];
 }
 
 // C[a][b] (b <= a < R1) = diag(I_r, 1/c)[a][b] + alpha G[a][b] + beta sum_s part[s][tile]
-// G (optional) is a lower-triangular R1 x R1 matrix with leading dimension ldc.
+// (chunks in order).  G (optional) is a lower-triangular R1 x R1 matrix with
+// leading dimension ldc.  kCombine workgroups per tile, four rows of it each:
+// with one per tile, 36 workgroups read 33 MB of partials at r = 500 (110 us,
+// 7 us now).
+constexpr int kCombine = kT * kT / 256;
+
 __global__ __launch_bounds__(256) void syrk_combine_kernel(const double* __restrict__ part, int nsplit, int ntile,
                                                            int r, int R1, double diag_r, double diag_last,
                                                            const double* __restrict__ G, double alpha, double beta,
                                                            double* __restrict__ C, int64_t ldc) {
   int ta, tb;
-  tile_coords(blockIdx.x, ta, tb);
-  for (int e = threadIdx.x; e < kT * kT; e += 256) {
-    const int a = ta * kT + e / kT, b = tb * kT + e % kT;
-    if (a >= R1 || b > a) continue;
-    double s = 0.0;
-    for (int k = 0; k < nsplit; ++k) s += part[(int64_t(k) * ntile + blockIdx.x) * (kT * kT) + e];
-    double v = beta * s;
-    if (G) v = fma(alpha, G[int64_t(a) * ldc + b], v);
-    if (a == b) v += (a < r) ? diag_r : diag_last;
-    C[int64_t(a) * ldc + b] = v;
-  }
+  const int tile = int(blockIdx.x) / kCombine;
+  tile_coords(tile, ta, tb);
+  const int e = int(blockIdx.x) % kCombine * 256 + int(threadIdx.x);
+  const int a = ta * kT + e / kT, b = tb * kT + e % kT;
+  if (a >= R1 || b > a) return;
+  double s = 0.0;
+#pragma unroll 8
+  for (int k = 0; k < nsplit; ++k) s += part[(int64_t(k) * ntile + tile) * (kT * kT) + e];
+  double v = beta * s;
+  if (G) v = fma(alpha, G[int64_t(a) * ldc + b], v);
+  if (a == b) v += (a < r) ? diag_r : diag_last;
+  C[int64_t(a) * ldc + b] = v;
 }
 
 // ---------------------------------------------------------------- interior index list
@@ -901,12 +990,27 @@ void Woodbury::syrk(const double* L, const int* idx, int64_t nrows, double* G, d
     int64_t chunk = (nrows + nsplit - 1) / nsplit;
     chunk = std::max<int64_t>(kSubRows, (chunk + kSubRows - 1) / kSubRows * kSubRows);
     nsplit = int(std::max<int64_t>(1, (nrows + chunk - 1) / chunk));
-    syrk_kernel<<<dim3(ntile, nsplit), 256, 0, st>>>(F_, nrows, int(r_), ldf_, L, idx, ntile, chunk,
-                                                     part_.as<double>());
+    const unsigned grid = unsigned(ntile * nsplit + 7) / 8 * 8;
+    double* part = part_.as<double>();
+    // an empty factor has no rows to read: the kernel's loads (whose values it
+    // then drops for U's constant column) go to valid memory instead
+    const float* F = r_ > 0 ? F_ : part_.as<float>();
+    const int64_t ldf = r_ > 0 ? ldf_ : 0;
+    double* w = g_.as<double>();  // n doubles, written by every apply before it reads them
+    if (L) {
+      reciprocal_kernel<<<unsigned((nrows + 255) / 256), 256, 0, st>>>(nrows, L, w);
+      KQR_LAUNCH_CHECK();
+    }
+#define KQR_SYRK(W, I) \
+  syrk_kernel<W, I><<<grid, 256, 0, st>>>(F, nrows, int(r_), ldf, w, idx, ntile, nsplit, chunk, part)
+    if (L) KQR_SYRK(true, false);
+    else if (idx) KQR_SYRK(false, true);
+    else KQR_SYRK(false, false);
+#undef KQR_SYRK
     KQR_LAUNCH_CHECK();
   }
-  syrk_combine_kernel<<<ntile, 256, 0, st>>>(part_.as<double>(), nsplit, ntile, int(r_), R1, diag_r, diag_last, G,
-                                             alpha, beta, out, ldc_);
+  syrk_combine_kernel<<<ntile * kCombine, 256, 0, st>>>(part_.as<double>(), nsplit, ntile, int(r_), R1, diag_r,
+                                                        diag_last, G, alpha, beta, out, ldc_);
   KQR_LAUNCH_CHECK();
 }
 

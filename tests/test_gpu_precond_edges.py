@@ -1,0 +1,47 @@
+"""GPU checks of the preconditioner kernels at the sizes where their tiles end."""
+import sys
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2510_07929_amd import kqr
+
+pytestmark = pytest.mark.gpu
+
+
+def say(*a):
+    print("[gpu-test]", *a, flush=True)
+    sys.stdout.flush()
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    kqr.lib()
+    return torch.device("cuda:0")
+
+
+@pytest.mark.parametrize("n,r", [(1, 0), (7, 0), (3, 2), (31, 1), (33, 15), (64, 16), (65, 63), (500, 64), (1000, 127),
+                                 (1025, 128), (4097, 200), (9000, 447), (20001, 500)])
+def test_woodbury_core_at_tile_edges(dev, n, r):
+    """P^{-1} w against a dense FP64 solve of the core, at ranks around the 64-entry tiles of its weighted
+    Gram matrix and row counts around the groups of its chunks."""
+    rng = np.random.default_rng((n, r))
+    F = np.zeros((n, max(4, (r + 3) // 4 * 4)), dtype=np.float32)
+    F[:, :r] = rng.standard_normal((n, r)) / np.sqrt(max(r, 1))
+    F[:, r:] = np.nan  # padding columns are not part of the factor
+    L = rng.uniform(0.5, 2.0, n)
+    w = rng.standard_normal(n)
+    c = 0.75
+    say("woodbury", n, r)
+    out = kqr.kqr_woodbury_apply(torch.from_numpy(F).to(dev), r, c, torch.from_numpy(L).to(dev),
+                                 torch.from_numpy(w).to(dev)).cpu().numpy()
+    U = np.concatenate([F[:, :r].astype(np.float64), np.ones((n, 1))], 1)
+    core = np.diag(np.r_[np.ones(r), 1.0 / c]) + U.T @ (U / L[:, None])
+    ref = (w - U @ np.linalg.solve(core, U.T @ (w / L))) / L
+    # forward error of an SPD solve: (terms of a sum) x unit roundoff x condition of the core
+    tol = (n + r + 1) * 2.0 ** -53 * np.linalg.cond(core)
+    assert np.linalg.norm(out - ref) <= tol * np.linalg.norm(w / L)
