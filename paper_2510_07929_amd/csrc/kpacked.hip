@@ -6,6 +6,7 @@
 // nt = ceil(n / kPkT), each tile row-major and zero beyond n.  A K-apply then
 // streams about n^2 / 2 entries instead of n^2: every off-diagonal tile feeds
 // its rows (K_IJ v_J) and its columns (K_IJ^T v_I).
+#include "reduce.h"
 #include "kernel_entry.h"
 #include "kqr_internal.h"
 
@@ -350,32 +351,6 @@ __global__ __launch_bounds__(256) void kapply_packed_cols_kernel(const void* __r
 // writes, mixed into the read stream, are what held the strip maps back.
 //   rowpart: (I nb + BJ) kPkT + r   (the row sums of tile-row I in block column BJ)
 //   colpart: (BI nt + J) kPkT + c   (the column sums of tile-column J in block row BI)
-template <int CTRL>
-__device__ __forceinline__ double pk_dpp(double x) {
-  const uint64_t u = __builtin_bit_cast(uint64_t, x);
-  const int lo = __builtin_amdgcn_update_dpp(0, int(uint32_t(u)), CTRL, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, int(uint32_t(u >> 32)), CTRL, 0xF, 0xF, false);
-  return __builtin_bit_cast(double, (uint64_t(uint32_t(hi)) << 32) | uint32_t(lo));
-}
-
-// x + the value of the lane 16 (SWAP16) or 32 lanes away, the same on both lanes
-template <bool SWAP16>
-__device__ __forceinline__ double pk_swap_sum(double x) {
-  const uint64_t u = __builtin_bit_cast(uint64_t, x);
-  const uint32_t l = uint32_t(u), h = uint32_t(u >> 32);
-  uint32_t l0, l1, h0, h1;
-  if constexpr (SWAP16) {
-    const auto a = __builtin_amdgcn_permlane16_swap(l, l, false, false);
-    const auto b = __builtin_amdgcn_permlane16_swap(h, h, false, false);
-    l0 = a[0]; l1 = a[1]; h0 = b[0]; h1 = b[1];
-  } else {
-    const auto a = __builtin_amdgcn_permlane32_swap(l, l, false, false);
-    const auto b = __builtin_amdgcn_permlane32_swap(h, h, false, false);
-    l0 = a[0]; l1 = a[1]; h0 = b[0]; h1 = b[1];
-  }
-  return __builtin_bit_cast(double, (uint64_t(h0) << 32) | l0) + __builtin_bit_cast(double, (uint64_t(h1) << 32) | l1);
-}
-
 template <bool BF16, bool EXACT, int B, bool WIDE>
 __global__ __launch_bounds__(256) void kapply_packed_blocks_kernel(const void* __restrict__ Kp, int64_t n,
                                                                    int64_t nt, int64_t nb,
@@ -477,7 +452,7 @@ __global__ __launch_bounds__(256) void kapply_packed_blocks_kernel(const void* _
       double t = 0.0;
 #pragma unroll
       for (int k = 0; k < NPART / 2; ++k) t += rs[half * (NPART / 2) + k][row];
-      t += pk_dpp<0xB1>(t);  // quad_perm [1, 0, 3, 2]: the other half of the row
+      t += dpp_f64<0xB1>(t);  // quad_perm [1, 0, 3, 2]: the other half of the row
       if (half == 0) rowpart[(size_t(I) * nb + BJ) * kPkT + row] = t;
     }
     __syncthreads();  // rs is rewritten by the next tile-row
@@ -490,10 +465,10 @@ __global__ __launch_bounds__(256) void kapply_packed_blocks_kernel(const void* _
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
       double t = cold[jj][e];
-      if (LPW <= 4) t += pk_dpp<0x124>(t);  // row_ror:4
-      if (LPW <= 8) t += pk_dpp<0x128>(t);  // row_ror:8
-      t = pk_swap_sum<true>(t);
-      t = pk_swap_sum<false>(t);
+      if (LPW <= 4) t += dpp_f64<0x124>(t);  // row_ror:4
+      if (LPW <= 8) t += dpp_f64<0x128>(t);  // row_ror:8
+      t = swap_sum_f64<true>(t);
+      t = swap_sum_f64<false>(t);
       if (RW == 1) {
         if (g == 0 && J < nt) colpart[(size_t(BI) * nt + J) * kPkT + chunk * VEC + e] = t;
       } else if (g == 0) {

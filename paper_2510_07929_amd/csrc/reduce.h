@@ -5,6 +5,45 @@
 
 namespace kqr {
 
+// x of another lane by DPP.  0xB1: lane ^ 1; 0x4E: lane ^ 2; 0x141: lane ^ 7
+// (row_half_mirror); 0x140: lane ^ 15 (row_mirror); 0x124 / 0x128: the lane 4 /
+// 8 further round its row of 16.
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double x) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, x);
+  const int lo = __builtin_amdgcn_update_dpp(0, int(uint32_t(u)), CTRL, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, int(uint32_t(u >> 32)), CTRL, 0xF, 0xF, false);
+  return __builtin_bit_cast(double, (uint64_t(uint32_t(hi)) << 32) | uint32_t(lo));
+}
+
+// x + the value of the lane 16 (SWAP16) or 32 lanes away, the same on both lanes
+template <bool SWAP16>
+__device__ __forceinline__ double swap_sum_f64(double x) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, x);
+  const uint32_t l = uint32_t(u), h = uint32_t(u >> 32);
+  uint32_t l0, l1, h0, h1;
+  if constexpr (SWAP16) {
+    const auto a = __builtin_amdgcn_permlane16_swap(l, l, false, false);
+    const auto b = __builtin_amdgcn_permlane16_swap(h, h, false, false);
+    l0 = a[0]; l1 = a[1]; h0 = b[0]; h1 = b[1];
+  } else {
+    const auto a = __builtin_amdgcn_permlane32_swap(l, l, false, false);
+    const auto b = __builtin_amdgcn_permlane32_swap(h, h, false, false);
+    l0 = a[0]; l1 = a[1]; h0 = b[0]; h1 = b[1];
+  }
+  return __builtin_bit_cast(double, (uint64_t(h0) << 32) | l0) + __builtin_bit_cast(double, (uint64_t(h1) << 32) | l1);
+}
+
+// Sum of x over the wave, the same in every lane, without LDS traffic.
+__device__ __forceinline__ double wave_sum_f64(double x) {
+  x += dpp_f64<0xB1>(x);
+  x += dpp_f64<0x4E>(x);
+  x += dpp_f64<0x141>(x);
+  x += dpp_f64<0x140>(x);
+  x = swap_sum_f64<true>(x);
+  return swap_sum_f64<false>(x);
+}
+
 // out[q] = sum over b < nblocks of partials[b nq + q], in a fixed order (one
 // 256-thread block).
 __device__ __forceinline__ void finish_sums(const double* __restrict__ partials, int nblocks, int nq,

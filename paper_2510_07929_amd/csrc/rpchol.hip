@@ -17,10 +17,12 @@
 // bisection with Sturm counts, and the number of eigenvalues above
 // xi lambda_1 by one more Sturm count.
 #include "kernel_entry.h"
+#include "reduce.h"
 #include "vec.h"
 
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 
 namespace kqr {
 
@@ -320,43 +322,247 @@ __global__ __launch_bounds__(1024) void tridiag_kernel(const double* __restrict_
   (void)bc;
 }
 
-// Number of eigenvalues below x of the symmetric tridiagonal (d, e) (Sturm count).
-__device__ int sturm_below(const double* d, const double* e, int m, double x, double tiny) {
-  int c = 0;
-  double qv = d[0] - x;
-  if (qv < 0.0) ++c;
+// The same for m <= kTriRegs with the matrix in registers (kTriRegs^2 doubles
+// are 392 of the 512 KB of vector registers of a CU): thread (ti, tj) of a
+// 16 x 32 grid holds A[ti + 16 a][tj + 32 b].  Per step, row k goes through LDS
+// to every thread, each thread multiplies its block of the trailing matrix by
+// its seven entries of v, the row sums are added over the 32 tj lanes by
+// halving exchanges (16 of them for 14 rows), and the rank-two update stays in
+// registers.  The sums of squares and v . p are formed by every wave alike, so
+// a step has two barriers.  The step loop is instantiated per 32-row block of
+// the front, which fixes the live register blocks.  Bound by the chain of one
+// step (two barriers, one square root, one division, four LDS round trips);
+// m = 224: 4443 us with the matrix streamed from L2 in each step (1.2 MB through
+// one CU), 476 us here.
+constexpr int kTriRegs = 224;
+constexpr int kTriThreads = 512;
+
+__global__ __launch_bounds__(kTriThreads) void tridiag_regs_kernel(const double* __restrict__ G, int64_t ldg, int m,
+                                                                   double* __restrict__ dg, double* __restrict__ eg) {
+  constexpr int NA = kTriRegs / 16, NB = kTriRegs / 32;
+  __shared__ double col[2][256];  // row k, by the parity of k
+  __shared__ double pw[2][256];   // p = (2 / vv) A22 v
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int ti = tid >> 5, tj = tid & 31;
+  double A[NA][NB];
+#pragma unroll
+  for (int a = 0; a < NA; ++a)
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const int i = ti + 16 * a, j = tj + 32 * b;
+      const int ic = min(max(i, j), m - 1), jc = min(min(i, j), m - 1);
+      const double g = G[int64_t(ic) * ldg + jc];
+      A[a][b] = i < m && j < m ? g : 0.0;
+    }
+  for (int e = tid; e < 512; e += kTriThreads) {
+    col[e >> 8][e & 255] = 0.0;
+    pw[e >> 8][e & 255] = 0.0;
+  }
+  __syncthreads();
+  auto front = [&](auto kb_c) {
+    constexpr int KB = decltype(kb_c)::value;
+    for (int kk = 0; kk < 32; ++kk) {
+      const int k = 32 * KB + kk;
+      if (k + 2 >= m) return;
+      double* c = col[k & 1];
+      double* pb = pw[k & 1];
+      if (ti == (kk & 15)) {  // row k: register row 2 KB or 2 KB + 1
+        if (kk < 16) {
+#pragma unroll
+          for (int b = KB; b < NB; ++b) c[tj + 32 * b] = A[2 * KB][b];
+        } else {
+#pragma unroll
+          for (int b = KB; b < NB; ++b) c[tj + 32 * b] = A[2 * KB + 1][b];
+        }
+      }
+      __syncthreads();
+      // x = row k right of the diagonal (zero past m); every wave forms ||x||^2
+      double x[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int j = lane + 64 * q;
+        const double t = c[j];
+        x[q] = j > k ? t : 0.0;
+      }
+      const double xx = wave_sum_f64(fma(x[3], x[3], fma(x[2], x[2], fma(x[1], x[1], x[0] * x[0]))));
+      const double x0 = c[k + 1];
+      if (tid == 0) dg[k] = c[k];
+      if (!(xx > 0.0)) {  // the same in every thread
+        if (tid == 0) eg[k] = 0.0;
+        continue;
+      }
+      const double alpha = x0 >= 0.0 ? -sqrt(xx) : sqrt(xx);
+      const double inv = 1.0 / (2.0 * (xx - x0 * alpha));  // 1 / ||x - alpha e1||^2
+      if (tid == 0) eg[k] = alpha;
+      auto v_at = [&](int j) {
+        const double t = c[j];
+        return j <= k ? 0.0 : (j == k + 1 ? t - alpha : t);
+      };
+      double vc[NB];
+#pragma unroll
+      for (int b = KB; b < NB; ++b) vc[b] = v_at(tj + 32 * b);
+      auto row_part = [&](int a) {  // this thread's part of the product of row ti + 16 a
+        double t = 0.0;
+        if (a >= 2 * KB && a < NA) {
+#pragma unroll
+          for (int b = KB; b < NB; ++b) t = fma(A[a][b], vc[b], t);
+        }
+        return t;
+      };
+      // sum over tj: each exchange halves the rows a lane carries; the lane ends
+      // with row a = 8 bit4 + 4 bit3 + 2 bit2 + bit0 of its lane number
+      double s[8];
+#pragma unroll
+      for (int a = 0; a < 8; ++a) {
+        const uint64_t u = __builtin_bit_cast(uint64_t, row_part(a)), w = __builtin_bit_cast(uint64_t, row_part(a + 8));
+        const auto l = __builtin_amdgcn_permlane16_swap(uint32_t(u), uint32_t(w), false, false);
+        const auto h = __builtin_amdgcn_permlane16_swap(uint32_t(u >> 32), uint32_t(w >> 32), false, false);
+        s[a] = __builtin_bit_cast(double, (uint64_t(h[0]) << 32) | l[0]) +
+               __builtin_bit_cast(double, (uint64_t(h[1]) << 32) | l[1]);
+      }
+      const bool b3 = lane & 8, b2 = lane & 4, b0 = lane & 1;
+#pragma unroll
+      for (int a = 0; a < 4; ++a) s[a] = (b3 ? s[a + 4] : s[a]) + dpp_f64<0x128>(b3 ? s[a] : s[a + 4]);
+#pragma unroll
+      for (int a = 0; a < 2; ++a) s[a] = (b2 ? s[a + 2] : s[a]) + dpp_f64<0x141>(b2 ? s[a] : s[a + 2]);
+      double p = (b0 ? s[1] : s[0]) + dpp_f64<0xB1>(b0 ? s[0] : s[1]);
+      p += dpp_f64<0x4E>(p);
+      const int arow = ((lane >> 1) & 8) | ((lane >> 1) & 4) | ((lane >> 1) & 2) | (lane & 1);
+      if (!(lane & 2) && arow >= 2 * KB && arow < NA) pb[ti + 16 * arow] = (2.0 * inv) * p;
+      __syncthreads();
+      // w = p - Kc v with Kc = (v . p) / ||v||^2, formed by every wave
+      double dot = 0.0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int j = lane + 64 * q;
+        dot = fma(j == k + 1 ? x[q] - alpha : x[q], pb[j], dot);
+      }
+      const double Kc = wave_sum_f64(dot) * inv;
+      double wc[NB];
+#pragma unroll
+      for (int b = KB; b < NB; ++b) {
+        const int j = tj + 32 * b;
+        const double t = pb[j];
+        wc[b] = j > k ? fma(-Kc, vc[b], t) : 0.0;
+      }
+      // A22 -= v w^T + w v^T
+#pragma unroll
+      for (int a = 2 * KB; a < NA; ++a) {
+        const int i = ti + 16 * a;
+        const double vr = v_at(i);
+        const double t = pb[i];
+        const double wr = i > k ? fma(-Kc, vr, t) : 0.0;
+#pragma unroll
+        for (int b = KB; b < NB; ++b) A[a][b] = fma(-vr, wc[b], fma(-wr, vc[b], A[a][b]));
+      }
+    }
+  };
+  front(std::integral_constant<int, 0>{});
+  front(std::integral_constant<int, 1>{});
+  front(std::integral_constant<int, 2>{});
+  front(std::integral_constant<int, 3>{});
+  front(std::integral_constant<int, 4>{});
+  front(std::integral_constant<int, 5>{});
+  front(std::integral_constant<int, 6>{});
+#pragma unroll
+  for (int a = 0; a < NA; ++a)
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const int i = ti + 16 * a, j = tj + 32 * b;
+      if (i == j && i < m && i + 2 >= m) dg[i] = A[a][b];
+      if (i == m - 1 && j == m - 2) eg[j] = A[a][b];
+    }
+}
+
+// Number of eigenvalues below x of the symmetric tridiagonal with diagonal d
+// and squared off-diagonal e2 (Sturm count), entries of magnitude at most
+// about 1.  The quotient uses v_rcp_f64 and two Newton steps (|q| >= 1e-18, so
+// nothing overflows): a third of the latency of the rounded division in this
+// serial chain, and an error of a unit in the last place only shifts the
+// matrix's entries by as much.
+__device__ __forceinline__ int sturm_below(const double* d, const double* e2, int m, double x) {
+  constexpr double tiny = 1e-18;
+  double q = d[0] - x;
+  int c = q < 0.0;
   for (int i = 1; i < m; ++i) {
-    if (fabs(qv) < tiny) qv = -tiny;
-    qv = d[i] - x - e[i - 1] * e[i - 1] / qv;
-    if (qv < 0.0) ++c;
+    if (fabs(q) < tiny) q = -tiny;
+    double y = __builtin_amdgcn_rcp(q);
+    y = fma(fma(-q, y, 1.0), y, y);
+    y = fma(fma(-q, y, 1.0), y, y);
+    q = fma(-e2[i - 1], y, d[i] - x);
+    c += q < 0.0;
   }
   return c;
 }
 
-// out[0] = r (as double), out[1] = lambda_1
-__global__ void rank_from_tridiag_kernel(const double* __restrict__ d, const double* __restrict__ e, int m, double xi,
-                                         double* __restrict__ out) {
-  if (threadIdx.x != 0) return;
-  double lo = 0.0, hi = 0.0;
-  for (int i = 0; i < m; ++i) {
-    const double rad = (i > 0 ? fabs(e[i - 1]) : 0.0) + (i + 1 < m ? fabs(e[i]) : 0.0);
-    lo = fmin(lo, d[i] - rad);
-    hi = fmax(hi, d[i] + rad);
+// out[0] = r (as double), out[1] = lambda_1.  One workgroup: each of the 256
+// threads counts at its own point, so a pass cuts the interval of lambda_1 by
+// 257 (seven passes over the recurrence where bisection takes about fifty).
+// m = 224: 1065 us by bisection in one thread, 99 us here.
+__global__ __launch_bounds__(256) void rank_from_tridiag_kernel(const double* __restrict__ dg,
+                                                                const double* __restrict__ eg, int m, double xi,
+                                                                double* __restrict__ out) {
+  __shared__ double d[1024], e2[1024];
+  __shared__ double red[3][256];
+  __shared__ int first[4];
+  const int t = threadIdx.x;
+  // Gershgorin bounds and the largest diagonal entry (lambda_1 is at least that)
+  double lo = 0.0, hi = 0.0, top = -INFINITY;
+  for (int i = t; i < m; i += 256) {
+    const double di = dg[i];
+    const double rad = (i > 0 ? fabs(eg[i - 1]) : 0.0) + (i + 1 < m ? fabs(eg[i]) : 0.0);
+    lo = fmin(lo, di - rad);
+    hi = fmax(hi, di + rad);
+    top = fmax(top, di);
   }
-  const double tiny = 1e-300 + 1e-18 * fmax(fabs(lo), fabs(hi));
-  // lambda_1: smallest x with no eigenvalue above it
-  double a = lo, b = hi;
-  for (int it = 0; it < 200 && b - a > 1e-15 * fmax(fabs(a), fabs(b)); ++it) {
-    const double mid = 0.5 * (a + b);
-    if (sturm_below(d, e, m, mid, tiny) >= m) b = mid;
-    else a = mid;
+  red[0][t] = lo;
+  red[1][t] = hi;
+  red[2][t] = top;
+  __syncthreads();
+  for (int off = 128; off >= 1; off >>= 1) {
+    if (t < off) {
+      red[0][t] = fmin(red[0][t], red[0][t + off]);
+      red[1][t] = fmax(red[1][t], red[1][t + off]);
+      red[2][t] = fmax(red[2][t], red[2][t + off]);
+    }
+    __syncthreads();
   }
-  const double lam1 = b;
-  const int below = sturm_below(d, e, m, xi * lam1, tiny);  // #{lambda < xi lambda_1}
-  int r = m - below + 1;                                     // smallest r with lambda_r <= xi lambda_1
-  if (r > m) r = m;
-  out[0] = double(r);
-  out[1] = lam1;
+  lo = red[0][0];
+  hi = red[1][0];
+  top = red[2][0];
+  // scaled by a power of two (exact) so that the largest bound is in [1, 2)
+  const double big = fmax(fabs(lo), fabs(hi));
+  const int ex = big > 0.0 && isfinite(big) ? ilogb(big) : 0;
+  for (int i = t; i < m; i += 256) {
+    d[i] = ldexp(dg[i], -ex);
+    if (i + 1 < m) {
+      const double e = ldexp(eg[i], -ex);
+      e2[i] = e * e;
+    }
+  }
+  __syncthreads();
+  double a = fmax(ldexp(lo, -ex), ldexp(top, -ex)), b = ldexp(hi, -ex);
+  for (int it = 0; it < 40 && b - a > 1e-15 * fmax(fabs(a), fabs(b)); ++it) {
+    const double h = (b - a) / 257.0;
+    const double x = fma(double(t + 1), h, a);
+    const unsigned long long hit = __ballot(sturm_below(d, e2, m, x) >= m);  // x at or above lambda_1
+    if ((t & 63) == 0) first[t >> 6] = hit ? __ffsll((long long)hit) - 1 : 64;
+    __syncthreads();
+    int f = 256;
+    for (int w = 3; w >= 0; --w)
+      if (first[w] < 64) f = 64 * w + first[w];
+    const double nb = f < 256 ? fma(double(f + 1), h, a) : b;
+    const double na = f > 0 ? fma(double(f), h, a) : a;
+    __syncthreads();
+    if (na == a && nb == b) break;  // the same in every thread
+    a = na;
+    b = nb;
+  }
+  if (t == 0) {
+    const int below = sturm_below(d, e2, m, xi * b);  // #{lambda < xi lambda_1}
+    out[0] = double(min(m - below + 1, m));           // smallest r with lambda_r <= xi lambda_1
+    out[1] = ldexp(b, ex);
+  }
 }
 
 Co<int64_t> adaptive_rank(const float* F0, int64_t n, int64_t r0, int64_t ldf, double xi, Exec& ex,
@@ -366,12 +572,19 @@ Co<int64_t> adaptive_rank(const float* F0, int64_t n, int64_t r0, int64_t ldf, d
   Woodbury W(F0, n, r0, ldf);
   const double* G = W.gram(st);  // (r0+1)^2 lower triangle of [F0 1]^T [F0 1]
   const int m = int(r0);
-  DevBuf A(size_t(m) * m * sizeof(double)), v(size_t(m) * sizeof(double)), w(size_t(m) * sizeof(double));
   DevBuf dg(size_t(m) * sizeof(double)), eg(size_t(m) * sizeof(double)), out(2 * sizeof(double));
-  tridiag_kernel<<<1, 1024, 0, st>>>(G, r0 + 1, m, A.as<double>(), v.as<double>(), w.as<double>(), dg.as<double>(),
-                                     eg.as<double>());
+  DevBuf A, v, w;
+  if (m <= kTriRegs) {
+    tridiag_regs_kernel<<<1, kTriThreads, 0, st>>>(G, r0 + 1, m, dg.as<double>(), eg.as<double>());
+  } else {  // more than the registers hold
+    A.alloc(size_t(m) * m * sizeof(double));
+    v.alloc(size_t(m) * sizeof(double));
+    w.alloc(size_t(m) * sizeof(double));
+    tridiag_kernel<<<1, 1024, 0, st>>>(G, r0 + 1, m, A.as<double>(), v.as<double>(), w.as<double>(), dg.as<double>(),
+                                       eg.as<double>());
+  }
   KQR_LAUNCH_CHECK();
-  rank_from_tridiag_kernel<<<1, 64, 0, st>>>(dg.as<double>(), eg.as<double>(), m, xi, out.as<double>());
+  rank_from_tridiag_kernel<<<1, 256, 0, st>>>(dg.as<double>(), eg.as<double>(), m, xi, out.as<double>());
   KQR_LAUNCH_CHECK();
   double h[2];
   co_await read_back(ex, out.ptr, 2 * sizeof(double), h);

@@ -45,3 +45,37 @@ def test_woodbury_core_at_tile_edges(dev, n, r):
     # forward error of an SPD solve: (terms of a sum) x unit roundoff x condition of the core
     tol = (n + r + 1) * 2.0 ** -53 * np.linalg.cond(core)
     assert np.linalg.norm(out - ref) <= tol * np.linalg.norm(w / L)
+
+
+@pytest.mark.parametrize("r", [2, 3, 16, 17, 32, 33, 64, 65, 97, 223, 224, 225])
+def test_rank_rule_at_register_block_edges(dev, r):
+    """lambda_1 and the rank of F0^T F0 against LAPACK's eigenvalues, at orders around the 16- and 32-entry
+    blocks of the tridiagonalisation and where its matrix leaves the registers."""
+    rng = np.random.default_rng(r)
+    n = 2 * r + 5
+    q, _ = np.linalg.qr(rng.standard_normal((n, r)))
+    p, _ = np.linalg.qr(rng.standard_normal((r, r)))
+    F = np.zeros((n, (r + 3) // 4 * 4), dtype=np.float32)
+    F[:, :r] = q @ np.diag(10.0 ** -np.linspace(0.0, 4.0, r)) @ p  # eigenvalues 1 .. 1e-8
+    say("rank rule", r)
+    xi = 1e-5
+    rank, top = kqr.kqr_adaptive_rank(torch.from_numpy(F).to(dev), r, xi)
+    F64 = F[:, :r].astype(np.float64)
+    ev = np.linalg.eigvalsh(F64.T @ F64)[::-1]
+    # backward error of forming and reducing the matrix: n r units of its norm
+    tol = n * r * 2.0 ** -53
+    assert abs(top - ev[0]) <= tol * ev[0]
+    below = np.nonzero(ev <= xi * ev[0])[0]
+    want = int(below[0]) + 1 if below.size else r
+    if rank != want:  # an eigenvalue within rounding of the threshold may count either way
+        assert np.min(np.abs(ev - xi * ev[0])) <= tol * ev[0], (rank, want)
+
+
+@pytest.mark.parametrize("diag", [(1.0, 1.0, 1.0, 1.0), (2.0, 0.0, 0.0, 0.0), (0.0, 0.0, 0.0, 0.0)])
+def test_rank_rule_of_diagonal_gram_matrices(dev, diag):
+    """Zero reflections throughout: equal eigenvalues, a single one, and the zero matrix."""
+    F = np.zeros((6, 4), dtype=np.float32)
+    F[:4, :4] = np.diag(diag)
+    rank, top = kqr.kqr_adaptive_rank(torch.from_numpy(F).to(dev), 4, 1e-3)
+    assert top == max(diag) ** 2
+    assert rank == (2 if diag[1] == 0.0 and diag[0] > 0.0 else 4)
