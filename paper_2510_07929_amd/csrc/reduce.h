@@ -5,6 +5,13 @@
 
 namespace kqr {
 
+// x of one lane in every lane
+__device__ __forceinline__ double readlane_f64(double x, int lane) {
+  const int lo = __builtin_amdgcn_readlane(__double2loint(x), lane);
+  const int hi = __builtin_amdgcn_readlane(__double2hiint(x), lane);
+  return __hiloint2double(hi, lo);
+}
+
 // x of another lane by DPP.  0xB1: lane ^ 1; 0x4E: lane ^ 2; 0x141: lane ^ 7
 // (row_half_mirror); 0x140: lane ^ 15 (row_mirror); 0x124 / 0x128: the lane 4 /
 // 8 further round its row of 16.

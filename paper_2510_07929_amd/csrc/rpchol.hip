@@ -5,11 +5,11 @@
 //   s    = first j with sum_{l<=j} d_l > u_i * sum(d)  (pivot ~ residual diagonal)
 //   g    = K[:, s] - F[:, :i] F[s, :i]^T
 //   F[:, i] = g / sqrt(g_s),  d <- max(d - F[:, i]^2, 0),  d_s <- 0
-// Everything stays on the device: the pivot is found by a one-wave scan over
-// block sums that the previous step's update kernel produced, the correction
-// F[:, :i] F[s, :i]^T is the streamed mat-vec of the K-apply with F as the
-// matrix, and the early stop (sum(d) <= 1e-14 tr K) is a device flag, so the
-// host synchronises once at the end.
+// Everything stays on the device, one launch per step: the pivot is found by a
+// one-wave scan over block sums that the previous step produced, the
+// correction F[:, :i] F[s, :i]^T streams F, and the early stop
+// (sum(d) <= 1e-14 tr K) is a device flag, so the host synchronises once at
+// the end.
 //
 // Rank heuristic: r0 = ceil(sqrt n), eigenvalues of F0^T F0, r = smallest index
 // with lambda_r <= xi lambda_1.  F0^T F0 is reduced to tridiagonal form by
@@ -44,12 +44,13 @@ __global__ __launch_bounds__(256) void rpc_blocksum_kernel(const double* __restr
   if (threadIdx.x == 0) bsum[blockIdx.x] = ((sh[0] + sh[1]) + sh[2]) + sh[3];
 }
 
-// One wave.  state[0] = tr K (set at step 0), state[1] = stopped flag.
-// Writes piv[step] = pivot, or -1 once the residual trace is negligible.
-__global__ __launch_bounds__(64) void rpc_select_kernel(const double* __restrict__ d, int64_t n, int64_t chunk,
-                                                        const double* __restrict__ bsum, int nblk, double u, int step,
-                                                        int64_t* __restrict__ piv, double* __restrict__ state) {
-  const int lane = threadIdx.x;
+// The pivot draw, by one wave: first j with sum_{l<=j} d_l > u * sum(d), or -1
+// once the residual trace is negligible.  state[0] = tr K (set at step 0),
+// state[1] = stopped flag; tr0 and stop return their new values.
+__device__ __forceinline__ int64_t rpc_select(const double* __restrict__ d, int64_t n, int64_t chunk,
+                                              const double* __restrict__ bsum, int nblk, double u, int step,
+                                              const double* __restrict__ state, double& tr0, bool& stop) {
+  const int lane = threadIdx.x & 63;
   // prefix sums of the block sums: lane l owns blocks [PER l, PER l + PER)
   constexpr int PER = kSelBlocks / 64;
   double bs[PER];
@@ -57,9 +58,11 @@ __global__ __launch_bounds__(64) void rpc_select_kernel(const double* __restrict
 #pragma unroll
   for (int q = 0; q < PER; ++q) {
     const int b = lane * PER + q;
-    bs[q] = b < nblk ? bsum[b] : 0.0;
+    const double v = bsum[min(b, nblk - 1)];
+    bs[q] = b < nblk ? v : 0.0;
     own += bs[q];
   }
+  const double st0 = state[0], st1 = state[1];
   double incl = own;
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) {
@@ -67,9 +70,8 @@ __global__ __launch_bounds__(64) void rpc_select_kernel(const double* __restrict
     if (lane >= off) incl += t;
   }
   const double total = __shfl(incl, 63);
-  bool stop = state[1] != 0.0;
-  if (step == 0) stop = false;
-  const double tr0 = step == 0 ? total : state[0];
+  stop = step > 0 && st1 != 0.0;
+  tr0 = step == 0 ? total : st0;
   if (!(total > 1e-14 * tr0)) stop = true;
   int64_t found = -1;
   if (!stop) {
@@ -97,21 +99,37 @@ __global__ __launch_bounds__(64) void rpc_select_kernel(const double* __restrict
     }
     if (bsel >= 0) {
       // scan from the selected block on (a later block only when the rounding
-      // of block sums and running sum disagree next to the target)
+      // of block sums and running sum disagree next to the target); the
+      // entries come four groups of 64 at a time, in one memory round trip
       double run = pref_sel;
-      for (int64_t base = int64_t(bsel) * chunk; base < n && found < 0; base += 64) {
-        const int64_t i = base + lane;
-        const double di = i < n ? d[i] : 0.0;
-        double incl = di;
+      for (int64_t base = int64_t(bsel) * chunk; base < n && found < 0; base += 256) {
+        double dv[4];
 #pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-          const double t = __shfl_up(incl, off);
-          if (lane >= off) incl += t;
+        for (int q = 0; q < 4; ++q) {
+          const int64_t i = base + 64 * q + lane;
+          const double v = d[min(i, n - 1)];
+          dv[q] = i < n ? v : 0.0;
         }
-        const bool hit = (i < n) && (run + incl > target) && di > 0.0;
-        const unsigned long long m = __ballot(hit);
-        if (m) found = base + __ffsll((long long)m) - 1;
-        else run += __shfl(incl, 63);
+        double inc[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) inc[q] = dv[q];
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {  // four independent scans, interleaved
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const double t = __shfl_up(inc[q], off);
+            if (lane >= off) inc[q] += t;
+          }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          if (found < 0) {
+            const bool hit = (run + inc[q] > target) && dv[q] > 0.0;
+            const unsigned long long m = __ballot(hit);
+            if (m) found = base + 64 * q + __ffsll((long long)m) - 1;
+            else run += readlane_f64(inc[q], 63);
+          }
+        }
       }
     }
     if (found < 0) {  // u*total rounded to the very end: take the last positive entry
@@ -123,68 +141,161 @@ __global__ __launch_bounds__(64) void rpc_select_kernel(const double* __restrict
     }
     if (found < 0) stop = true;
   }
-  if (lane == 0) {
-    piv[step] = stop ? -1 : found;
-    if (step == 0) state[0] = tr0;
-    state[1] = stop ? 1.0 : 0.0;
-  }
+  return found;
 }
 
-// fs[k] = F[s][k] for k < i (FP64 copy of the pivot row of F)
-__global__ void rpc_pivrow_kernel(const float* __restrict__ F, int64_t ldf, int i, const int64_t* __restrict__ piv,
-                                  int step, double* __restrict__ fs) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= i) return;
-  const int64_t s = piv[step];
-  fs[k] = s >= 0 ? double(F[s * ldf + k]) : 0.0;
-}
+// One step of RPCholesky in one launch (it was four: draw, pivot row, F f_s,
+// update).  A workgroup owns one of the kSelBlocks chunks of rows.  Its first
+// wave draws the pivot s from the previous step's residual diagonal and block
+// sums (every workgroup alike, so nothing is exchanged inside the launch; d,
+// the block sums and the state alternate between two buffers), the pivot row
+// of F goes to LDS, and then
+//   u_j = F[j, :i] . F[s, :i],  g_j = K[s][j] - u_j,  F[j][i] = g_j / sqrt(g_s),
+//   d_j <- max(d_j - F[j][i]^2, 0),  d_s <- 0
+// with 16 lanes per row (16-byte pieces 64 columns apart, four rows per group
+// in flight), and the block sums of the new d.  u_s is formed from the LDS row alongside.
+// Per step: the launch, three dependent memory round trips for the draw and
+// its row, then F's first i columns (cache-resident for the most part: 50 MB on
+// average at n = 50,000, r = 500).  There, 500 steps: 11.1 ms in four launches
+// each (12.3 + 5.2 + 3.3 + 1.7 us and their gaps), 7.5 ms now (7 us for an empty step, 23 us for the last).
+constexpr int kRpcThreads = 1024;
+constexpr int kRpcSlots = 4;                               // rows of a 16-lane group in flight
+constexpr int kRpcRows = kRpcThreads / 16 * kRpcSlots;     // rows of a pass
 
-// g_j = K[s][j] - u_j, F[j][i] = g_j / sqrt(g_s), d_j <- max(d_j - F[j][i]^2, 0),
-// d_s <- 0, and the block sums of the new d for the next pivot draw.
-__global__ __launch_bounds__(256) void rpc_update_kernel(const KMat km, const float* __restrict__ X,
-                                                         const float* __restrict__ q, int p, int lap, float ng,
-                                                         float* __restrict__ F, int64_t n, int64_t ldf, int i,
-                                                         const int64_t* __restrict__ piv, int step,
-                                                         const double* __restrict__ u, double* __restrict__ d,
-                                                         int64_t chunk, double* __restrict__ bsum) {
+struct RpcStep {
+  const double *d, *bsum, *state;  // after the previous step
+  double *dn, *bsumn, *staten;     // after this one
+  int64_t* piv;
+  int64_t chunk;
+  double u;  // this step's uniform
+};
+
+template <bool STORED>
+__global__ __launch_bounds__(kRpcThreads) void rpc_step_kernel(const KMat km, const float* __restrict__ X,
+                                                               const float* __restrict__ q, int p, int lap, float ng,
+                                                               float* __restrict__ F, int64_t n, int64_t ldf, int i,
+                                                               const RpcStep a) {
+  static_assert(kRpcRows == 256, "a pass covers the 256 running sums of a block sum");
+  __shared__ double xs[1024];
+  __shared__ double part[256];
   __shared__ double sh[4];
-  const int64_t s = piv[step];
-  const int64_t i0 = int64_t(blockIdx.x) * chunk;
-  const int64_t i1 = min(n, i0 + chunk);
-  double bs = 0.0;
-  if (s < 0) {
-    for (int64_t j = i0 + threadIdx.x; j < i1; j += 256) {
-      F[j * ldf + i] = 0.f;
-      bs += d[j];
+  __shared__ int64_t pivot;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int g = lane >> 4, t = lane & 15;
+  const int64_t i0 = int64_t(blockIdx.x) * a.chunk, i1 = min(n, i0 + a.chunk);
+  const int nvec = i >> 2;
+  if (wave == 0) {
+    double tr0;
+    bool stop;
+    const int64_t s = rpc_select(a.d, n, a.chunk, a.bsum, kSelBlocks, a.u, i, a.state, tr0, stop);
+    if (lane == 0) {
+      pivot = stop ? -1 : s;
+      if (blockIdx.x == 0) {
+        a.piv[i] = stop ? -1 : s;
+        a.staten[0] = tr0;
+        a.staten[1] = stop ? 1.0 : 0.0;
+      }
     }
-  } else {
-    auto kentry = [&](int64_t j) -> double {
-      if (km.K) {
-        const size_t off = km.layout == 1 ? pk_offset(s, j, km.ld) : size_t(s * km.ld + j);
+  }
+  __syncthreads();
+  const int64_t s = pivot;
+  if (s >= 0) {
+    for (int k = tid; k < i; k += kRpcThreads) xs[k] = double(F[s * ldf + k]);
+  }
+  __syncthreads();
+  double bs = 0.0;  // of row 64 t + 4 wave + g of every pass, lanes t < kRpcSlots
+  for (int64_t base = i0; base < i1; base += kRpcRows) {
+    const int64_t j = base + 64 * t + 4 * wave + g;
+    const bool mine = t < kRpcSlots && j < i1;
+    if (s < 0) {
+      if (mine) {
+        F[j * ldf + i] = 0.f;
+        const double dj = a.d[j];
+        a.dn[j] = dj;
+        bs += dj;
+      }
+      continue;
+    }
+    auto kentry = [&](int64_t jj) -> double {
+      if (STORED) {
+        const size_t off = km.layout == 1 ? pk_offset(s, jj, km.ld) : size_t(s * km.ld + jj);
         if (km.dtype == KQR_BF16)
           return double(__uint_as_float(uint32_t(static_cast<const uint16_t*>(km.K)[off]) << 16));
         return double(static_cast<const float*>(km.K)[off]);
       }
-      float dd = pair_dist_dyn(X + s * p, q ? q[s] : 0.f, X + j * p, q ? q[j] : 0.f, p, lap != 0);
-      if (j == s) dd = 0.f;
+      float dd = pair_dist_dyn(X + s * p, q ? q[s] : 0.f, X + jj * p, q ? q[jj] : 0.f, p, lap != 0);
+      if (jj == s) dd = 0.f;
       return double(kexp2(ng * dd));
     };
-    const double gs = kentry(s) - (i > 0 ? u[s] : 0.0);
-    const double inv = gs > 0.0 ? 1.0 / sqrt(gs) : 0.0;
-    for (int64_t j = i0 + threadIdx.x; j < i1; j += 256) {
-      const double g = kentry(j) - (i > 0 ? u[j] : 0.0);
-      const double f = g * inv;
+    const double ks = STORED ? kentry(s) : 1.0;  // from X: exp2(0)
+    double kj = 0.0, dj = 0.0;
+    if (mine) {
+      kj = kentry(j);
+      dj = a.d[j];
+    }
+    double acc[kRpcSlots] = {0.0, 0.0, 0.0, 0.0}, us = 0.0;
+    // slot sl of a group holds row 64 sl + 4 wave + g of the pass, so a short
+    // last pass leaves every wave the same share; rows past the chunk repeat its last
+    const float* rows[kRpcSlots];
+#pragma unroll
+    for (int sl = 0; sl < kRpcSlots; ++sl) rows[sl] = F + min(base + 64 * sl + 4 * wave + g, i1 - 1) * ldf;
+    // (deeper explicit buffering of these loads was slower every time: past 128
+    // registers it spills, and 512 threads leave half the waves for the draw's tail)
+#pragma unroll 2
+    for (int c = t; c < nvec; c += 16) {
+      float4 v[kRpcSlots];
+#pragma unroll
+      for (int sl = 0; sl < kRpcSlots; ++sl) v[sl] = reinterpret_cast<const float4*>(rows[sl])[c];
+      const double x0 = xs[4 * c], x1 = xs[4 * c + 1], x2 = xs[4 * c + 2], x3 = xs[4 * c + 3];
+#pragma unroll
+      for (int sl = 0; sl < kRpcSlots; ++sl) {
+        acc[sl] = fma(double(v[sl].x), x0, acc[sl]);
+        acc[sl] = fma(double(v[sl].y), x1, acc[sl]);
+        acc[sl] = fma(double(v[sl].z), x2, acc[sl]);
+        acc[sl] = fma(double(v[sl].w), x3, acc[sl]);
+      }
+      us = fma(x0, x0, us);
+      us = fma(x1, x1, us);
+      us = fma(x2, x2, us);
+      us = fma(x3, x3, us);
+    }
+#pragma unroll 1
+    for (int c = nvec * 4 + t; c < i; c += 16) {
+#pragma unroll
+      for (int sl = 0; sl < kRpcSlots; ++sl) acc[sl] = fma(double(rows[sl][c]), xs[c], acc[sl]);
+      us = fma(xs[c], xs[c], us);
+    }
+    // sums over the 16 lanes (8, 4, 2, 1 lanes apart)
+    auto sum16 = [](double x) {
+      x += dpp_f64<0x128>(x);
+      x += dpp_f64<0x124>(x);
+      x += dpp_f64<0x4E>(x);
+      return x + dpp_f64<0xB1>(x);
+    };
+    us = sum16(us);
+#pragma unroll
+    for (int sl = 0; sl < kRpcSlots; ++sl) acc[sl] = sum16(acc[sl]);
+    if (mine) {
+      const double gs = ks - us;
+      const double inv = gs > 0.0 ? 1.0 / sqrt(gs) : 0.0;
+      const double uj = t == 0 ? acc[0] : t == 1 ? acc[1] : t == 2 ? acc[2] : acc[3];
+      const double f = (kj - uj) * inv;
       F[j * ldf + i] = float(f);
-      const double dj = (j == s) ? 0.0 : fmax(d[j] - f * f, 0.0);
-      d[j] = dj;
-      bs += dj;
+      const double dnew = j == s ? 0.0 : fmax(dj - f * f, 0.0);
+      a.dn[j] = dnew;
+      bs += dnew;
     }
   }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) bs += __shfl_xor(bs, off);
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = bs;
+  if (t < kRpcSlots) part[64 * t + 4 * wave + g] = bs;
   __syncthreads();
-  if (threadIdx.x == 0) bsum[blockIdx.x] = ((sh[0] + sh[1]) + sh[2]) + sh[3];
+  if (tid < 256) {
+    double b = part[tid];
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) b += __shfl_xor(b, off);
+    if ((tid & 63) == 0) sh[tid >> 6] = b;
+  }
+  __syncthreads();
+  if (tid == 0) a.bsumn[blockIdx.x] = ((sh[0] + sh[1]) + sh[2]) + sh[3];
 }
 
 __global__ void rpc_diag_kernel(const KMat km, int64_t n, double* __restrict__ d) {
@@ -206,29 +317,34 @@ Co<std::vector<int64_t>> rpcholesky(KMat km, const float* X, const float* sqn, i
   if (rank <= 0 || n <= 0) co_return pivots;
   rank = std::min<int64_t>(rank, n);
   if (rank > 1024) fail(KQR_EINVAL, "RPCholesky rank %lld exceeds 1024", (long long)rank);
-  DevBuf d(size_t(n) * sizeof(double)), u(size_t(n) * sizeof(double)), fs(1024 * sizeof(double));
-  DevBuf bsum(kSelBlocks * sizeof(double)), piv(size_t(rank) * sizeof(int64_t)), state(2 * sizeof(double));
+  if (ldf & 3) fail(KQR_EINVAL, "RPCholesky: ldf must be a multiple of 4");
+  DevBuf d(size_t(2 * n) * sizeof(double)), bsum(2 * kSelBlocks * sizeof(double)), state(4 * sizeof(double));
+  DevBuf piv(size_t(rank) * sizeof(int64_t));
   rpc_diag_kernel<<<dim3((unsigned)((n + 255) / 256)), 256, 0, st>>>(km, n, d.as<double>());
   KQR_LAUNCH_CHECK();
-  KQR_CHECK_HIP(hipMemsetAsync(state.ptr, 0, 2 * sizeof(double), st));
+  KQR_CHECK_HIP(hipMemsetAsync(state.ptr, 0, 4 * sizeof(double), st));
   const int64_t chunk = (n + kSelBlocks - 1) / kSelBlocks;
   rpc_blocksum_kernel<<<kSelBlocks, 256, 0, st>>>(d.as<double>(), n, chunk, bsum.as<double>());
   KQR_LAUNCH_CHECK();
   const float ng = -float(ks.gamma) * kLog2e;
   const bool lap = ks.kind == KQR_LAPLACIAN;
   for (int64_t i = 0; i < rank; ++i) {
-    rpc_select_kernel<<<1, 64, 0, st>>>(d.as<double>(), n, chunk, bsum.as<double>(), kSelBlocks, uniforms[i],
-                                        int(i), piv.as<int64_t>(), state.as<double>());
-    KQR_LAUNCH_CHECK();
-    if (i > 0) {
-      rpc_pivrow_kernel<<<(unsigned)((i + 255) / 256), 256, 0, st>>>(F, ldf, int(i), piv.as<int64_t>(), int(i),
-                                                                      fs.as<double>());
-      KQR_LAUNCH_CHECK();
-      gemv_skinny(F, ldf, n, i, fs.as<double>(), u.as<double>(), st);
-    }
-    rpc_update_kernel<<<kSelBlocks, 256, 0, st>>>(km, X, lap ? nullptr : sqn, p, lap ? 1 : 0, ng, F, n, ldf, int(i),
-                                                  piv.as<int64_t>(), int(i), u.as<double>(), d.as<double>(), chunk,
-                                                  bsum.as<double>());
+    const int from = int(i & 1), to = 1 - from;
+    RpcStep a;
+    a.d = d.as<double>() + from * n;
+    a.dn = d.as<double>() + to * n;
+    a.bsum = bsum.as<double>() + from * kSelBlocks;
+    a.bsumn = bsum.as<double>() + to * kSelBlocks;
+    a.state = state.as<double>() + 2 * from;
+    a.staten = state.as<double>() + 2 * to;
+    a.piv = piv.as<int64_t>();
+    a.chunk = chunk;
+    a.u = uniforms[i];
+    if (km.K)
+      rpc_step_kernel<true><<<kSelBlocks, kRpcThreads, 0, st>>>(km, X, nullptr, p, 0, ng, F, n, ldf, int(i), a);
+    else
+      rpc_step_kernel<false><<<kSelBlocks, kRpcThreads, 0, st>>>(km, X, lap ? nullptr : sqn, p, lap ? 1 : 0, ng, F, n,
+                                                                 ldf, int(i), a);
     KQR_LAUNCH_CHECK();
   }
   std::vector<int64_t> h(size_t(rank), -1);

@@ -304,12 +304,6 @@ __global__ __launch_bounds__(64) void flag_scatter_kernel(const uint8_t* __restr
 }
 
 // ---------------------------------------------------------------- blocked Cholesky (lower)
-__device__ __forceinline__ double readlane_f64(double x, int lane) {
-  const int lo = __builtin_amdgcn_readlane(__double2loint(x), lane);
-  const int hi = __builtin_amdgcn_readlane(__double2hiint(x), lane);
-  return __hiloint2double(hi, lo);
-}
-
 // 1 / sqrt(a) for a normal a > 0: v_rsq_f64 and two Newton steps
 // y <- y + y (1 - a y^2) / 2.
 __device__ __forceinline__ double rsqrt_f64(double a) {

@@ -79,3 +79,38 @@ def test_rank_rule_of_diagonal_gram_matrices(dev, diag):
     rank, top = kqr.kqr_adaptive_rank(torch.from_numpy(F).to(dev), 4, 1e-3)
     assert top == max(diag) ** 2
     assert rank == (2 if diag[1] == 0.0 and diag[0] > 0.0 else 4)
+
+
+@pytest.mark.parametrize("n,rank,stored", [(2, 2, False), (3, 3, True), (65, 18, False), (255, 67, True),
+                                           (256, 68, False), (257, 131, True), (65535, 21, False),
+                                           (65537, 66, False), (131073, 5, False)])
+def test_rpcholesky_steps_at_chunk_edges(dev, n, rank, stored):
+    """Pivots, factor columns and the zero residual at the pivots, against the steps in FP64 on the host, at row
+    counts around the 256 chunks of rows (one and several passes of 256 rows each) and ranks around the
+    16-byte pieces of a pivot row."""
+    rng = np.random.default_rng((n, rank))
+    X = rng.uniform(-1.0, 1.0, (n, 3)).astype(np.float32)
+    gamma = 2.0
+    u = rng.uniform(0.0, 1.0, rank)
+    say("rpcholesky", n, rank, stored)
+    Xt = torch.from_numpy(X).to(dev)
+    K = kqr.kqr_kernel_build(Xt, "rbf", gamma) if stored else None
+    F, piv, r = kqr.kqr_rpcholesky(rank, u, X=Xt, kernel="rbf", gamma=gamma, K=K)
+    F = F.cpu().numpy().astype(np.float64)
+    assert r == rank and len(set(piv.tolist())) == rank
+    x = X.astype(np.float64)
+    G = np.zeros((n, rank))
+    d = np.ones(n)
+    for i, s in enumerate(piv):
+        # the draw: the running sum passes u_i sum(d) at the pivot, up to the FP32 entries' rounding
+        run, target = np.cumsum(d), u[i] * d.sum()
+        slack = 1e-5 * d.sum()
+        assert run[s] > target - slack and run[s] - d[s] <= target + slack, (i, s)
+        g = np.exp(-gamma * ((x - x[s]) ** 2).sum(1)) - G[:, :i] @ G[s, :i]
+        G[:, i] = g / np.sqrt(g[s])
+        # an entry carries FP32 roundings of K and F (a few 2^-24), magnified by 1 / sqrt(g_s) and the earlier columns
+        tol = 64 * (i + 1) * 2.0 ** -24 / g[s]
+        assert np.max(np.abs(F[:, i] - G[:, i])) <= tol, (i, np.max(np.abs(F[:, i] - G[:, i])), tol)
+        G[:, i] = F[:, i]
+        d = np.maximum(d - G[:, i] ** 2, 0.0)
+        d[s] = 0.0
