@@ -7,6 +7,7 @@
 #include "kernel_entry.h"
 #include "kqr_internal.h"
 #include "pstep.h"
+#include "reduce.h"
 
 #include <algorithm>
 #include <atomic>
@@ -247,9 +248,7 @@ __global__ __launch_bounds__(256) void kapply_rows_kernel(const void* __restrict
     }
   }
 #pragma unroll
-  for (int r = 0; r < ROWS; ++r)
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) acc[r] += __shfl_xor(acc[r], off);
+  for (int r = 0; r < ROWS; ++r) acc[r] = wave_sum_f64(acc[r]);
   if (part) {
 #pragma unroll
     for (int r = 0; r < ROWS; ++r)
@@ -1010,12 +1009,7 @@ __global__ __launch_bounds__(256) void kapply_otf_mfma_kernel(
 #pragma unroll
   for (int s = 0; s < 2; ++s)
 #pragma unroll
-    for (int rr = 0; rr < 4; ++rr) {
-      double x = acc[s][rr];
-#pragma unroll
-      for (int off = 1; off < 16; off <<= 1) x += __shfl_xor(x, off);
-      acc[s][rr] = x;
-    }
+    for (int rr = 0; rr < 4; ++rr) acc[s][rr] = row16_sum_f64<true>(acc[s][rr]);
   if (li == 0) {
 #pragma unroll
     for (int s = 0; s < 2; ++s)
@@ -1213,12 +1207,7 @@ __global__ __launch_bounds__(256) void kapply_otf_mfma3_kernel(
 #pragma unroll
   for (int s = 0; s < 2; ++s)
 #pragma unroll
-    for (int rr = 0; rr < 4; ++rr) {
-      double x = acc[s][rr];
-#pragma unroll
-      for (int off = 1; off < 16; off <<= 1) x += __shfl_xor(x, off);
-      acc[s][rr] = x;
-    }
+    for (int rr = 0; rr < 4; ++rr) acc[s][rr] = row16_sum_f64<true>(acc[s][rr]);
   if (li == 0) {
 #pragma unroll
     for (int s = 0; s < 2; ++s)
@@ -1375,12 +1364,7 @@ __global__ __launch_bounds__(256) void kapply_otf_mfma3_sym_kernel(
 #pragma unroll
   for (int s = 0; s < 2; ++s)
 #pragma unroll
-    for (int rr = 0; rr < 4; ++rr) {
-      double x = acc[s][rr];
-#pragma unroll
-      for (int off = 1; off < 16; off <<= 1) x += __shfl_xor(x, off);
-      acc[s][rr] = x;
-    }
+    for (int rr = 0; rr < 4; ++rr) acc[s][rr] = row16_sum_f64<true>(acc[s][rr]);
   if (li == 0) {
 #pragma unroll
     for (int s = 0; s < 2; ++s)
@@ -1507,12 +1491,7 @@ __global__ __launch_bounds__(256) void kapply_otf_mfma_sym_kernel(
 #pragma unroll
   for (int s = 0; s < 2; ++s)
 #pragma unroll
-    for (int rr = 0; rr < 4; ++rr) {
-      double x = acc[s][rr];
-#pragma unroll
-      for (int off = 1; off < 16; off <<= 1) x += __shfl_xor(x, off);
-      acc[s][rr] = x;
-    }
+    for (int rr = 0; rr < 4; ++rr) acc[s][rr] = row16_sum_f64<true>(acc[s][rr]);
   if (li == 0) {
 #pragma unroll
     for (int s = 0; s < 2; ++s)
@@ -2024,9 +2003,7 @@ __device__ __forceinline__ void gemv_skinny_body(const float* __restrict__ A, in
     for (int sl = 0; sl < 4; ++sl) acc[sl] = fma(double(rows[sl][c]), xs[c], acc[sl]);
   }
 #pragma unroll
-  for (int sl = 0; sl < 4; ++sl)
-#pragma unroll
-    for (int off = 8; off >= 1; off >>= 1) acc[sl] += __shfl_xor(acc[sl], off, 16);
+  for (int sl = 0; sl < 4; ++sl) acc[sl] = row16_sum_f64(acc[sl]);
   if (t == 0) {
 #pragma unroll
     for (int sl = 0; sl < 4; ++sl) {

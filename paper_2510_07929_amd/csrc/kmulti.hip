@@ -6,6 +6,7 @@
 //    (problem, row block) pairs of all problems.
 #include "kqr_internal.h"
 #include "kmulti.h"
+#include "reduce.h"
 
 #include <algorithm>
 #include <cstring>
@@ -370,9 +371,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MX == 1 ? 3
 #pragma unroll
     for (int rr = 0; rr < 4; ++rr)
 #pragma unroll
-      for (int j = 0; j < (MX > 0 ? MX : 1); ++j)
-#pragma unroll
-        for (int off = 1; off < 16; off <<= 1) accx[rr][j] += __shfl_xor(accx[rr][j], off);
+      for (int j = 0; j < (MX > 0 ? MX : 1); ++j) accx[rr][j] = row16_sum_f64<true>(accx[rr][j]);
     if ((t & 15) == 0) {
 #pragma unroll
       for (int rr = 0; rr < 4; ++rr) {
@@ -632,9 +631,7 @@ __device__ __forceinline__ void problem_rows(const ProblemTask& tk, int64_t row0
     }
   }
 #pragma unroll
-  for (int r = 0; r < ROWS; ++r)
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) acc[r] += __shfl_xor(acc[r], off);
+  for (int r = 0; r < ROWS; ++r) acc[r] = wave_sum_f64(acc[r]);
 #pragma unroll
   for (int r = 0; r < ROWS; ++r)
     if (lane == r && row0 + r < tk.n) tk.u[row0 + r] = acc[r];

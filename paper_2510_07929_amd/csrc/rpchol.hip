@@ -37,8 +37,7 @@ __global__ __launch_bounds__(256) void rpc_blocksum_kernel(const double* __restr
   const int64_t i1 = min(n, i0 + chunk);
   double s = 0.0;
   for (int64_t i = i0 + threadIdx.x; i < i1; i += 256) s += d[i];
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
+  s = wave_sum_f64(s);
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
   __syncthreads();
   if (threadIdx.x == 0) bsum[blockIdx.x] = ((sh[0] + sh[1]) + sh[2]) + sh[3];
@@ -265,16 +264,9 @@ __global__ __launch_bounds__(kRpcThreads) void rpc_step_kernel(const KMat km, co
       for (int sl = 0; sl < kRpcSlots; ++sl) acc[sl] = fma(double(rows[sl][c]), xs[c], acc[sl]);
       us = fma(xs[c], xs[c], us);
     }
-    // sums over the 16 lanes (8, 4, 2, 1 lanes apart)
-    auto sum16 = [](double x) {
-      x += dpp_f64<0x128>(x);
-      x += dpp_f64<0x124>(x);
-      x += dpp_f64<0x4E>(x);
-      return x + dpp_f64<0xB1>(x);
-    };
-    us = sum16(us);
+    us = row16_sum_f64(us);
 #pragma unroll
-    for (int sl = 0; sl < kRpcSlots; ++sl) acc[sl] = sum16(acc[sl]);
+    for (int sl = 0; sl < kRpcSlots; ++sl) acc[sl] = row16_sum_f64(acc[sl]);
     if (mine) {
       const double gs = ks - us;
       const double inv = gs > 0.0 ? 1.0 / sqrt(gs) : 0.0;
@@ -290,8 +282,7 @@ __global__ __launch_bounds__(kRpcThreads) void rpc_step_kernel(const KMat km, co
   __syncthreads();
   if (tid < 256) {
     double b = part[tid];
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) b += __shfl_xor(b, off);
+    b = wave_sum_f64(b);
     if ((tid & 63) == 0) sh[tid >> 6] = b;
   }
   __syncthreads();

@@ -760,8 +760,7 @@ __global__ __launch_bounds__(256) void trmv_kernel(const double* __restrict__ M,
   const double* mr = M + int64_t(row) * ldm;
   double s = 0.0;
   for (int k = lo + lane; k <= hi; k += 64) s = fma(mr[k], x[k], s);
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
+  s = wave_sum_f64(s);
   if (lane == 0) out[row] = s;
 }
 
