@@ -469,6 +469,11 @@ int kqr_kernel_apply(const float* X, int64_t n, int64_t p, int kernel, double ga
     hipStream_t st = static_cast<hipStream_t>(stream);
     const KernelSpec ks{kernel, gamma};
     const KMat km{K, k_dtype, ldk};
+    const bool strided = ldv != 1 || (reinterpret_cast<uintptr_t>(V) & 15) != 0;  // kernels read 16-byte vectors
+    if (K && m == 1 && !strided) {  // v is rounded as it is read: no FP32 copy, no memory for one
+      kapply_dense(km, n, n, nullptr, V, U, ldu, mode == KQR_APPLY_EXACT, st);
+      return;
+    }
     void* tmp = nullptr;
     // per column: contiguous FP64 copy (when strided) and its FP32 rounding
     const size_t bytes = size_t(n) * (sizeof(double) + sizeof(float)) + 256;

@@ -137,6 +137,8 @@ void kbuild(const float* X, const float* sqn, int64_t n, int p, KernelSpec ks, i
 //   fast  (EXACT=false): v in FP32, FP32 products summed in FP32 over one step
 //                        and then added into FP64 accumulators.
 //   exact (EXACT=true) : v in FP64, products and sums in FP64.
+// V64 (fast): v comes in FP64 and is rounded to FP32 as it is read, the same
+// values as an FP32 copy without the launch and the memory for one.
 template <bool BF16>
 __device__ __forceinline__ float kelem(const u32x4& w, int e) {
   if (BF16) {
@@ -150,7 +152,7 @@ __device__ __forceinline__ float kelem(const u32x4& w, int e) {
 // Columns can be split into gridDim.y segments (smaller work items balance the
 // tail of the launch); each segment then writes a partial sum per row and
 // kapply_seg_reduce adds the segments in order.
-template <int ROWS, int UNROLL, bool EXACT, bool BF16>
+template <int ROWS, int UNROLL, bool EXACT, bool BF16, bool V64>
 __global__ __launch_bounds__(256) void kapply_rows_kernel(const void* __restrict__ Kp, int64_t ldk,
                                                           int64_t nrows, int64_t ncols,
                                                           const float* __restrict__ v32,
@@ -206,14 +208,24 @@ __global__ __launch_bounds__(256) void kapply_rows_kernel(const void* __restrict
 #pragma unroll
       for (int s = 0; s < UNROLL; ++s) {
         float vv[VEC];
-        const float* vp = v32 + (c + 64 * s) * VEC;
+        if (V64) {
+          const double* vp = v64 + (c + 64 * s) * VEC;
 #pragma unroll
-        for (int e = 0; e < VEC; e += 4) {
-          const float4 t = *reinterpret_cast<const float4*>(vp + e);
-          vv[e] = t.x;
-          vv[e + 1] = t.y;
-          vv[e + 2] = t.z;
-          vv[e + 3] = t.w;
+          for (int e = 0; e < VEC; e += 2) {
+            const double2 t = *reinterpret_cast<const double2*>(vp + e);
+            vv[e] = float(t.x);
+            vv[e + 1] = float(t.y);
+          }
+        } else {
+          const float* vp = v32 + (c + 64 * s) * VEC;
+#pragma unroll
+          for (int e = 0; e < VEC; e += 4) {
+            const float4 t = *reinterpret_cast<const float4*>(vp + e);
+            vv[e] = t.x;
+            vv[e + 1] = t.y;
+            vv[e + 2] = t.z;
+            vv[e + 3] = t.w;
+          }
         }
 #pragma unroll
         for (int r = 0; r < ROWS; ++r)
@@ -230,7 +242,7 @@ __global__ __launch_bounds__(256) void kapply_rows_kernel(const void* __restrict
     for (int r = 0; r < ROWS; ++r) kk[r] = __builtin_nontemporal_load(rp[r] + c);
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
-      const double ve = EXACT ? v64[c * VEC + e] : double(v32[c * VEC + e]);
+      const double ve = EXACT ? v64[c * VEC + e] : double(V64 ? float(v64[c * VEC + e]) : v32[c * VEC + e]);
 #pragma unroll
       for (int r = 0; r < ROWS; ++r) acc[r] = fma(double(kelem<BF16>(kk[r], e)), ve, acc[r]);
     }
@@ -238,7 +250,7 @@ __global__ __launch_bounds__(256) void kapply_rows_kernel(const void* __restrict
   // trailing columns that do not fill a 16-byte chunk (last segment)
   const int64_t col = nchunk_all * VEC + lane;
   if (last_seg && col < ncols) {
-    const double ve = EXACT ? v64[col] : double(v32[col]);
+    const double ve = EXACT ? v64[col] : double(V64 ? float(v64[col]) : v32[col]);
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) {
       const char* base = reinterpret_cast<const char*>(rp[r]);
@@ -284,9 +296,23 @@ ApplyShape default_apply_shape(int dtype, int exact, int64_t n) {
   const int d = dtype == KQR_BF16, e = exact != 0, b = size_bucket(n);
   if (g_shape_set[d][e][b]) return g_shape[d][e][b];
   ApplyShape s;
-  s.rows = 8;
   s.unroll = 2;
   s.segs = n >= 16384 ? 4 : 1;  // keeps work items ~n/4 columns long on large matrices
+  // Rows per wave (every output's sums are the same for any of them).  Eight
+  // read the vector least often but make n / 32 workgroups: CUs idle well below
+  // 8192 rows, and from there to about 12,500 a thin second round follows the
+  // first.  FP64 products keep two or four rows ahead for longer.  Measured
+  // (us; 2 / 4 / 8 rows): FP32 fast n = 2000 5.7 / 6.9 / 10.0, 6000 22 / 25 / 25,
+  // 7000 35 / 31 / 32, 8192 49 / 52 / 46, 10,000 58 / 64 / 75, 13,000 106 / 109 / 104;
+  // FP32 exact 2000 6.3 / 7.9 / 17.7, 7000 35 / 34 / 57, 13,000 121 / 122 / 139,
+  // 16,383 183 / 167 / 181; BF16 fast 2000 4.1 / 5.6 / 8.4, 8192 22 / 31 / 31, 12,000
+  // 50 / 46 / 53, 14,000 68 / 67 / 65; BF16 exact 6000 16 / 19 / 18, 7500 28 / 24 / 22,
+  // 10,000 52 / 42 / 49, 13,000 95 / 84 / 66.
+  const bool thin = n > 8192 && n <= 12500;
+  if (n >= 16384) s.rows = 8;
+  else if (n <= 6250) s.rows = 2;
+  else if (e) s.rows = !d || thin ? 4 : 8;
+  else s.rows = thin || (d && n <= 12500) ? 2 : 8;
   return s;
 }
 
@@ -323,18 +349,16 @@ static void kapply_rows_launch(const KMat& km, int64_t nrows, int64_t ncols, con
   if (own)
     KQR_CHECK_HIP(hipMallocAsync(reinterpret_cast<void**>(&part), size_t(segs) * nrows * sizeof(double), st));
   const bool bf = km.dtype == KQR_BF16;
-  if (exact && bf)
-    kapply_rows_kernel<ROWS, UNROLL, true, true><<<grid, 256, 0, st>>>(km.K, km.ld, nrows, ncols, v32, v64, u, ldu,
-                                                                        seg_chunks, part);
-  else if (exact)
-    kapply_rows_kernel<ROWS, UNROLL, true, false><<<grid, 256, 0, st>>>(km.K, km.ld, nrows, ncols, v32, v64, u, ldu,
-                                                                         seg_chunks, part);
-  else if (bf)
-    kapply_rows_kernel<ROWS, UNROLL, false, true><<<grid, 256, 0, st>>>(km.K, km.ld, nrows, ncols, v32, v64, u, ldu,
-                                                                         seg_chunks, part);
-  else
-    kapply_rows_kernel<ROWS, UNROLL, false, false><<<grid, 256, 0, st>>>(km.K, km.ld, nrows, ncols, v32, v64, u, ldu,
-                                                                          seg_chunks, part);
+#define KQR_ROWS(EX, BF, V)                                                                                       \
+  kapply_rows_kernel<ROWS, UNROLL, EX, BF, V><<<grid, 256, 0, st>>>(km.K, km.ld, nrows, ncols, v32, v64, u, ldu, \
+                                                                    seg_chunks, part)
+  if (exact && bf) KQR_ROWS(true, true, false);
+  else if (exact) KQR_ROWS(true, false, false);
+  else if (!v32 && bf) KQR_ROWS(false, true, true);
+  else if (!v32) KQR_ROWS(false, false, true);
+  else if (bf) KQR_ROWS(false, true, false);
+  else KQR_ROWS(false, false, false);
+#undef KQR_ROWS
   KQR_LAUNCH_CHECK();
   if (part) {
     kapply_seg_reduce<<<dim3((unsigned)((nrows + 255) / 256)), 256, 0, st>>>(part, segs, nrows, u, ldu);
