@@ -209,6 +209,13 @@ def padded_ld(n: int) -> int:
     return (int(n) + 63) // 64 * 64
 
 
+def _pivot_uniforms(uniforms):
+    """Host copy for kqr_options.pivot_uniforms, which the library reads up to the rank it
+    arrives at (at most 1024): fewer values start again from the first."""
+    u = np.ascontiguousarray(np.asarray(uniforms, dtype=np.float64)).reshape(-1)
+    return np.resize(u, 1024) if 0 < u.size < 1024 else u
+
+
 # ----------------------------------------------------------------------- entry points
 def kqr_default_options(**overrides) -> KqrOptions:
     o = KqrOptions()
@@ -537,7 +544,7 @@ def kqr_fit(X, y, tau, lam, kernel="rbf", gamma=1.0, options: KqrOptions | None 
         o.v_out, o.z_out = vz[0].data_ptr(), vz[1].data_ptr()
     keep = None
     if uniforms is not None:
-        keep = np.ascontiguousarray(np.asarray(uniforms, dtype=np.float64))
+        keep = _pivot_uniforms(uniforms)
         o.pivot_uniforms = keep.ctypes.data_as(C.POINTER(C.c_double))
     tbuf = None
     if trace > 0:
@@ -570,7 +577,7 @@ def _options(options, uniforms, overrides):
         setattr(o, k, v)
     keep = None
     if uniforms is not None:
-        keep = np.ascontiguousarray(np.asarray(uniforms, dtype=np.float64))
+        keep = _pivot_uniforms(uniforms)
         o.pivot_uniforms = keep.ctypes.data_as(C.POINTER(C.c_double))
     return o, keep
 
