@@ -741,7 +741,7 @@ int kqr_rpcholesky(const float* X, int64_t n, int64_t p, int kernel, double gamm
     DevBuf sqn(size_t(n) * sizeof(float));
     if (X) row_sqnorms(X, n, int(p), sqn.as<float>(), st);
     KQR_CHECK_HIP(hipMemsetAsync(F, 0, size_t(n) * ldf * sizeof(float), st));
-    Exec ex(st);
+    LoneExec ex(st);
     std::vector<int64_t> piv = run_sync(rpcholesky(KMat{K, k_dtype, ldk}, X, sqn.as<float>(), n, int(p),
                                                    KernelSpec{kernel, gamma}, rank, uniforms, F, ldf, ex));
     for (size_t i = 0; i < piv.size(); ++i) pivots[i] = piv[i];
@@ -759,7 +759,7 @@ int kqr_adaptive_rank(const float* F0, int64_t n, int64_t r0, int64_t ldf, doubl
     ensure_device();
     hipStream_t st = static_cast<hipStream_t>(stream);
     double l1 = 0.0;
-    Exec ex(st);
+    LoneExec ex(st);
     *rank = r0 <= 1 ? r0 : run_sync(adaptive_rank(F0, n, r0, ldf, xi, ex, &l1));
     if (lambda1) *lambda1 = l1;
   });
@@ -876,7 +876,7 @@ int kqr_woodbury_apply(const float* F, int64_t n, int64_t r, int64_t ldf, double
     ensure_device();
     hipStream_t st = static_cast<hipStream_t>(stream);
     Workspace ws(st);
-    Exec ex(st);
+    LoneExec ex(st);
     Woodbury P(F, n, r, ldf);
     if (!run_sync(P.build(Ldiag, c, ex))) fail(KQR_ENUMERIC, "Woodbury core is not positive definite");
     P.apply(w, out, nullptr, nullptr, ws, st);
@@ -899,7 +899,7 @@ int kqr_pcg_solve(const float* X, int64_t n, int64_t p, int kernel, double gamma
     hipStream_t st = static_cast<hipStream_t>(stream);
     Operator op(X, n, int(p), KernelSpec{kernel, gamma}, KMat{K, k_dtype, ldk}, st);
     Workspace ws(st);
-    Exec ex(st);
+    LoneExec ex(st);
     Pcg pcg(op, ws, n, ex);
     std::unique_ptr<Woodbury> P;
     if (r > 0) {
@@ -929,11 +929,8 @@ int kqr_ssn_gradient(int64_t n, double tau, double lambda, double beta, double s
     DevBuf red(8 * sizeof(double));
     HostPinned h(8 * sizeof(double));
     vec_dots(n, alpha, nullptr, ws, red.as<double>(), st);
-    KQR_CHECK_HIP(hipMemcpyAsync(h.ptr, red.ptr, 3 * sizeof(double), hipMemcpyDeviceToHost, st));
-    KQR_CHECK_HIP(hipStreamSynchronize(st));
-    const double sa = h.as<double>()[0];
-    ssn_grad(n, alpha, Kalpha, y, z, beta, sigma, sa, tau, lambda, grad, S, ws, red.as<double>(), st);
-    KQR_CHECK_HIP(hipMemcpyAsync(h.ptr, red.ptr, sizeof(double), hipMemcpyDeviceToHost, st));
+    ssn_grad(n, alpha, Kalpha, y, z, beta, sigma, red.as<double>(), tau, lambda, grad, S, ws, red.as<double>() + 3, st);
+    KQR_CHECK_HIP(hipMemcpyAsync(h.ptr, red.as<double>() + 3, sizeof(double), hipMemcpyDeviceToHost, st));
     KQR_CHECK_HIP(hipStreamSynchronize(st));
     const double gn = std::sqrt(h.as<double>()[0]);
     const double et = std::max(tau1 * std::min(tau2, gn), eps_floor);
@@ -963,7 +960,7 @@ int kqr_kkt_residuals(int64_t n, double tau, double lambda, double beta, double 
     KQR_CHECK_HIP(hipMemcpyAsync(h.ptr, red.ptr, 3 * sizeof(double), hipMemcpyDeviceToHost, st));
     KQR_CHECK_HIP(hipStreamSynchronize(st));
     const double ynorm = std::sqrt(std::max(h.as<double>()[2], 0.0));
-    multiplier_kkt(n, alpha, Kalpha, y, z, v, beta, update ? sigma : 1.0, update ? step : 0.0, tau, lambda,
+    multiplier_kkt(n, alpha, Kalpha, y, z, v, BetaStep{beta}, update ? sigma : 1.0, update ? step : 0.0, tau, lambda,
                    update != 0, ws, red.as<double>(), st);
     KQR_CHECK_HIP(hipMemcpyAsync(h.ptr, red.ptr, kKktSums * sizeof(double), hipMemcpyDeviceToHost, st));
     KQR_CHECK_HIP(hipStreamSynchronize(st));
@@ -989,7 +986,7 @@ int kqr_fit(const float* X, const double* y, int64_t n, int64_t p, double tau, d
     ensure_device();
     hipStream_t st = static_cast<hipStream_t>(stream);
     const KernelSpec ks{kernel, gamma};
-    Exec ex(st);
+    LoneExec ex(st);
     Prepared pr = run_sync(prepare_fit(X, n, int(p), ks, o, ex));
     Operator op(X, n, int(p), ks, pr.kmat(), st);
     pr.attach(op);
@@ -1093,7 +1090,7 @@ int kqr_fit_grad(const float* X, const double* y, int64_t n, int64_t p, double t
     double b = 0.0;
     kqr_info inf{};
     {
-      Exec ex(st);
+      LoneExec ex(st);
       Prepared pr = run_sync(prepare_fit(X, n, int(p), ks, o, ex));
       Operator op(X, n, int(p), ks, pr.kmat(), st);
       pr.attach(op);

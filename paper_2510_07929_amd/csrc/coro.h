@@ -97,6 +97,11 @@ struct Exec {
   int slot = -1;
   HostPinned hbuf{kReadBackBytes};
   hipEvent_t ev = nullptr;
+  // Reads of a lone fit without a copy command and a stream synchronisation
+  // (LoneExec in vec.h): post enqueues a kernel that stores the words straight
+  // into hbuf, wait polls for them.  Null: copy and synchronise.
+  bool (*post)(Exec&, const void*, size_t) = nullptr;  // false: not a size it takes
+  void (*wait)(Exec&, size_t) = nullptr;
   explicit Exec(hipStream_t s, Scheduler* sc = nullptr, int sl = -1);
   ~Exec();
   Exec(const Exec&) = delete;
@@ -254,6 +259,10 @@ struct ReadBack {
   void* out;
   bool await_ready() {
     if (bytes > kReadBackBytes) fail(KQR_EHIP, "internal: read-back of %zu bytes", bytes);
+    if (!ex.sched && ex.post && ex.post(ex, dev, bytes)) {
+      ex.wait(ex, bytes);
+      return true;
+    }
     KQR_CHECK_HIP(hipMemcpyAsync(ex.hbuf.ptr, dev, bytes, hipMemcpyDeviceToHost, ex.st));
     if (!ex.sched) {
       KQR_CHECK_HIP(hipStreamSynchronize(ex.st));

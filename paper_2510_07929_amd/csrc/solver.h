@@ -123,8 +123,9 @@ class Solver {
   Co<Unit> ssn(double stop, kqr_info& info);
   Kkt kkt_from_sums(const double* s) const;
   Co<Kkt> update_and_kkt(double beta_new, double sigma, double step, bool update);
+  // beta_ += c 1^T alpha, then the multiplier step and the measures
+  Co<Kkt> beta_and_kkt(double c, double sigma, double step);
   void record(int phase, int it, double err);
-  Co<double> sum_of(const double* x);
 
   Operator& op_;
   Exec& ex_;

@@ -180,11 +180,16 @@ Co<PcgStats> Pcg::solve(double c, const double* L, Woodbury* P, const double* b,
     }
     pcg_init_r(n, b, x, Kx0, L, c, sc, TMP, pb_.r.as<double>(), ws_, sc + RR, st);
   }
-  double rr = 0.0;
-  co_await read_back(ex_, sc + RR, sizeof(double), &rr);
+  // A lone fit enqueues the first preconditioner step before it waits for
+  // ||r|| (it writes nothing that outlives a solve that stops here).
+  const bool ahead = !ex_.sched && ex_.post && ex_.post(ex_, sc + RR, sizeof(double));
   PcgStats stats;
-  stats.resnorm = std::sqrt(rr);
-  if (!(stats.resnorm > tol)) co_return stats;
+  double rr = 0.0;
+  if (!ahead) {
+    co_await read_back(ex_, sc + RR, sizeof(double), &rr);
+    stats.resnorm = std::sqrt(rr);
+    if (!(stats.resnorm > tol)) co_return stats;
+  }
   int cur = 0;
   float* p32 = (fast && op_.materialized()) ? pb_.p32.as<float>() : nullptr;
   // zz = P^{-1} r, sc[rz_new] = r . zz, then p = zz + beta p (beta = sc[rz_new] / sc[rz_old])
@@ -225,6 +230,12 @@ Co<PcgStats> Pcg::solve(double c, const double* L, Woodbury* P, const double* b,
     if (ex_.sched->complete_on_resume()) step.status = ex_.hbuf.as<double>();
   }
   precond_p(RZ0, RZ0, true);
+  if (ahead) {
+    ex_.wait(ex_, sizeof(double));
+    memcpy(&rr, ex_.hbuf.ptr, sizeof(double));
+    stats.resnorm = std::sqrt(rr);
+    if (!(stats.resnorm > tol)) co_return stats;
+  }
   for (int it = 1; it <= maxit; ++it) {
     if (batched_step) {
       step.rz = cur == 0 ? RZ0 : RZ1;
@@ -310,19 +321,26 @@ Kkt kkt_from_sums(const double* s, double ynorm, double lam) {
 
 Kkt Solver::kkt_from_sums(const double* s) const { return ::kqr::kkt_from_sums(s, ynorm_, lam_); }
 
-Co<double> Solver::sum_of(const double* x) {
-  double t3[3];
-  vec_dots(n_, x, nullptr, ws_, red_.as<double>(), st_);
-  co_await read_back(ex_, red_.as<double>(), 3 * sizeof(double), t3);
-  co_return t3[0];
-}
-
 Co<Kkt> Solver::update_and_kkt(double beta_new, double sigma, double step, bool update) {
   double s[kKktSums];
-  multiplier_kkt(n_, alpha_.as<double>(), Ka_.as<double>(), y_, z_.as<double>(), v_.as<double>(), beta_new, sigma,
-                 step, tau_, lam_, update, ws_, red_.as<double>(), st_);
+  multiplier_kkt(n_, alpha_.as<double>(), Ka_.as<double>(), y_, z_.as<double>(), v_.as<double>(), BetaStep{beta_new},
+                 sigma, step, tau_, lam_, update, ws_, red_.as<double>(), st_);
   co_await read_back(ex_, red_.as<double>(), kKktSums * sizeof(double), s);
   co_return kkt_from_sums(s);
+}
+
+// 1^T alpha stays on the device for the multiplier step, so one read-back
+// returns it with the sums of the measures.
+Co<Kkt> Solver::beta_and_kkt(double c, double sigma, double step) {
+  constexpr int kAt = 4;  // vec_dots' three sums come first
+  double s[kAt + kKktSums];
+  double* red = red_.as<double>();
+  vec_dots(n_, alpha_.as<double>(), nullptr, ws_, red, st_);
+  multiplier_kkt(n_, alpha_.as<double>(), Ka_.as<double>(), y_, z_.as<double>(), v_.as<double>(),
+                 BetaStep{beta_, c, red}, sigma, step, tau_, lam_, true, ws_, red + kAt, st_);
+  co_await read_back(ex_, red, sizeof(s), s);
+  beta_ = beta_ + c * s[0];
+  co_return kkt_from_sums(s + kAt);
 }
 
 // Linear solve of (K + c 1 1^T + diag(L)) x = b to ||b - A x|| <= tol, with K x
@@ -428,10 +446,7 @@ Co<Unit> Solver::phase1(kqr_info& info) {
     PcgStats ps = co_await linsolve(c, L_.as<double>(), b_.as<double>(), alpha_.as<double>(), Ka_.as<double>(),
                                     it == 0, eps_k, false, info);
     info.admm_pcg_iters += ps.iters;
-    const double sa = co_await sum_of(alpha_.as<double>());
-    const double beta_new = beta_ + step * sigma * sa;
-    k = co_await update_and_kkt(beta_new, sigma, step, true);
-    beta_ = beta_new;
+    k = co_await beta_and_kkt(step * sigma, sigma, step);
     if (o_.verbose)
       fprintf(stderr, "[kqr] admm %3d pcg %3d eta_p %.2e eta_d %.2e eta_c %.2e gap %.2e\n", it + 1, ps.iters,
               k.eta_p, k.eta_d, k.eta_c, k.eta_gap);
@@ -477,12 +492,13 @@ Co<Unit> Solver::ssn(double stop, kqr_info& info) {
   const int64_t n = n_;
   const double sigma = sigma_, c1 = lam_ * sigma;
   for (int t = 0; t < o_.ssn_max_iter; ++t) {
-    const double sa = co_await sum_of(alpha_.as<double>());
-    ssn_grad(n, alpha_.as<double>(), Ka_.as<double>(), y_, z_.as<double>(), beta_, sigma, sa, tau_, lam_,
-             grad_.as<double>(), S_.as<uint8_t>(), ws_, red_.as<double>(), st_);
-    double gg = 0.0;
-    co_await read_back(ex_, red_.as<double>(), sizeof(double), &gg);
-    const double gn = std::sqrt(gg);
+    double sums[4];  // 1^T alpha, -, ||alpha||^2, ||grad||^2
+    double* red = red_.as<double>();
+    vec_dots(n, alpha_.as<double>(), nullptr, ws_, red, st_);
+    ssn_grad(n, alpha_.as<double>(), Ka_.as<double>(), y_, z_.as<double>(), beta_, sigma, red, tau_, lam_,
+             grad_.as<double>(), S_.as<uint8_t>(), ws_, red + 3, st_);
+    co_await read_back(ex_, red, sizeof(sums), sums);
+    const double sa = sums[0], gn = std::sqrt(sums[3]);
     if (!std::isfinite(gn)) fail(KQR_ENUMERIC, "non-finite gradient in SSN");
     if (gn <= stop) break;
     double eps_t = std::max(o_.tau1 * std::min(o_.tau2, gn), eps_floor_);
@@ -560,10 +576,7 @@ Co<Unit> Solver::phase2(kqr_info& info) {
     const double stop = scale * std::max(o_.ssn_rel * o_.tol, std::min(o_.ssn_adapt * e_prev, 1.0));
     co_await op_.apply_exact(alpha_.as<double>(), Ka_.as<double>(), ex_);  // reset drift of the tracked K alpha
     co_await ssn(stop, info);
-    const double sa = co_await sum_of(alpha_.as<double>());
-    const double beta_new = beta_ + sigma_ * sa;
-    k = co_await update_and_kkt(beta_new, sigma_, 1.0, true);
-    beta_ = beta_new;
+    k = co_await beta_and_kkt(sigma_, sigma_, 1.0);
     record(2, it + 1, k.err);
     if (o_.verbose)
       fprintf(stderr, "[kqr] alm %3d sigma %.1e eta_p %.2e eta_d %.2e eta_c %.2e gap %.2e\n", it + 1, sigma_,

@@ -7,6 +7,12 @@
 
 namespace kqr {
 
+// Execution context of a lone fit: its read-backs are stored by a kernel and polled.
+struct LoneExec : Exec {
+  explicit LoneExec(hipStream_t s);
+  ~LoneExec();
+};
+
 constexpr int kKktSums = 9;    // sums produced by multiplier_kkt
 constexpr int kLsTrials = 24;  // step lengths evaluated per line-search pass
 constexpr int kMaxPartialQ = 5 + kLsTrials;
@@ -39,11 +45,19 @@ void pcg_qxr(int64_t n, const double* Kp, const double* p, const double* L, doub
              hipStream_t st);
 void admm_rhs(int64_t n, const double* y, const double* z, const double* v, double beta, double sigma,
               double lam, double* b, hipStream_t st);
+// The intercept at the new multipliers: beta, plus step * *sum (device) where sum
+// is given.
+struct BetaStep {
+  double beta;
+  double step = 0.0;
+  const double* sum = nullptr;
+};
 void multiplier_kkt(int64_t n, const double* alpha, const double* Ka, const double* y, double* z, double* v,
-                    double beta_new, double sigma, double step, double tau, double lam, bool update,
+                    BetaStep beta_new, double sigma, double step, double tau, double lam, bool update,
                     Workspace& ws, double* out, hipStream_t st);
+// sum_alpha: device
 void ssn_grad(int64_t n, const double* alpha, const double* Ka, const double* y, const double* z, double beta,
-              double sigma, double sum_alpha, double tau, double lam, double* grad, uint8_t* S, Workspace& ws,
+              double sigma, const double* sum_alpha, double tau, double lam, double* grad, uint8_t* S, Workspace& ws,
               double* gg_out, hipStream_t st);
 void ssn_system(int64_t n, const uint8_t* S, const double* grad, double lam, double sigma, double eps_t,
                 double* L, double* rhs, hipStream_t st);
