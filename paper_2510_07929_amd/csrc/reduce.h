@@ -124,25 +124,24 @@ __device__ __forceinline__ void block_sums(double (&v)[NQ], double* __restrict__
   block_sums_at<NQ>(v, partials, out, int(blockIdx.x), int(gridDim.x));
 }
 
-// Sum of v over the (single) workgroup in block_sums' order, returned to
-// every thread.
+// Sum of v over the (single) workgroup in block_sums' order, in every thread.
+// Each thread adds the waves' sums itself, so a call has one barrier; calls of
+// a kernel alternate SLOT, which keeps a call's sums while the next is formed.
+template <int SLOT>
 __device__ __forceinline__ double block_sum_all(double v) {
   __shared__ double sh[16];
-  __shared__ double tot;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = int(blockDim.x) >> 6;
   v = wave_sum_f64(v);
   if (lane == 0) sh[wave] = v;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    double s = 0.0;
-    for (int w = 0; w < nw; ++w) s += sh[w];
-    tot = s;
-  }
-  __syncthreads();
-  const double r = tot;
-  __syncthreads();  // sh and tot are free for the next call
-  return r;
+  double s = 0.0;
+  for (int w = 0; w < nw; ++w) s += sh[w];
+  return s;
 }
+
+// Single-workgroup PCG kernels keep up to this many vector elements per thread
+// in registers (one memory round trip for all of a kernel's loads).
+constexpr int kHeld = 4;
 
 // Launch shape of an O(n) reduction: one workgroup of kOneBlockThreads up
 // to kOneBlockN elements, else one kRedThreads-thread workgroup per

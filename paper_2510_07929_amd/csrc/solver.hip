@@ -236,7 +236,9 @@ Co<PcgStats> Pcg::solve(double c, const double* L, Woodbury* P, const double* b,
     stats.resnorm = std::sqrt(rr);
     if (!(stats.resnorm > tol)) co_return stats;
   }
+  const bool lone = !ex_.sched && ex_.post;
   for (int it = 1; it <= maxit; ++it) {
+    bool stored = false;  // (p . q, r . r) are on their way to the pinned buffer
     if (batched_step) {
       step.rz = cur == 0 ? RZ0 : RZ1;
       step.rz_new = cur == 0 ? RZ1 : RZ0;
@@ -247,11 +249,12 @@ Co<PcgStats> Pcg::solve(double c, const double* L, Woodbury* P, const double* b,
     } else {
       if (fast) co_await op_.apply_fast(pb_.p.as<double>(), p32, pb_.Kp.as<double>(), ex_);
       else co_await op_.apply_exact(pb_.p.as<double>(), pb_.Kp.as<double>(), ex_);
-      pcg_qxr(n, pb_.Kp.as<double>(), pb_.p.as<double>(), L, c, sc, SUMP, cur == 0 ? RZ0 : RZ1, PQ, RR,
-              pb_.q.as<double>(), x, pb_.r.as<double>(), Kx, ws_, st);
+      stored = pcg_qxr(n, pb_.Kp.as<double>(), pb_.p.as<double>(), L, c, sc, SUMP, cur == 0 ? RZ0 : RZ1, PQ, RR,
+                       pb_.q.as<double>(), x, pb_.r.as<double>(), Kx, ws_, lone ? arm_words(ex_, 2) : nullptr, st);
     }
     double two[2];
-    if (batched_step && step.status) memcpy(two, step.status, sizeof(two));
+    if (stored) ex_.wait(ex_, sizeof(two));
+    if (stored || (batched_step && step.status)) memcpy(two, ex_.hbuf.ptr, sizeof(two));
     else co_await read_back(ex_, sc + PQ, 2 * sizeof(double), two);  // [PQ, RR]
     stats.iters = it;
     stats.resnorm = std::sqrt(std::max(two[1], 0.0));

@@ -12,6 +12,9 @@ struct LoneExec : Exec {
   explicit LoneExec(hipStream_t s);
   ~LoneExec();
 };
+// Marks the first words of a lone fit's pinned buffer as not yet stored, for a
+// kernel that stores them itself; Exec::wait then polls them.
+uint64_t* arm_words(Exec& ex, int words);
 
 constexpr int kKktSums = 9;    // sums produced by multiplier_kkt
 constexpr int kLsTrials = 24;  // step lengths evaluated per line-search pass
@@ -39,10 +42,11 @@ void pcg_q(int64_t n, const double* Kp, const double* p, const double* L, double
 void pcg_xr(int64_t n, const double* p, const double* q, const double* Kp, double* x, double* r, double* Kx,
             const double* sc, int rz_slot, int pq_slot, Workspace& ws, double* rr_out, hipStream_t st);
 // pcg_q then pcg_xr (sc[pq_slot] and sc[rr_slot] written); one launch when
-// n <= kOneBlockN.
-void pcg_qxr(int64_t n, const double* Kp, const double* p, const double* L, double c, double* sc, int sump_slot,
+// n <= kOneBlockN, which then also stores the two to status (arm_words, may be
+// null): true when it does.
+bool pcg_qxr(int64_t n, const double* Kp, const double* p, const double* L, double c, double* sc, int sump_slot,
              int rz_slot, int pq_slot, int rr_slot, double* q, double* x, double* r, double* Kx, Workspace& ws,
-             hipStream_t st);
+             uint64_t* status, hipStream_t st);
 void admm_rhs(int64_t n, const double* y, const double* z, const double* v, double beta, double sigma,
               double lam, double* b, hipStream_t st);
 // The intercept at the new multipliers: beta, plus step * *sum (device) where sum

@@ -845,7 +845,8 @@ __global__ __launch_bounds__(1024) void wood_out_kernel(int64_t n, int r, const 
 // One workgroup (n <= kOneBlockN): wood_out with its dot product, then PCG's
 // direction update p = out + beta p (beta = the new dot over sc[rz_old]),
 // p32, sum(p) -- the same per-thread order and block sums as wood_out_kernel
-// followed by pcg_p_kernel.
+// followed by pcg_p_kernel.  Up to kHeld elements per thread all loads come
+// first.  n = 2000: 5.0 us before, 4.2 us now.
 __device__ __forceinline__ void wood_out_p_one_body(int64_t n, int r, const double* __restrict__ L,
                                                     const double* __restrict__ g, const double* __restrict__ Fs,
                                                     const double* __restrict__ s, double* __restrict__ out,
@@ -853,25 +854,69 @@ __device__ __forceinline__ void wood_out_p_one_body(int64_t n, int r, const doub
                                                     int rz_new, int sump, int first, double* __restrict__ p,
                                                     float* __restrict__ p32) {
   const double sr = s[r];
-  double acc = 0.0;
-  for (int64_t i = threadIdx.x; i < n; i += blockDim.x) {
-    const double fs = r > 0 ? Fs[i] : 0.0;
-    const double o = g[i] - (fs + sr) / L[i];
-    out[i] = o;
-    acc = fma(o, dot_with[i], acc);
+  const double rz0 = first ? 1.0 : sc[rz_old];
+  double rz, sum;
+  if (n <= kHeld * kOneBlockThreads) {
+    double gv[kHeld], fv[kHeld], lv[kHeld], dv[kHeld], pv[kHeld], ov[kHeld];
+#pragma unroll
+    for (int e = 0; e < kHeld; ++e) {
+      if (e * kOneBlockThreads >= n) break;  // (uniform)
+      const int i = min(int(threadIdx.x) + e * kOneBlockThreads, int(n) - 1);
+      gv[e] = g[i];
+      fv[e] = r > 0 ? Fs[i] : 0.0;
+      lv[e] = L[i];
+      dv[e] = dot_with[i];
+      pv[e] = first ? 0.0 : p[i];
+    }
+    double acc = 0.0;
+#pragma unroll
+    for (int e = 0; e < kHeld; ++e) {
+      if (e * kOneBlockThreads >= n) break;
+      const int i = int(threadIdx.x) + e * kOneBlockThreads;
+      const double o = gv[e] - (fv[e] + sr) / lv[e];
+      ov[e] = o;
+      if (i < n) {
+        out[i] = o;
+        acc = fma(o, dv[e], acc);
+      }
+    }
+    rz = block_sum_all<0>(acc);
+    const double beta = first ? 0.0 : rz / rz0;
+    acc = 0.0;
+#pragma unroll
+    for (int e = 0; e < kHeld; ++e) {
+      const int i = int(threadIdx.x) + e * kOneBlockThreads;
+      if (i < n) {
+        const double pi = first ? ov[e] : fma(beta, pv[e], ov[e]);
+        p[i] = pi;
+        if (p32) p32[i] = float(pi);
+        acc += pi;
+      }
+    }
+    sum = block_sum_all<1>(acc);
+  } else {
+    double acc = 0.0;
+    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) {
+      const double fs = r > 0 ? Fs[i] : 0.0;
+      const double o = g[i] - (fs + sr) / L[i];
+      out[i] = o;
+      acc = fma(o, dot_with[i], acc);
+    }
+    rz = block_sum_all<0>(acc);
+    const double beta = first ? 0.0 : rz / rz0;
+    acc = 0.0;
+    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) {  // out[i] was written by this thread
+      const double pi = first ? out[i] : fma(beta, p[i], out[i]);
+      p[i] = pi;
+      if (p32) p32[i] = float(pi);
+      acc += pi;
+    }
+    sum = block_sum_all<1>(acc);
   }
-  const double rz = block_sum_all(acc);
-  if (threadIdx.x == 0) sc[rz_new] = rz;
-  const double beta = first ? 0.0 : rz / sc[rz_old];
-  acc = 0.0;
-  for (int64_t i = threadIdx.x; i < n; i += blockDim.x) {  // out[i] was written by this thread
-    const double pi = first ? out[i] : fma(beta, p[i], out[i]);
-    p[i] = pi;
-    if (p32) p32[i] = float(pi);
-    acc += pi;
+  if (threadIdx.x == 0) {
+    sc[rz_new] = rz;
+    sc[sump] = sum;
   }
-  const double sum = block_sum_all(acc);
-  if (threadIdx.x == 0) sc[sump] = sum;
 }
 
 __global__ __launch_bounds__(1024) void wood_out_p_one_kernel(int64_t n, int r, const double* __restrict__ L,
