@@ -255,6 +255,13 @@ void pcg_xr(int64_t n, const double* p, const double* q, const double* Kp, doubl
   finish(g, ws.partials, 1, rr_out, st);
 }
 
+// a b rounded by itself: never joined with a later sum into one FMA (in the
+// general path the product and the sum are in different blocks)
+__device__ __forceinline__ double mul_f64(double a, double b) {
+#pragma clang fp contract(off)
+  return a * b;
+}
+
 // One workgroup (n <= kOneBlockN): pcg_q and pcg_xr in one launch, with the
 // same per-thread order and block sums as the two kernels (bitwise the same).
 // Up to kHeld elements per thread every vector is read once, all loads before
@@ -282,7 +289,7 @@ __device__ __forceinline__ void pcg_qxr_one_body(int64_t n, const double* __rest
       rv[e] = r[i];
       Kv[e] = Kx ? Kx[i] : 0.0;
     }
-    const double cs = c * sump;
+    const double cs = mul_f64(c, sump);
     double acc = 0.0;
 #pragma unroll
     for (int e = 0; e < kHeld; ++e) {
@@ -308,7 +315,7 @@ __device__ __forceinline__ void pcg_qxr_one_body(int64_t n, const double* __rest
     }
     rr = block_sum_all<1>(acc);
   } else {
-    const double cs = c * sump;
+    const double cs = mul_f64(c, sump);
     double acc = 0.0;
     for (int64_t i = threadIdx.x; i < n; i += blockDim.x) {
       const double pi = p[i];
