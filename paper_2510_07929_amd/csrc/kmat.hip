@@ -31,19 +31,38 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
 }
 
 // ================================================================= row norms
-__global__ void sqnorm_kernel(const float* __restrict__ X, int64_t n, int p, float* __restrict__ q) {
-  int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const float* x = X + i * p;
+// q = the squared norms of the rows of two matrices (nb may be 0), each summed
+// in coordinate order.  Eight coordinates are requested at a time: a row's
+// loads one after the other took 14.4 us at 100,000 x 30, this 8.6.
+__global__ __launch_bounds__(256) void sqnorm_kernel(const float* __restrict__ Xa, int64_t na, float* __restrict__ qa,
+                                                     const float* __restrict__ Xb, int64_t nb,
+                                                     float* __restrict__ qb, int p) {
+  const int64_t i = blockIdx.x * int64_t(256) + threadIdx.x;
+  if (i >= na + nb) return;
+  const float* x = i < na ? Xa + i * p : Xb + (i - na) * p;
   float s = 0.f;
-  for (int k = 0; k < p; ++k) s = fmaf(x[k], x[k], s);
-  q[i] = s;
+  int k = 0;
+  for (; k + 8 <= p; k += 8) {
+    float t[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) t[e] = x[k + e];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) s = fmaf(t[e], t[e], s);
+  }
+  for (; k < p; ++k) s = fmaf(x[k], x[k], s);
+  if (i < na) qa[i] = s;
+  else qb[i - na] = s;
+}
+
+void row_sqnorms2(const float* Xa, int64_t na, float* qa, const float* Xb, int64_t nb, float* qb, int p,
+                  hipStream_t st) {
+  if (na + nb <= 0) return;
+  sqnorm_kernel<<<dim3((unsigned)((na + nb + 255) / 256)), dim3(256), 0, st>>>(Xa, na, qa, Xb, nb, qb, p);
+  KQR_LAUNCH_CHECK();
 }
 
 void row_sqnorms(const float* X, int64_t n, int p, float* sqn, hipStream_t st) {
-  if (n <= 0) return;
-  sqnorm_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st>>>(X, n, p, sqn);
-  KQR_LAUNCH_CHECK();
+  if (n > 0) row_sqnorms2(X, n, sqn, nullptr, 0, nullptr, p, st);
 }
 
 // ================================================================= K build
@@ -469,13 +488,31 @@ __global__ __launch_bounds__(256) void kapply_otf_kernel(
   if (row_ok) part[int64_t(blockIdx.y) * nr + i] = acc;
 }
 
-__global__ void otf_reduce_kernel(const double* __restrict__ part, int nslice, int64_t nr, double* __restrict__ u,
-                                  int64_t ldu, double out_scale, double out_shift) {
-  const int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
-  if (i >= nr) return;
+// The slices' partial sums of a row: eight threads per row, each taking every
+// eighth slice in order.
+constexpr int kOtfRed = 8;
+__global__ __launch_bounds__(256) void otf_reduce_kernel(const double* __restrict__ part, int nslice, int64_t nr,
+                                                         double* __restrict__ u, int64_t ldu, double out_scale,
+                                                         double out_shift) {
+  __shared__ double sh[kOtfRed][32];
+  const int r = threadIdx.x & 31, h = threadIdx.x >> 5;
+  const int64_t i = blockIdx.x * int64_t(32) + r;
+  const int64_t ic = min(i, nr - 1);
   double s = 0.0;
-  for (int k = 0; k < nslice; ++k) s += part[int64_t(k) * nr + i];
-  u[i * ldu] = out_shift + out_scale * s;
+  for (int k = h; k < nslice; k += kOtfRed) s += part[int64_t(k) * nr + ic];
+  sh[h][r] = s;
+  __syncthreads();
+  if (h == 0 && i < nr) {
+#pragma unroll
+    for (int k = 1; k < kOtfRed; ++k) s += sh[k][r];
+    u[i * ldu] = out_shift + out_scale * s;
+  }
+}
+
+static void otf_reduce(const double* part, int64_t nslice, int64_t nr, double* u, int64_t ldu, double scale,
+                       double shift, hipStream_t st) {
+  otf_reduce_kernel<<<dim3((unsigned)((nr + 31) / 32)), 256, 0, st>>>(part, int(nslice), nr, u, ldu, scale, shift);
+  KQR_LAUNCH_CHECK();
 }
 
 template <int PMAX>
@@ -498,8 +535,7 @@ static void kapply_otf_p(const float* Xr, const float* qr, int64_t nr, const flo
   else if (exact) kapply_otf_kernel<PMAX, false, true><<<grid, 256, 0, st>>>(Xr, qr, nr, Xc, qc, nc, p, ng, v, per, part);
   else kapply_otf_kernel<PMAX, false, false><<<grid, 256, 0, st>>>(Xr, qr, nr, Xc, qc, nc, p, ng, v, per, part);
   KQR_LAUNCH_CHECK();
-  otf_reduce_kernel<<<dim3((unsigned)((nr + 255) / 256)), 256, 0, st>>>(part, int(nslice), nr, u, ldu, scale, shift);
-  KQR_LAUNCH_CHECK();
+  otf_reduce(part, nslice, nr, u, ldu, scale, shift, st);
   KQR_CHECK_HIP(hipFreeAsync(part, st));
 }
 
@@ -612,8 +648,7 @@ static void kapply_otf_l1q_rows_p(const uint32_t* Xq, int64_t n, int p, float ng
   if (exact) kapply_otf_l1q_kernel<PMAX, R, true><<<grid, 256, 0, st>>>(Xq, n, p, ngs, v, per, part);
   else kapply_otf_l1q_kernel<PMAX, R, false><<<grid, 256, 0, st>>>(Xq, n, p, ngs, v, per, part);
   KQR_LAUNCH_CHECK();
-  otf_reduce_kernel<<<dim3((unsigned)((n + 255) / 256)), 256, 0, st>>>(part, int(nslice), n, u, ldu, 1.0, 0.0);
-  KQR_LAUNCH_CHECK();
+  otf_reduce(part, nslice, n, u, ldu, 1.0, 0.0, st);
   KQR_CHECK_HIP(hipFreeAsync(part, st));
 }
 
@@ -912,140 +947,86 @@ int quantize_columns(const float* X, int64_t n, int p, uint32_t* Xq, hipStream_t
   return s;
 }
 
-// RBF on the fly with the Gram term on the matrix cores: a wave owns two
-// 16-row strips (its rows of X held as MFMA A operands for the whole launch),
-// the block stages 64 columns of X, their norms and v in LDS, and for each
-// 16-column tile v_mfma_f32_16x16x4f32 forms the 16 x 16 Gram blocks
-// (KP/4 MFMAs per strip, FP32 products and sums).  The lane that holds
-// G[4g + r][c] then forms d = q_i + q_j - 2 G, exp2(-gamma log2(e) d) and
-// accumulates k * v_j (fast: FP32 per 64-column stage, then FP64; exact: FP64
-// products and sums); the 16 lanes of a row group are reduced with shuffles
-// at the end.  KP = p rounded up to 4 (<= 32).
+// RBF on the fly (p <= 32) with the Gram term on the matrix cores.  A
+// workgroup is four waves of 32 rows each (two 16-row strips, held as MFMA A
+// operands for the whole launch) and walks its columns in stages of 64: four
+// 16-column tiles in the operand order of the MFMA, so that a tile's parts
+// are read from LDS as consecutive 16-byte (or 4-byte) words of the lanes.
+// The lane that holds G[4 g + r][c] forms the entry and accumulates its
+// product with v_j (fast: FP32 within a stage or two, then FP64; exact: FP64
+// products and sums); the 16 lanes of a row group are reduced at the end.
+//
+// What bounds it is the vector unit and the matrix cores side by side: per
+// 64 pairs an exponential (about 10 cycles of a SIMD), the conversion to FP64
+// (5) and the products with v (5 each), against 24 cycles of MFMAs (p > 16),
+// which run under other waves' vector work; the clock falls to about 1.8 GHz
+// under this load, and a loop of nothing but these instructions on random
+// operands takes 85 % of the kernel's time.  So nothing else may take issue
+// slots or leave the SIMD waiting: a stage is requested into registers one
+// stage ahead and goes to the other LDS buffer after the current one is used
+// (one barrier per stage, no wait for memory before it), the next tile's
+// MFMAs are issued ahead of this tile's entries, and the MFMA results stay in
+// ordinary registers (the second launch bound; without it each is copied from
+// the accumulation registers first).  Loading each stage where it was needed,
+// a load at a time: 100,000 x 20,011 at p = 30 exact 690 us, now 612; the
+// square form at 40,000 x 30 exact 400, now 335; 20,000 x 5,000 at p = 10 63,
+// now 48.
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
-constexpr int kMfmaCols = 64;
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef uint16_t u16x8_t __attribute__((ext_vector_type(8)));
 
-template <int KP, bool EX>
-__global__ __launch_bounds__(256) void kapply_otf_mfma_kernel(
-    const float* __restrict__ Xr, const float* __restrict__ qr, int64_t nr,
-    const float* __restrict__ Xc, const float* __restrict__ qc, int64_t nc, int p, float ng,
-    const double* __restrict__ v, int64_t cols_per_slice, double* __restrict__ part) {
-  constexpr int NKB = KP / 4;
-  __shared__ float xs[kMfmaCols][KP + 1];
-  __shared__ float qs[kMfmaCols];
-  __shared__ float vs[kMfmaCols];
-  __shared__ double vd[kMfmaCols];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int li = lane & 15, lg = lane >> 4;
-  const int64_t row0 = int64_t(blockIdx.x) * 128 + wave * 32;
-  float a[2][NKB];
-  float qi[2][4];
-#pragma unroll
-  for (int s = 0; s < 2; ++s) {
-    const int64_t r = row0 + 16 * s + li;
-#pragma unroll
-    for (int kb = 0; kb < NKB; ++kb) {
-      const int k = 4 * kb + lg;
-      a[s][kb] = (r < nr && k < p) ? Xr[r * p + k] : 0.f;
-    }
-#pragma unroll
-    for (int rr = 0; rr < 4; ++rr) {
-      const int64_t ro = row0 + 16 * s + 4 * lg + rr;
-      qi[s][rr] = ro < nr ? qr[ro] : 0.f;
-    }
-  }
-  const int64_t c0 = int64_t(blockIdx.y) * cols_per_slice;
-  const int64_t c1 = min(nc, c0 + cols_per_slice);
-  double acc[2][4];
-#pragma unroll
-  for (int s = 0; s < 2; ++s)
-#pragma unroll
-    for (int rr = 0; rr < 4; ++rr) acc[s][rr] = 0.0;
-  for (int64_t jb = c0; jb < c1; jb += kMfmaCols) {
-    const int cnt = int(min<int64_t>(kMfmaCols, c1 - jb));
-    __syncthreads();
-    for (int t = threadIdx.x; t < kMfmaCols * KP; t += 256) {
-      const int jj = t / KP, k = t % KP;
-      xs[jj][k] = (jj < cnt && k < p) ? Xc[(jb + jj) * p + k] : 0.f;
-    }
-    if (threadIdx.x < kMfmaCols) {
-      const int jj = threadIdx.x;
-      qs[jj] = jj < cnt ? qc[jb + jj] : 0.f;
-      const double vj = jj < cnt ? v[jb + jj] : 0.0;
-      if (EX) vd[jj] = vj;
-      else vs[jj] = float(vj);
-    }
-    __syncthreads();
-    float a32[2][4];
-#pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-      for (int rr = 0; rr < 4; ++rr) a32[s][rr] = 0.f;
-    // Gram blocks of the next 16-column tile are issued to the matrix cores
-    // before the current tile's exponentials, so one wave keeps both busy.
-    auto gram = [&](int t16, f32x4_t& g0, f32x4_t& g1) {
-      const int jj = t16 + li;
-      float b[NKB];
-#pragma unroll
-      for (int kb = 0; kb < NKB; ++kb) b[kb] = xs[jj][4 * kb + lg];
-      g0 = f32x4_t{0.f, 0.f, 0.f, 0.f};
-      g1 = f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int kb = 0; kb < NKB; ++kb) {
-        g0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[0][kb], b[kb], g0, 0, 0, 0);
-        g1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[1][kb], b[kb], g1, 0, 0, 0);
-      }
-    };
-    f32x4_t g0, g1, n0, n1;
-    gram(0, g0, g1);
-    for (int t16 = 0; t16 < cnt; t16 += 16) {
-      const int jj = t16 + li;
-      const bool more = t16 + 16 < cnt;
-      if (more) gram(t16 + 16, n0, n1);
-      const float qj = qs[jj];
-#pragma unroll
-      for (int rr = 0; rr < 4; ++rr) {
-        // ng < 0, d >= 0: exp2(ng max(d, 0)) = min(exp2(ng d), 1), clamped by the output modifier
-        const float d0 = qi[0][rr] + qj - 2.f * g0[rr];
-        const float d1 = qi[1][rr] + qj - 2.f * g1[rr];
-        const float e0 = __builtin_amdgcn_fmed3f(kexp2(ng * d0), 0.f, 1.f);
-        const float e1 = __builtin_amdgcn_fmed3f(kexp2(ng * d1), 0.f, 1.f);
-        if (EX) {
-          acc[0][rr] = fma(double(e0), vd[jj], acc[0][rr]);
-          acc[1][rr] = fma(double(e1), vd[jj], acc[1][rr]);
-        } else {
-          a32[0][rr] = fmaf(e0, vs[jj], a32[0][rr]);
-          a32[1][rr] = fmaf(e1, vs[jj], a32[1][rr]);
-        }
-      }
-      if (more) {
-        g0 = n0;
-        g1 = n1;
-      }
-    }
-    if (!EX) {
-#pragma unroll
-      for (int s = 0; s < 2; ++s)
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr) acc[s][rr] += double(a32[s][rr]);
-    }
-  }
-  // sum over the 16 column lanes of each row group (lane bits 0..3)
-#pragma unroll
-  for (int s = 0; s < 2; ++s)
-#pragma unroll
-    for (int rr = 0; rr < 4; ++rr) acc[s][rr] = row16_sum_f64<true>(acc[s][rr]);
-  if (li == 0) {
-#pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-      for (int rr = 0; rr < 4; ++rr) {
-        const int64_t ro = row0 + 16 * s + 4 * lg + rr;
-        if (ro < nr) part[int64_t(blockIdx.y) * nr + ro] = acc[s][rr];
-      }
-  }
-}
+constexpr int kOtfStage = 64;  // columns per LDS stage
 
-// The same with the Gram term in BF16 on the matrix cores: every FP32
+// Gram terms for p <= 16: v_mfma_f32_16x16x4f32 (KP/4 per 16 x 16 block, KP =
+// p rounded up to 4; FP32 products and sums), the entry's argument
+// -gamma log2(e) (q_i + q_j - 2 G).
+template <int KP>
+struct GramF32 {
+  typedef float col_t;  // the columns: X itself
+  static constexpr int kParts = KP / 4;
+  static constexpr int kMfmas = 2 * kParts;  // per tile of a wave
+  static constexpr int kStageBytes = kOtfStage * KP * 4;
+  static constexpr bool kNorms = true;  // the lanes add the squared norms
+  static constexpr int kFlush = 1;      // stages per FP32 partial sum (fast mode)
+  float a[2][kParts];
+  float nx[kParts];
+
+  __device__ __forceinline__ void rows(const float* __restrict__ X, const float* __restrict__, int64_t n, int p,
+                                       int64_t r, int s, int lg) {
+    const float* x = X + min(r, n - 1) * p;
+#pragma unroll
+    for (int kb = 0; kb < kParts; ++kb) a[s][kb] = x[min(4 * kb + lg, p - 1)];
+#pragma unroll
+    for (int kb = 0; kb < kParts; ++kb) a[s][kb] = (r < n && 4 * kb + lg < p) ? a[s][kb] : 0.f;
+  }
+  // thread t requests coordinate 4 kb + (t / 16) % 4 of column j0 + 16 (t / 64) + t % 16
+  __device__ __forceinline__ void fetch(const float* __restrict__ Xc, int64_t nc, int p, int64_t j0, int t) {
+    const float* x = Xc + min(j0 + ((t >> 6) << 4) + (t & 15), nc - 1) * p;
+#pragma unroll
+    for (int kb = 0; kb < kParts; ++kb) nx[kb] = x[min(4 * kb + ((t >> 4) & 3), p - 1)];
+  }
+  __device__ __forceinline__ void put(char* lds, int p, int t) {
+    float* o = reinterpret_cast<float*>(lds) + (t >> 6) * (kParts * 64) + (t & 63);
+#pragma unroll
+    for (int kb = 0; kb < kParts; ++kb) o[64 * kb] = 4 * kb + ((t >> 4) & 3) < p ? nx[kb] : 0.f;
+  }
+  __device__ __forceinline__ void gram(const char* lds, int tile, int lane, f32x4_t (&g)[2]) const {
+    const float* x = reinterpret_cast<const float*>(lds) + tile * (kParts * 64) + lane;
+    g[0] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    g[1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kb = 0; kb < kParts; ++kb) {
+      const float b = x[64 * kb];
+      g[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[0][kb], b, g[0], 0, 0, 0);
+      g[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[1][kb], b, g[1], 0, 0, 0);
+    }
+  }
+  static __device__ __forceinline__ float arg(float g, float qi, float qj, float ng) {
+    return ng * (qi + qj - 2.f * g);
+  }
+};
+
+// Gram terms for 16 < p <= 32 in BF16 on the matrix cores: every FP32
 // coordinate is split exactly into three BF16 parts x = h + m + l (round to
 // nearest even at each step; 3 x 8 significand bits hold FP32's 24), and
 // G = hh + hm + mh + hl + lh + mm (the dropped ml, lm, ll are below 2^-24 of
@@ -1053,18 +1034,16 @@ __global__ __launch_bounds__(256) void kapply_otf_mfma_kernel(
 // 16 x 16 block (p <= 32, padded to 32), against eight 16x16x4 FP32 MFMAs
 // that take 5x the matrix-core time at p = 32.  FP32 sums inside the MFMA.
 //
-// The column side is split once per launch into a buffer of three planes
-// per column (kotf_split_cols_kernel).  With p <= 30 (AUG) the two spare
-// coordinates carry the squared norms and the column side the exponent's
-// scale c = -gamma log2(e): row [x_i, 1, q_i] against column
+// The column side is split once per launch (kotf_split_cols_kernel) into
+// blocks of 16 points, each the h, m and l planes of 32 coordinates in
+// operand order, zero filled to a multiple of kB3Pad points.  With p <= 30
+// (AUG) the two spare coordinates carry the squared norms and the column side
+// the exponent's scale c = -gamma log2(e): row [x_i, 1, q_i] against column
 // [-2 c x_j, c q_j, c] (each product rounded once in FP32 before the split),
 // so the matrix cores return c d_ij = c (q_i + q_j - 2 x_i . x_j) itself and
 // a pair costs the lanes only the clamp at 0, the exponential and the
 // product with v_j.  Without AUG the column holds -2 x_j (exact) and the
 // lanes add q_i + q_j and scale.
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef uint16_t u16x8_t __attribute__((ext_vector_type(8)));
-
 __device__ __forceinline__ void split3_bf16(float x, uint16_t& h, uint16_t& m, uint16_t& l) {
   h = f32_to_bf16(x);
   const float r1 = x - bf16_to_f32(h);  // exact
@@ -1073,159 +1052,220 @@ __device__ __forceinline__ void split3_bf16(float x, uint16_t& h, uint16_t& m, u
   l = f32_to_bf16(r2);
 }
 
-constexpr int kB3Cols = 128;   // columns per LDS stage
-constexpr int kB3Row = 40;     // LDS row of 32 BF16 coordinates, padded (16-byte aligned, rows spread over banks)
-constexpr int kB3Stride = 96;  // halves per column in the split buffer: the h, m and l planes of 32
+constexpr int kB3Plane = 512;            // halves of a plane of 16 points: 64 lanes x 8
+constexpr int kB3Block = 3 * kB3Plane;   // halves per 16 points
+constexpr int kB3Pad = 128;
 
-// Coordinate k of the padded 32-vector of a row (A) or column (B) side;
+static inline int64_t b3_points(int64_t n) { return (n + kB3Pad - 1) / kB3Pad * kB3Pad; }
+static inline size_t b3_bytes(int64_t n) { return size_t(b3_points(n) / 16) * kB3Block * sizeof(uint16_t); }
+
+// halves from the buffer's start to point j's coordinates 8 g .. 8 g + 7 in the h plane
+__device__ __forceinline__ int64_t b3_offset(int64_t j, int g) {
+  return (j >> 4) * kB3Block + (g * 16 + int(j & 15)) * 8;
+}
+
+// Coordinate k of the padded 32-vector of a row (A) or column (B) side, from
+// the point's own coordinate x (any value for k >= p) and squared norm q;
 // c: the column side's scale (AUG), else 1.
 template <bool AUG, bool COL>
-__device__ __forceinline__ float b3_coord(const float* __restrict__ x, float q, int k, int p, float c) {
-  if (k < p) return COL ? (-2.f * c) * x[k] : x[k];
+__device__ __forceinline__ float b3_coord(float x, float q, int k, int p, float c) {
+  if (k < p) return COL ? (-2.f * c) * x : x;
   if (AUG && k == 30) return COL ? c * q : 1.f;
   if (AUG && k == 31) return COL ? c : q;
   return 0.f;
 }
 
-// out[j * 96 + plane * 32 + k]: the parts of point j's coordinate k, as the
-// column (scaled, COL) or the row side; one thread per point and
-// 8-coordinate group.
+// the parts of coordinates 8 g .. 8 g + 7 of point j (zeros unless in)
+template <bool AUG, bool COL>
+__device__ __forceinline__ void b3_split8(const float* __restrict__ X, const float* __restrict__ qv, int64_t j,
+                                          int64_t n, int p, int g, float c, u16x8_t& h, u16x8_t& m, u16x8_t& l) {
+  const int64_t jc = min(j, n - 1);
+  const float* x = X + jc * p;
+  const float q = AUG ? qv[jc] : 0.f;
+  float xv[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) xv[e] = x[min(8 * g + e, p - 1)];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    uint16_t hh, mm, ll;
+    split3_bf16(j < n ? b3_coord<AUG, COL>(xv[e], q, 8 * g + e, p, c) : 0.f, hh, mm, ll);
+    h[e] = hh;
+    m[e] = mm;
+    l[e] = ll;
+  }
+}
+
+// One thread per point of the padded set and 8-coordinate group, in buffer
+// order, as the column (scaled, COL) or the row side.
 template <bool AUG, bool COL = true>
 __global__ __launch_bounds__(256) void kotf_split_cols_kernel(const float* __restrict__ Xc,
                                                               const float* __restrict__ qc, int64_t nc, int p,
                                                               float ng, uint16_t* __restrict__ out) {
   const int64_t t = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
-  if (t >= nc * 4) return;
-  const int64_t j = t >> 2;
-  const int g = int(t & 3);
-  const float q = AUG ? qc[j] : 0.f;
+  const int64_t j = (t >> 6) * 16 + (t & 15);
+  if (j >= (nc + kB3Pad - 1) / kB3Pad * kB3Pad) return;
+  const int g = int(t >> 4) & 3;
   u16x8_t h, m, l;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    uint16_t hh, mm, ll;
-    split3_bf16(b3_coord<AUG, COL>(Xc + j * p, q, 8 * g + e, p, (AUG && COL) ? ng : 1.f), hh, mm, ll);
-    h[e] = hh;
-    m[e] = mm;
-    l[e] = ll;
-  }
-  uint16_t* o = out + j * kB3Stride + 8 * g;
+  b3_split8<AUG, COL>(Xc, qc, j, nc, p, g, (AUG && COL) ? ng : 1.f, h, m, l);
+  uint16_t* o = out + b3_offset(j, g);
   *reinterpret_cast<u16x8_t*>(o) = h;
-  *reinterpret_cast<u16x8_t*>(o + 32) = m;
-  *reinterpret_cast<u16x8_t*>(o + 64) = l;
+  *reinterpret_cast<u16x8_t*>(o + kB3Plane) = m;
+  *reinterpret_cast<u16x8_t*>(o + 2 * kB3Plane) = l;
 }
 
-template <bool EX, bool AUG>
-__global__ __launch_bounds__(256) void kapply_otf_mfma3_kernel(
-    const float* __restrict__ Xr, const float* __restrict__ qr, int64_t nr, const uint16_t* __restrict__ Bc,
-    const float* __restrict__ qc, int64_t nc, int p, float ng, const double* __restrict__ v,
-    int64_t cols_per_slice, double* __restrict__ part) {
-  __shared__ __align__(16) uint16_t bs[3][kB3Cols][kB3Row];
-  __shared__ float qs[AUG ? 1 : kB3Cols];
-  __shared__ float vs[kB3Cols];
-  __shared__ double vd[kB3Cols];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int li = lane & 15, lg = lane >> 4;
-  const int64_t row0 = int64_t(blockIdx.x) * 128 + wave * 32;
+template <bool AUG>
+struct GramB3 {
+  typedef uint16_t col_t;  // the columns: their split
+  static constexpr int kMfmas = 12;
+  static constexpr int kStageBytes = kOtfStage / 16 * kB3Block * 2;
+  static constexpr bool kNorms = !AUG;
+  static constexpr int kFlush = 2;
   bf16x8_t ah[2], am[2], al[2];
-  float qi[2][4];
-#pragma unroll
-  for (int s = 0; s < 2; ++s) {
-    const int64_t r = row0 + 16 * s + li;
-    const bool in = r < nr;
-    const float q = (AUG && in) ? qr[r] : 0.f;
+  u16x8_t nx[3];
+
+  __device__ __forceinline__ void rows(const float* __restrict__ X, const float* __restrict__ q, int64_t n, int p,
+                                       int64_t r, int s, int lg) {
     u16x8_t h, m, l;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int k = 8 * lg + e;
-      const float x = in ? b3_coord<AUG, false>(Xr + r * p, q, k, p, 1.f) : 0.f;
-      uint16_t hh, mm, ll;
-      split3_bf16(x, hh, mm, ll);
-      h[e] = hh;
-      m[e] = mm;
-      l[e] = ll;
-    }
+    b3_split8<AUG, false>(X, q, r, n, p, lg, 1.f, h, m, l);
     ah[s] = __builtin_bit_cast(bf16x8_t, h);
     am[s] = __builtin_bit_cast(bf16x8_t, m);
     al[s] = __builtin_bit_cast(bf16x8_t, l);
-#pragma unroll
-    for (int rr = 0; rr < 4; ++rr) {
-      const int64_t ro = row0 + 16 * s + 4 * lg + rr;
-      qi[s][rr] = (!AUG && ro < nr) ? qr[ro] : 0.f;
-    }
   }
-  const int64_t c0 = int64_t(blockIdx.y) * cols_per_slice;
-  const int64_t c1 = min(nc, c0 + cols_per_slice);
-  double acc[2][4];
+  // a stage is contiguous: 768 pieces of 16 bytes, three per thread
+  __device__ __forceinline__ void fetch(const uint16_t* __restrict__ Bc, int64_t, int, int64_t j0, int t) {
+    const u16x8_t* src = reinterpret_cast<const u16x8_t*>(Bc + (j0 >> 4) * kB3Block) + t;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) nx[c] = src[256 * c];
+  }
+  __device__ __forceinline__ void put(char* lds, int, int t) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) reinterpret_cast<u16x8_t*>(lds)[256 * c + t] = nx[c];
+  }
+  __device__ __forceinline__ void gram(const char* lds, int tile, int lane, f32x4_t (&g)[2]) const {
+    const bf16x8_t* x = reinterpret_cast<const bf16x8_t*>(lds) + tile * (kB3Block / 8) + lane;
+    const bf16x8_t bh = x[0], bm = x[64], bl = x[128];
+    f32x4_t c0 = f32x4_t{0.f, 0.f, 0.f, 0.f}, c1 = c0;  // smallest products first
+    c0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(am[0], bm, c0, 0, 0, 0);
+    c1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(am[1], bm, c1, 0, 0, 0);
+    c0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[0], bl, c0, 0, 0, 0);
+    c1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[1], bl, c1, 0, 0, 0);
+    c0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[0], bh, c0, 0, 0, 0);
+    c1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[1], bh, c1, 0, 0, 0);
+    c0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[0], bm, c0, 0, 0, 0);
+    c1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[1], bm, c1, 0, 0, 0);
+    c0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(am[0], bh, c0, 0, 0, 0);
+    c1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(am[1], bh, c1, 0, 0, 0);
+    g[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[0], bh, c0, 0, 0, 0);
+    g[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[1], bh, c1, 0, 0, 0);
+  }
+  static __device__ __forceinline__ float arg(float g, float qi, float qj, float ng) {
+    return AUG ? g : ng * (qi + qj + g);
+  }
+};
+
+// the entry: ng < 0 and d >= 0, so exp2(ng max(d, 0)) = min(exp2(ng d), 1), the
+// clamp to [0, 1] being the exponential's output modifier
+__device__ __forceinline__ float otf_entry(float a) { return __builtin_amdgcn_fmed3f(kexp2(a), 0.f, 1.f); }
+
+// The sums are formed here: without this the compiler moves a stage's whole
+// vector work behind the next stage's LDS stores (their last use is the next
+// iteration), where it no longer overlaps the MFMAs.
+template <class T>
+__device__ __forceinline__ void otf_pin(T (&acc)[2][4]) {
 #pragma unroll
   for (int s = 0; s < 2; ++s)
 #pragma unroll
-    for (int rr = 0; rr < 4; ++rr) acc[s][rr] = 0.0;
-  for (int64_t jb = c0; jb < c1; jb += kB3Cols) {
-    const int cnt = int(min<int64_t>(kB3Cols, c1 - jb));
-    __syncthreads();
-    // 16-byte chunks: column jj, plane pl, coordinates 8g..8g+7
-    for (int t = threadIdx.x; t < kB3Cols * 12; t += 256) {
-      const int jj = t / 12, r = t - 12 * (t / 12), pl = r >> 2, g = r & 3;
-      u16x8_t val = u16x8_t{0, 0, 0, 0, 0, 0, 0, 0};
-      if (jj < cnt) val = *reinterpret_cast<const u16x8_t*>(Bc + (jb + jj) * kB3Stride + 32 * pl + 8 * g);
-      *reinterpret_cast<u16x8_t*>(&bs[pl][jj][8 * g]) = val;
+    for (int rr = 0; rr < 4; ++rr) asm volatile("" : "+v"(acc[s][rr]));
+}
+
+// u = K(Xr, Xc) v over a slice of the columns (blockIdx.y) for 128 rows
+// (blockIdx.x): one partial per slice and row.
+template <class G, bool EX>
+__global__ __launch_bounds__(256, 4) void kapply_otf_mfma_kernel(
+    const float* __restrict__ Xr, const float* __restrict__ qr, int64_t nr,
+    const typename G::col_t* __restrict__ Xc, const float* __restrict__ qc, int64_t nc, int p, float ng,
+    const double* __restrict__ v, int64_t cols_per_slice, double* __restrict__ part) {
+  typedef std::conditional_t<EX, double, float> acc_t;
+  __shared__ __align__(16) char xs[2][G::kStageBytes];
+  __shared__ acc_t vs[2][kOtfStage];
+  __shared__ float qs[2][G::kNorms ? kOtfStage : 1];
+  const int t = threadIdx.x;
+  const int lane = t & 63, wave = t >> 6;
+  const int li = lane & 15, lg = lane >> 4;
+  const int64_t row0 = int64_t(blockIdx.x) * 128 + wave * 32;
+  const int64_t c0 = int64_t(blockIdx.y) * cols_per_slice;
+  const int64_t c1 = min(nc, c0 + cols_per_slice);
+  G gm;
+  double nv;
+  float nq = 0.f;
+  auto fetch = [&](int64_t jb) {
+    gm.fetch(Xc, nc, p, jb, t);
+    const int64_t j = min(jb + lane, c1 - 1);
+    nv = v[j];
+    if (G::kNorms) nq = qc[j];
+  };
+  auto put = [&](int64_t jb, int b) {
+    gm.put(xs[b], p, t);
+    if (t < kOtfStage) {  // columns past the slice count with v_j = 0
+      vs[b][t] = jb + t < c1 ? acc_t(nv) : acc_t(0);
+      if (G::kNorms) qs[b][t] = nq;
     }
-    if (threadIdx.x < kB3Cols) {
-      const int jj = threadIdx.x;
-      if (!AUG) qs[jj] = jj < cnt ? qc[jb + jj] : 0.f;
-      const double vj = jj < cnt ? v[jb + jj] : 0.0;
-      if (EX) vd[jj] = vj;
-      else vs[jj] = float(vj);
+  };
+  fetch(c0);
+  float qi[2][4];
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    gm.rows(Xr, qr, nr, p, row0 + 16 * s + li, s, lg);
+#pragma unroll
+    for (int rr = 0; rr < 4; ++rr) qi[s][rr] = G::kNorms ? qr[min(row0 + 16 * s + 4 * lg + rr, nr - 1)] : 0.f;
+  }
+  put(c0, 0);
+  double acc[2][4];
+  float a32[2][4];
+#pragma unroll
+  for (int s = 0; s < 2; ++s)
+#pragma unroll
+    for (int rr = 0; rr < 4; ++rr) {
+      acc[s][rr] = 0.0;
+      a32[s][rr] = 0.f;
     }
-    __syncthreads();
-    float a32[2][4];
+  __syncthreads();
+  int b = 0;
+  for (int64_t jb = c0; jb < c1; jb += kOtfStage, b ^= 1) {
+    const bool more = jb + kOtfStage < c1;
+    if (more) fetch(jb + kOtfStage);
+    f32x4_t g[2][2];
+    gm.gram(xs[b], 0, lane, g[0]);
 #pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-      for (int rr = 0; rr < 4; ++rr) a32[s][rr] = 0.f;
-    // Gram blocks of one 16-column tile (issuing the next tile's MFMAs ahead
-    // of these exponentials measured slower: the other waves of the SIMD
-    // already fill the matrix-core latency)
-    auto gram = [&](int t16, f32x4_t* g) {
-      const int jj = t16 + li;
-      const bf16x8_t b_h = *reinterpret_cast<const bf16x8_t*>(&bs[0][jj][8 * lg]);
-      const bf16x8_t b_m = *reinterpret_cast<const bf16x8_t*>(&bs[1][jj][8 * lg]);
-      const bf16x8_t b_l = *reinterpret_cast<const bf16x8_t*>(&bs[2][jj][8 * lg]);
-#pragma unroll
-      for (int s = 0; s < 2; ++s) {  // smallest products first
-        f32x4_t c = f32x4_t{0.f, 0.f, 0.f, 0.f};
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(am[s], b_m, c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[s], b_l, c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[s], b_h, c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[s], b_m, c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(am[s], b_h, c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[s], b_h, c, 0, 0, 0);
-        g[s] = c;
-      }
-    };
-    f32x4_t g[2];
-    for (int t16 = 0; t16 < cnt; t16 += 16) {
-      const int jj = t16 + li;
-      gram(t16, g);
-      const float qj = AUG ? 0.f : qs[jj];
+    for (int tile = 0; tile < kOtfStage / 16; ++tile) {
+      __builtin_amdgcn_s_setprio(1);  // a wave that feeds the matrix cores goes first
+      if (tile + 1 < kOtfStage / 16) gm.gram(xs[b], tile + 1, lane, g[(tile + 1) & 1]);
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_setprio(0);
+      const acc_t vj = vs[b][16 * tile + li];
+      const float qj = G::kNorms ? qs[b][16 * tile + li] : 0.f;
 #pragma unroll
       for (int s = 0; s < 2; ++s)
 #pragma unroll
         for (int rr = 0; rr < 4; ++rr) {
-          // ng < 0 and d >= 0: exp2(min(ng d, 0)) = min(exp2(ng d), 1), the clamp
-          // to [0, 1] being the exponential's output modifier
-          const float a = AUG ? g[s][rr] : ng * (qi[s][rr] + qj + g[s][rr]);
-          const float e = __builtin_amdgcn_fmed3f(kexp2(a), 0.f, 1.f);
-          if (EX) acc[s][rr] = fma(double(e), vd[jj], acc[s][rr]);
-          else a32[s][rr] = fmaf(e, vs[jj], a32[s][rr]);
+          const float e = otf_entry(G::arg(g[tile & 1][s][rr], qi[s][rr], qj, ng));
+          if (EX) acc[s][rr] = fma(double(e), double(vj), acc[s][rr]);
+          else a32[s][rr] = fmaf(e, float(vj), a32[s][rr]);
         }
     }
-    if (!EX) {
+    if (EX) otf_pin(acc);
+    else otf_pin(a32);
+    if (!EX && (!more || G::kFlush == 1 || b == 1)) {
 #pragma unroll
       for (int s = 0; s < 2; ++s)
 #pragma unroll
-        for (int rr = 0; rr < 4; ++rr) acc[s][rr] += double(a32[s][rr]);
+        for (int rr = 0; rr < 4; ++rr) {
+          acc[s][rr] += double(a32[s][rr]);
+          a32[s][rr] = 0.f;
+        }
     }
+    if (more) put(jb + kOtfStage, b ^ 1);
+    __syncthreads();
   }
   // sum over the 16 column lanes of each row group (lane bits 0..3)
 #pragma unroll
@@ -1243,26 +1283,47 @@ __global__ __launch_bounds__(256) void kapply_otf_mfma3_kernel(
   }
 }
 
-// Symmetric form of the BF16x3 apply for the square K(X, X): each distinct
-// pair once, over the upper-triangle 128 x 128 tiles of the packed geometry.
-// A workgroup takes a strip of tiles of tile-row I; its rows are held as in
-// kapply_otf_mfma3_kernel (wave w: rows 32 w .. 32 w + 31 of the tile-row,
-// split once into registers) and each tile J is one 128-column stage.
-// Every entry feeds the row sum (times v_j) and, off the diagonal tile, the
-// column sum (times v_i): a lane adds its eight rows, the four lane groups
-// are added across lanes and the four waves in LDS.  Row sums are added over
-// the 16 column lanes at the end of the strip.  packed_reduce adds the
-// partials in a fixed order.
-template <bool EX, bool AUG>
-__global__ __launch_bounds__(256) void kapply_otf_mfma3_sym_kernel(
-    const float* __restrict__ X, const float* __restrict__ q, int64_t n, const uint16_t* __restrict__ Bc, int p,
-    float ng, const double* __restrict__ v, int64_t nt, int strip, int64_t nsx, double* __restrict__ rowpart,
-    double* __restrict__ colpart) {
-  static_assert(kB3Cols == kPkT, "one stage per tile");
-  __shared__ __align__(16) uint16_t bs[3][kB3Cols][kB3Row];
-  __shared__ float qs[AUG ? 1 : kB3Cols];
-  __shared__ double vd[kB3Cols];
-  __shared__ double red[4][kB3Cols];
+// the sums of four per-lane values over the four lane groups of 16: group k
+// returns the total of value k
+__device__ __forceinline__ double groups4_sum_f64(const double (&x)[4]) {
+  auto pair = [](double a, double b, auto wide) {
+    const uint64_t ua = __builtin_bit_cast(uint64_t, a), ub = __builtin_bit_cast(uint64_t, b);
+    uint32_t l0, l1, h0, h1;
+    if constexpr (decltype(wide)::value) {
+      const auto lo = __builtin_amdgcn_permlane32_swap(uint32_t(ua), uint32_t(ub), false, false);
+      const auto hi = __builtin_amdgcn_permlane32_swap(uint32_t(ua >> 32), uint32_t(ub >> 32), false, false);
+      l0 = lo[0]; l1 = lo[1]; h0 = hi[0]; h1 = hi[1];
+    } else {
+      const auto lo = __builtin_amdgcn_permlane16_swap(uint32_t(ua), uint32_t(ub), false, false);
+      const auto hi = __builtin_amdgcn_permlane16_swap(uint32_t(ua >> 32), uint32_t(ub >> 32), false, false);
+      l0 = lo[0]; l1 = lo[1]; h0 = hi[0]; h1 = hi[1];
+    }
+    return __builtin_bit_cast(double, (uint64_t(h0) << 32) | l0) +
+           __builtin_bit_cast(double, (uint64_t(h1) << 32) | l1);
+  };
+  return pair(pair(x[0], x[1], std::false_type{}), pair(x[2], x[3], std::false_type{}), std::true_type{});
+}
+
+// Symmetric form for the square K(X, X): each distinct pair once, over the
+// upper-triangle 128 x 128 tiles of the packed geometry.  A workgroup takes a
+// strip of tiles of tile-row I, two 64-column stages per tile.  Every entry
+// feeds the row sum (times v_j) and, off the diagonal tile, the column sum
+// (times v_i): a lane adds its eight rows of each of the stage's four
+// 16-column tiles, the four lane groups are added across lanes (one exchange
+// for the four tiles: lane l ends with column l of the stage) and the four
+// waves in LDS.  Row sums are added over the 16 column lanes at the end of
+// the strip.  packed_reduce adds the partials in a fixed order.
+template <class G, bool EX>
+__global__ __launch_bounds__(256, 4) void kapply_otf_mfma_sym_kernel(
+    const float* __restrict__ X, const float* __restrict__ q, int64_t n, const typename G::col_t* __restrict__ Xc,
+    int p, float ng, const double* __restrict__ v, int64_t nt, int strip, int64_t nsx,
+    double* __restrict__ rowpart, double* __restrict__ colpart) {
+  typedef std::conditional_t<EX, double, float> acc_t;
+  static_assert(2 * kOtfStage == kPkT, "two stages per tile");
+  __shared__ __align__(16) char xs[2][G::kStageBytes];
+  __shared__ acc_t vs[2][kOtfStage];
+  __shared__ float qs[2][G::kNorms ? kOtfStage : 1];
+  __shared__ double red[2][4][kOtfStage];
   const int t = threadIdx.x;
   const int lane = t & 63, wave = t >> 6;
   const int li = lane & 15, lg = lane >> 4;
@@ -1270,119 +1331,98 @@ __global__ __launch_bounds__(256) void kapply_otf_mfma3_sym_kernel(
   pk_strip_coords(blockIdx.x, nt, strip, I, kst);
   const int64_t J0 = I + kst * strip, J1 = min(nt, J0 + strip);
   const int64_t row0 = I * kPkT + wave * 32;
-  bf16x8_t ah[2], am[2], al[2];
+  const int64_t c0 = J0 * kPkT, c1 = min(n, J1 * kPkT);
+  G gm;
+  double nv;
+  float nq = 0.f;
+  auto fetch = [&](int64_t jb) {
+    gm.fetch(Xc, n, p, jb, t);
+    const int64_t j = min(jb + lane, n - 1);
+    nv = v[j];
+    if (G::kNorms) nq = q[j];
+  };
+  auto put = [&](int64_t jb, int b) {
+    gm.put(xs[b], p, t);
+    if (t < kOtfStage) {  // columns past n count with v_j = 0 (their own sums are never read)
+      vs[b][t] = jb + t < n ? acc_t(nv) : acc_t(0);
+      if (G::kNorms) qs[b][t] = nq;
+    }
+  };
+  fetch(c0);
   float qi[2][4];
-  double vi[2][4];
+  acc_t vi[2][4];
 #pragma unroll
   for (int s = 0; s < 2; ++s) {
-    const int64_t r = row0 + 16 * s + li;
-    const bool in = r < n;
-    const float qq = (AUG && in) ? q[r] : 0.f;
-    u16x8_t h, m, l;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int k = 8 * lg + e;
-      const float x = in ? b3_coord<AUG, false>(X + r * p, qq, k, p, 1.f) : 0.f;
-      uint16_t hh, mm, ll;
-      split3_bf16(x, hh, mm, ll);
-      h[e] = hh;
-      m[e] = mm;
-      l[e] = ll;
-    }
-    ah[s] = __builtin_bit_cast(bf16x8_t, h);
-    am[s] = __builtin_bit_cast(bf16x8_t, m);
-    al[s] = __builtin_bit_cast(bf16x8_t, l);
+    gm.rows(X, q, n, p, row0 + 16 * s + li, s, lg);
 #pragma unroll
     for (int rr = 0; rr < 4; ++rr) {
       const int64_t ro = row0 + 16 * s + 4 * lg + rr;
       const int64_t rc = min(ro, n - 1);
-      const float qv = q[rc];
       const double vv = v[rc];
-      qi[s][rr] = (!AUG && ro < n) ? qv : 0.f;
-      vi[s][rr] = ro < n ? vv : 0.0;  // rows past n add nothing to the column sums
+      qi[s][rr] = G::kNorms ? q[rc] : 0.f;
+      vi[s][rr] = ro < n ? acc_t(vv) : acc_t(0);  // rows past n add nothing to the column sums
     }
   }
+  put(c0, 0);
   double acc[2][4];
+  float a32[2][4];
 #pragma unroll
   for (int s = 0; s < 2; ++s)
 #pragma unroll
-    for (int rr = 0; rr < 4; ++rr) acc[s][rr] = 0.0;
-  for (int64_t J = J0; J < J1; ++J) {
-    const bool diag = J == I;
-    const int64_t jb = J * kPkT;
-    const int cnt = int(min<int64_t>(kB3Cols, n - jb));
-    __syncthreads();
-    for (int e = t; e < kB3Cols * 12; e += 256) {
-      const int jj = e / 12, r = e - 12 * (e / 12), pl = r >> 2, g = r & 3;
-      u16x8_t val = u16x8_t{0, 0, 0, 0, 0, 0, 0, 0};
-      if (jj < cnt) val = *reinterpret_cast<const u16x8_t*>(Bc + (jb + jj) * kB3Stride + 32 * pl + 8 * g);
-      *reinterpret_cast<u16x8_t*>(&bs[pl][jj][8 * g]) = val;
+    for (int rr = 0; rr < 4; ++rr) {
+      acc[s][rr] = 0.0;
+      a32[s][rr] = 0.f;
     }
-    if (t < kB3Cols) {
-      if (!AUG) qs[t] = t < cnt ? q[jb + t] : 0.f;
-      vd[t] = t < cnt ? v[jb + t] : 0.0;
-    }
-    __syncthreads();
-    float a32[2][4];
+  __syncthreads();
+  int b = 0;  // the stage's buffers, and its half of the tile (c0 is a multiple of the tile)
+  for (int64_t jb = c0; jb < c1; jb += kOtfStage, b ^= 1) {
+    const bool more = jb + kOtfStage < c1;
+    if (more) fetch(jb + kOtfStage);
+    f32x4_t g[2][2];
+    gm.gram(xs[b], 0, lane, g[0]);
 #pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-      for (int rr = 0; rr < 4; ++rr) a32[s][rr] = 0.f;
-    for (int t16 = 0; t16 < cnt; t16 += 16) {
-      const int jj = t16 + li;
-      const bf16x8_t b_h = *reinterpret_cast<const bf16x8_t*>(&bs[0][jj][8 * lg]);
-      const bf16x8_t b_m = *reinterpret_cast<const bf16x8_t*>(&bs[1][jj][8 * lg]);
-      const bf16x8_t b_l = *reinterpret_cast<const bf16x8_t*>(&bs[2][jj][8 * lg]);
-      f32x4_t g[2];
-#pragma unroll
-      for (int s = 0; s < 2; ++s) {  // smallest products first
-        f32x4_t c = f32x4_t{0.f, 0.f, 0.f, 0.f};
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(am[s], b_m, c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[s], b_l, c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[s], b_h, c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[s], b_m, c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(am[s], b_h, c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[s], b_h, c, 0, 0, 0);
-        g[s] = c;
-      }
-      const float qj = AUG ? 0.f : qs[jj];
-      const double vj = vd[jj];
-      double cs64 = 0.0;
-      float cs32 = 0.f;
+    for (int tile = 0; tile < kOtfStage / 16; ++tile) {
+      __builtin_amdgcn_s_setprio(1);  // a wave that feeds the matrix cores goes first
+      if (tile + 1 < kOtfStage / 16) gm.gram(xs[b], tile + 1, lane, g[(tile + 1) & 1]);
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_setprio(0);
+      const acc_t vj = vs[b][16 * tile + li];
+      const float qj = G::kNorms ? qs[b][16 * tile + li] : 0.f;
+      acc_t c = acc_t(0);
 #pragma unroll
       for (int s = 0; s < 2; ++s)
 #pragma unroll
         for (int rr = 0; rr < 4; ++rr) {
-          // ng < 0 and d >= 0: exp2(min(ng d, 0)) = min(exp2(ng d), 1), the clamp
-          // to [0, 1] being the exponential's output modifier
-          const float a = AUG ? g[s][rr] : ng * (qi[s][rr] + qj + g[s][rr]);
-          const float e = __builtin_amdgcn_fmed3f(kexp2(a), 0.f, 1.f);
+          const float e = otf_entry(G::arg(g[tile & 1][s][rr], qi[s][rr], qj, ng));
           if (EX) {
-            acc[s][rr] = fma(double(e), vj, acc[s][rr]);
-            cs64 = fma(double(e), vi[s][rr], cs64);
+            acc[s][rr] = fma(double(e), double(vj), acc[s][rr]);
+            c = fma(double(e), double(vi[s][rr]), double(c));
           } else {
             a32[s][rr] = fmaf(e, float(vj), a32[s][rr]);
-            cs32 = fmaf(e, float(vi[s][rr]), cs32);
+            c = fmaf(e, float(vi[s][rr]), float(c));
           }
         }
-      if (!diag) {  // the column's 32 rows of this wave: add the four lane groups
-        double cs = EX ? cs64 : double(cs32);
-        cs += __shfl_xor(cs, 16);
-        cs += __shfl_xor(cs, 32);
-        if (lg == 0) red[wave][jj] = cs;
-      }
+      const double w = swap_sum_f64<false>(swap_sum_f64<true>(double(c)));
+      red[b][wave][16 * tile + li] = w;  // the same value from the four lane groups
     }
-    if (!EX) {
+    if (EX) otf_pin(acc);
+    else otf_pin(a32);
+    if (!EX && (!more || b == 1)) {
 #pragma unroll
       for (int s = 0; s < 2; ++s)
 #pragma unroll
-        for (int rr = 0; rr < 4; ++rr) acc[s][rr] += double(a32[s][rr]);
+        for (int rr = 0; rr < 4; ++rr) {
+          acc[s][rr] += double(a32[s][rr]);
+          a32[s][rr] = 0.f;
+        }
     }
-    if (!diag) {  // the same in every thread of the block
-      __syncthreads();
-      if (t < kB3Cols)
-        colpart[size_t(pk_tile_index(I, J, nt)) * kPkT + t] = ((red[0][t] + red[1][t]) + red[2][t]) + red[3][t];
-    }
+    if (more) put(jb + kOtfStage, b ^ 1);
+    __syncthreads();
+    // the other half of red is written in the next stage, this one only after that stage's barrier
+    const int64_t J = jb / kPkT;
+    if (t < kOtfStage && J != I)
+      colpart[size_t(pk_tile_index(I, J, nt)) * kPkT + b * kOtfStage + t] =
+          ((red[b][0][t] + red[b][1][t]) + red[b][2][t]) + red[b][3][t];
   }
   // row sums over the 16 column lanes of each row group (lane bits 0..3)
 #pragma unroll
@@ -1398,136 +1438,28 @@ __global__ __launch_bounds__(256) void kapply_otf_mfma3_sym_kernel(
   }
 }
 
-// The same for p <= 16 with the Gram term on v_mfma_f32_16x16x4f32 (FP32
-// operands, as kapply_otf_mfma_kernel): each distinct pair of the square
-// K(X, X) once, in the strip and tile geometry above.
-template <int KP, bool EX>
-__global__ __launch_bounds__(256) void kapply_otf_mfma_sym_kernel(
-    const float* __restrict__ X, const float* __restrict__ q, int64_t n, int p, float ng,
-    const double* __restrict__ v, int64_t nt, int strip, int64_t nsx, double* __restrict__ rowpart,
-    double* __restrict__ colpart) {
-  constexpr int NKB = KP / 4;
-  constexpr int T = kPkT;
-  __shared__ float xs[T][KP + 1];
-  __shared__ float qs[T];
-  __shared__ double vd[T];
-  __shared__ double red[4][T];
-  const int t = threadIdx.x;
-  const int lane = t & 63, wave = t >> 6;
-  const int li = lane & 15, lg = lane >> 4;
-  int64_t I, kst;
-  pk_strip_coords(blockIdx.x, nt, strip, I, kst);
-  const int64_t J0 = I + kst * strip, J1 = min(nt, J0 + strip);
-  const int64_t row0 = I * T + wave * 32;
-  float a[2][NKB];
-  float qi[2][4];
-  double vi[2][4];
-#pragma unroll
-  for (int s = 0; s < 2; ++s) {
-    const int64_t r = row0 + 16 * s + li;
-#pragma unroll
-    for (int kb = 0; kb < NKB; ++kb) {
-      const int k = 4 * kb + lg;
-      a[s][kb] = (r < n && k < p) ? X[r * p + k] : 0.f;
-    }
-#pragma unroll
-    for (int rr = 0; rr < 4; ++rr) {
-      const int64_t ro = row0 + 16 * s + 4 * lg + rr;
-      const int64_t rc = min(ro, n - 1);
-      const float qv = q[rc];
-      const double vv = v[rc];
-      qi[s][rr] = ro < n ? qv : 0.f;
-      vi[s][rr] = ro < n ? vv : 0.0;  // rows past n add nothing to the column sums
-    }
-  }
-  double acc[2][4];
-#pragma unroll
-  for (int s = 0; s < 2; ++s)
-#pragma unroll
-    for (int rr = 0; rr < 4; ++rr) acc[s][rr] = 0.0;
-  for (int64_t J = J0; J < J1; ++J) {
-    const bool diag = J == I;
-    const int64_t jb = J * T;
-    const int cnt = int(min<int64_t>(T, n - jb));
-    __syncthreads();
-    for (int e = t; e < T * KP; e += 256) {
-      const int jj = e / KP, k = e % KP;
-      xs[jj][k] = (jj < cnt && k < p) ? X[(jb + jj) * p + k] : 0.f;
-    }
-    if (t < T) {
-      qs[t] = t < cnt ? q[jb + t] : 0.f;
-      vd[t] = t < cnt ? v[jb + t] : 0.0;
-    }
-    __syncthreads();
-    float a32[2][4];
-#pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-      for (int rr = 0; rr < 4; ++rr) a32[s][rr] = 0.f;
-    for (int t16 = 0; t16 < cnt; t16 += 16) {
-      const int jj = t16 + li;
-      float b[NKB];
-#pragma unroll
-      for (int kb = 0; kb < NKB; ++kb) b[kb] = xs[jj][4 * kb + lg];
-      f32x4_t g0 = f32x4_t{0.f, 0.f, 0.f, 0.f}, g1 = f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int kb = 0; kb < NKB; ++kb) {
-        g0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[0][kb], b[kb], g0, 0, 0, 0);
-        g1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[1][kb], b[kb], g1, 0, 0, 0);
-      }
-      const float qj = qs[jj];
-      const double vj = vd[jj];
-      double cs64 = 0.0;
-      float cs32 = 0.f;
-#pragma unroll
-      for (int s = 0; s < 2; ++s)
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-          const float gg = s == 0 ? g0[rr] : g1[rr];
-          // ng < 0, d >= 0: exp2(ng max(d, 0)) = min(exp2(ng d), 1), clamped by the output modifier
-          const float e = __builtin_amdgcn_fmed3f(kexp2(ng * (qi[s][rr] + qj - 2.f * gg)), 0.f, 1.f);
-          if (EX) {
-            acc[s][rr] = fma(double(e), vj, acc[s][rr]);
-            cs64 = fma(double(e), vi[s][rr], cs64);
-          } else {
-            a32[s][rr] = fmaf(e, float(vj), a32[s][rr]);
-            cs32 = fmaf(e, float(vi[s][rr]), cs32);
-          }
-        }
-      if (!diag) {  // the column's 32 rows of this wave: add the four lane groups
-        double cs = EX ? cs64 : double(cs32);
-        cs += __shfl_xor(cs, 16);
-        cs += __shfl_xor(cs, 32);
-        if (lg == 0) red[wave][jj] = cs;
-      }
-    }
-    if (!EX) {
-#pragma unroll
-      for (int s = 0; s < 2; ++s)
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr) acc[s][rr] += double(a32[s][rr]);
-    }
-    if (!diag) {  // the same in every thread of the block
-      __syncthreads();
-      if (t < T) colpart[size_t(pk_tile_index(I, J, nt)) * T + t] = ((red[0][t] + red[1][t]) + red[2][t]) + red[3][t];
-    }
-  }
-#pragma unroll
-  for (int s = 0; s < 2; ++s)
-#pragma unroll
-    for (int rr = 0; rr < 4; ++rr) acc[s][rr] = row16_sum_f64<true>(acc[s][rr]);
-  if (li == 0) {
-#pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-      for (int rr = 0; rr < 4; ++rr)
-        rowpart[(size_t(I) * nsx + kst) * T + wave * 32 + 16 * s + 4 * lg + rr] = acc[s][rr];
+// The column side of a Gram engine: X itself, or its split formed here in buf.
+template <class G>
+static const typename G::col_t* otf_columns(const float* X, const float* q, int64_t n, int p, float ng, void* buf,
+                                            hipStream_t st) {
+  if constexpr (std::is_same_v<typename G::col_t, float>) {
+    return X;
+  } else {
+    uint16_t* bc = static_cast<uint16_t*>(buf);
+    const dim3 grid((unsigned)(b3_points(n) * 4 / 256));
+    kotf_split_cols_kernel<!G::kNorms><<<grid, 256, 0, st>>>(X, q, n, p, ng, bc);
+    KQR_LAUNCH_CHECK();
+    return bc;
   }
 }
 
-// K(X, X) v with each distinct pair once (RBF, p <= 32; KP = p rounded up to
-// 4, the BF16x3 Gram above 16); u = K v.
-template <int KP>
+template <class G>
+static size_t otf_columns_bytes(int64_t n) {
+  return std::is_same_v<typename G::col_t, float> ? 0 : b3_bytes(n);
+}
+
+// K(X, X) v with each distinct pair once; u = K v.
+template <class G>
 static void kapply_otf_mfma_sym(const float* X, const float* q, int64_t n, int p, KernelSpec ks, const double* v,
                                 double* u, int64_t ldu, bool exact, hipStream_t st, double* scratch,
                                 size_t scratch_doubles) {
@@ -1535,87 +1467,78 @@ static void kapply_otf_mfma_sym(const float* X, const float* q, int64_t n, int p
   const int strip = otf_sym_strip(n);
   const int64_t nsx = (nt + strip - 1) / strip;
   const size_t need = packed_scratch_doubles(n, strip);
-  const size_t split_bytes = KP > 16 ? size_t(n) * kB3Stride * sizeof(uint16_t) : 0;
+  const size_t col_bytes = otf_columns_bytes<G>(n);
   double* part = scratch && scratch_doubles >= need ? scratch : nullptr;
   const size_t part_bytes = part ? 0 : (need * sizeof(double) + 255) / 256 * 256;
   char* buf = nullptr;
-  if (part_bytes + split_bytes > 0)
-    KQR_CHECK_HIP(hipMallocAsync(reinterpret_cast<void**>(&buf), part_bytes + split_bytes, st));
+  if (part_bytes + col_bytes > 0)
+    KQR_CHECK_HIP(hipMallocAsync(reinterpret_cast<void**>(&buf), part_bytes + col_bytes, st));
   if (!part) part = reinterpret_cast<double*>(buf);
   double* rowpart = part;
   double* colpart = part + size_t(nt) * nsx * kPkT;
   const float ng = -float(ks.gamma) * kLog2e;
+  const typename G::col_t* cols = otf_columns<G>(X, q, n, p, ng, buf + part_bytes, st);
   const dim3 grid((unsigned)pk_strips_tail(nt, strip));
-  if (KP <= 16) {
-    if (exact)
-      kapply_otf_mfma_sym_kernel<KP, true><<<grid, 256, 0, st>>>(X, q, n, p, ng, v, nt, strip, nsx, rowpart, colpart);
-    else
-      kapply_otf_mfma_sym_kernel<KP, false><<<grid, 256, 0, st>>>(X, q, n, p, ng, v, nt, strip, nsx, rowpart, colpart);
-    KQR_LAUNCH_CHECK();
-    packed_reduce(rowpart, colpart, n, strip, u, ldu, st);
-    if (buf) KQR_CHECK_HIP(hipFreeAsync(buf, st));
-    return;
-  }
-  uint16_t* bc = reinterpret_cast<uint16_t*>(buf + part_bytes);
-  const bool aug = p <= 30;
-  const dim3 sgrid((unsigned)((n * 4 + 255) / 256));
-  if (aug) kotf_split_cols_kernel<true><<<sgrid, 256, 0, st>>>(X, q, n, p, ng, bc);
-  else kotf_split_cols_kernel<false><<<sgrid, 256, 0, st>>>(X, q, n, p, ng, bc);
-  KQR_LAUNCH_CHECK();
-  if (aug && exact)
-    kapply_otf_mfma3_sym_kernel<true, true><<<grid, 256, 0, st>>>(X, q, n, bc, p, ng, v, nt, strip, nsx, rowpart, colpart);
-  else if (aug)
-    kapply_otf_mfma3_sym_kernel<false, true><<<grid, 256, 0, st>>>(X, q, n, bc, p, ng, v, nt, strip, nsx, rowpart, colpart);
-  else if (exact)
-    kapply_otf_mfma3_sym_kernel<true, false><<<grid, 256, 0, st>>>(X, q, n, bc, p, ng, v, nt, strip, nsx, rowpart, colpart);
+  if (exact)
+    kapply_otf_mfma_sym_kernel<G, true><<<grid, 256, 0, st>>>(X, q, n, cols, p, ng, v, nt, strip, nsx, rowpart, colpart);
   else
-    kapply_otf_mfma3_sym_kernel<false, false><<<grid, 256, 0, st>>>(X, q, n, bc, p, ng, v, nt, strip, nsx, rowpart, colpart);
+    kapply_otf_mfma_sym_kernel<G, false><<<grid, 256, 0, st>>>(X, q, n, cols, p, ng, v, nt, strip, nsx, rowpart, colpart);
   KQR_LAUNCH_CHECK();
   packed_reduce(rowpart, colpart, n, strip, u, ldu, st);
-  KQR_CHECK_HIP(hipFreeAsync(buf, st));
+  if (buf) KQR_CHECK_HIP(hipFreeAsync(buf, st));
 }
 
-template <int KP>
+// Column slices of a rectangular launch on the matrix cores, in stages of
+// `stage` columns: where the launch is more than 32 workgroups per CU, as
+// otf_slices; below that, so that the workgroups come out in whole rounds of
+// the CUs (a CU with one more workgroup than the others is what the launch
+// waits for), the time taken as that of the busiest CU, two stages' time for
+// a workgroup's start and a half or a fifth more where one or two
+// workgroups per CU leave its units waiting.  5,000 x 20,000 at p = 10 takes 48 us in
+// 760 workgroups of 17 stages, 52 in 800 of 16.
+static int64_t otf_mfma_per(int64_t rblk, int64_t nc, int64_t stage) {
+  const int64_t cus = 256, ns = (nc + stage - 1) / stage;
+  const int64_t big = std::min<int64_t>(otf_slices(rblk, nc), 65535);
+  if (rblk * std::min<int64_t>(ns, big) > 32 * cus || g_otf_wgs.load() != 8192)
+    return ((nc + big - 1) / big + stage - 1) / stage * stage;
+  int64_t best = ns;
+  double best_t = 0.0;
+  for (int64_t k = 1; k <= 16; ++k) {
+    const int64_t slices = std::max<int64_t>(1, std::min(ns, cus * k / rblk));
+    const int64_t per = (ns + slices - 1) / slices;
+    const int64_t wgs = rblk * ((ns + per - 1) / per);
+    const int64_t on_cu = (wgs + cus - 1) / cus;
+    const double t = double(on_cu * (per * stage + 128)) * (on_cu == 1 ? 1.5 : on_cu == 2 ? 1.2 : 1.0);
+    if (k == 1 || t < best_t) {
+      best = per;
+      best_t = t;
+    }
+  }
+  return best * stage;
+}
+
+template <class G>
 static void kapply_otf_mfma_p(const float* Xr, const float* qr, int64_t nr, const float* Xc, const float* qc,
                               int64_t nc, int p, KernelSpec ks, const double* v, double* u, int64_t ldu, double scale,
                               double shift, bool exact, hipStream_t st, double* scratch, size_t scratch_doubles) {
   if (Xr == Xc && qr == qc && nr == nc && scale == 1.0 && shift == 0.0 && otf_sym_fits(nr)) {  // square: symmetric
-    kapply_otf_mfma_sym<KP>(Xr, qr, nr, p, ks, v, u, ldu, exact, st, scratch, scratch_doubles);
+    kapply_otf_mfma_sym<G>(Xr, qr, nr, p, ks, v, u, ldu, exact, st, scratch, scratch_doubles);
     return;
   }
   const int64_t rblk = (nr + 127) / 128;
-  int64_t nslice = otf_slices(rblk, nc);
-  nslice = std::min<int64_t>(nslice, 65535);
-  int64_t per = (nc + nslice - 1) / nslice;
-  const int64_t stage = KP > 16 ? kB3Cols : kMfmaCols;
-  per = (per + stage - 1) / stage * stage;
-  nslice = (nc + per - 1) / per;
+  const int64_t per = otf_mfma_per(rblk, nc, int64_t(kOtfStage) * G::kFlush);
+  const int64_t nslice = (nc + per - 1) / per;
   const size_t part_bytes = (size_t(nslice) * size_t(nr) * sizeof(double) + 255) / 256 * 256;
-  const size_t split_bytes = KP > 16 ? size_t(nc) * kB3Stride * sizeof(uint16_t) : 0;
   char* buf = nullptr;
-  KQR_CHECK_HIP(hipMallocAsync(reinterpret_cast<void**>(&buf), part_bytes + split_bytes, st));
+  KQR_CHECK_HIP(hipMallocAsync(reinterpret_cast<void**>(&buf), part_bytes + otf_columns_bytes<G>(nc), st));
   double* part = reinterpret_cast<double*>(buf);
   const dim3 grid((unsigned)rblk, (unsigned)nslice);
   const float ng = -float(ks.gamma) * kLog2e;
-  if (KP > 16) {  // BF16x3 Gram: 6 MFMAs of K = 32 against KP/4 FP32 ones
-    uint16_t* bc = reinterpret_cast<uint16_t*>(buf + part_bytes);
-    const bool aug = p <= 30;
-    const dim3 sgrid((unsigned)((nc * 4 + 255) / 256));
-    if (aug) kotf_split_cols_kernel<true><<<sgrid, 256, 0, st>>>(Xc, qc, nc, p, ng, bc);
-    else kotf_split_cols_kernel<false><<<sgrid, 256, 0, st>>>(Xc, qc, nc, p, ng, bc);
-    KQR_LAUNCH_CHECK();
-    if (aug && exact) kapply_otf_mfma3_kernel<true, true><<<grid, 256, 0, st>>>(Xr, qr, nr, bc, qc, nc, p, ng, v, per, part);
-    else if (aug) kapply_otf_mfma3_kernel<false, true><<<grid, 256, 0, st>>>(Xr, qr, nr, bc, qc, nc, p, ng, v, per, part);
-    else if (exact) kapply_otf_mfma3_kernel<true, false><<<grid, 256, 0, st>>>(Xr, qr, nr, bc, qc, nc, p, ng, v, per, part);
-    else kapply_otf_mfma3_kernel<false, false><<<grid, 256, 0, st>>>(Xr, qr, nr, bc, qc, nc, p, ng, v, per, part);
-  } else if (exact) {
-    kapply_otf_mfma_kernel<KP, true><<<grid, 256, 0, st>>>(Xr, qr, nr, Xc, qc, nc, p, ng, v, per, part);
-  } else {
-    kapply_otf_mfma_kernel<KP, false><<<grid, 256, 0, st>>>(Xr, qr, nr, Xc, qc, nc, p, ng, v, per, part);
-  }
+  const typename G::col_t* cols = otf_columns<G>(Xc, qc, nc, p, ng, buf + part_bytes, st);
+  if (exact) kapply_otf_mfma_kernel<G, true><<<grid, 256, 0, st>>>(Xr, qr, nr, cols, qc, nc, p, ng, v, per, part);
+  else kapply_otf_mfma_kernel<G, false><<<grid, 256, 0, st>>>(Xr, qr, nr, cols, qc, nc, p, ng, v, per, part);
   KQR_LAUNCH_CHECK();
-  otf_reduce_kernel<<<dim3((unsigned)((nr + 255) / 256)), 256, 0, st>>>(part, int(nslice), nr, u, ldu, scale, shift);
-  KQR_LAUNCH_CHECK();
+  otf_reduce(part, nslice, nr, u, ldu, scale, shift, st);
   KQR_CHECK_HIP(hipFreeAsync(buf, st));
 }
 
@@ -1625,20 +1548,16 @@ void kapply_otf(const float* Xr, const float* sqr, int64_t nr, const float* Xc, 
                 size_t scratch_doubles) {
   if (nr <= 0) return;
   if (ks.kind == KQR_RBF && p <= 32) {
-#define KQR_OTF_MFMA(KP) \
-  kapply_otf_mfma_p<KP>(Xr, sqr, nr, Xc, sqc, nc, p, ks, v64, u, ldu, out_scale, out_shift, exact, st, scratch, \
-                        scratch_doubles)
-    switch ((p + 3) / 4) {
-      case 1:
-      case 2: KQR_OTF_MFMA(8); return;
-      case 3: KQR_OTF_MFMA(12); return;
-      case 4: KQR_OTF_MFMA(16); return;
-      case 5: KQR_OTF_MFMA(20); return;
-      case 6: KQR_OTF_MFMA(24); return;
-      case 7: KQR_OTF_MFMA(28); return;
-      default: KQR_OTF_MFMA(32); return;
-    }
+#define KQR_OTF_MFMA(...) \
+  kapply_otf_mfma_p<__VA_ARGS__>(Xr, sqr, nr, Xc, sqc, nc, p, ks, v64, u, ldu, out_scale, out_shift, exact, st, \
+                                 scratch, scratch_doubles)
+    if (p <= 8) KQR_OTF_MFMA(GramF32<8>);
+    else if (p <= 12) KQR_OTF_MFMA(GramF32<12>);
+    else if (p <= 16) KQR_OTF_MFMA(GramF32<16>);
+    else if (p <= 30) KQR_OTF_MFMA(GramB3<true>);
+    else KQR_OTF_MFMA(GramB3<false>);
 #undef KQR_OTF_MFMA
+    return;
   }
   KQR_DISPATCH_P(p, kapply_otf_p, Xr, sqr, nr, Xc, sqc, nc, p, ks, v64, u, ldu, out_scale, out_shift, exact, st);
 }
@@ -1650,8 +1569,9 @@ void kapply_otf(const float* Xr, const float* sqr, int64_t nr, const float* Xc, 
 // the spare coordinates when p <= 30 (the matrix cores then return
 // c d_ij, c = -gamma log2(e)), so an entry costs the lanes a clamp, the
 // exponential, the diagonal test and its share of a store.  Both sides are
-// split once per build into buffers of 96 halves per point (row side
-// [x, 1, q], column side [-2 c x, c q, c]; without the fold [x] and [-2 x]).
+// split once per build into buffers in operand order (kotf_split_cols_kernel;
+// row side [x, 1, q], column side [-2 c x, c q, c]; without the fold [x] and
+// [-2 x]).
 // FP32 storage takes all six significant products.  BF16 storage takes the
 // three leading ones (hi.hi, hi.mid, mid.hi): the dropped ones are at most
 // 3 2^-16 sum_k |a_k| |b_k|, and that sum is at most 2 |c| (q_i + q_j)
@@ -1722,12 +1642,13 @@ __global__ __launch_bounds__(256) void kbuild_b3_kernel(const uint16_t* __restri
 #pragma unroll
   for (int s = 0; s < 2; ++s) {
     const int64_t ic = min(wrow + 16 * s + li, n - 1);  // rows past n: any valid point (entries not kept)
-    bh[s] = *reinterpret_cast<const bf16x8_t*>(Pr + ic * kB3Stride + 8 * lg);
-    bm[s] = *reinterpret_cast<const bf16x8_t*>(Pr + ic * kB3Stride + 32 + 8 * lg);
-    bl[s] = *reinterpret_cast<const bf16x8_t*>(Pr + ic * kB3Stride + 64 + 8 * lg);
+    const uint16_t* rp = Pr + b3_offset(ic, lg);
+    bh[s] = *reinterpret_cast<const bf16x8_t*>(rp);
+    bm[s] = *reinterpret_cast<const bf16x8_t*>(rp + kB3Plane);
+    bl[s] = *reinterpret_cast<const bf16x8_t*>(rp + 2 * kB3Plane);
     qi[s] = AUG ? 0.f : q[ic];
   }
-  const uint32_t col_off = uint32_t(li) * kB3Stride + 8 * lg;  // this lane's column part within a block
+  const uint32_t col_off = uint32_t(lane) * 8;  // this lane's column part within a plane
   float (*sl)[kBuildSlab] = slab[wave];
   bslab_row* bsl = reinterpret_cast<bslab_row*>(slab[wave]);  // BF16 view: rows of 2 kBuildSlab halves
   // BF16 storage: three products when the largest squared norm allows (see
@@ -1741,18 +1662,19 @@ __global__ __launch_bounds__(256) void kbuild_b3_kernel(const uint16_t* __restri
       if (jb + kBuildStep <= n) {  // (uniform) whole step inside: a scalar base per block, the lane's offset fixed
 #pragma unroll
         for (int blk = 0; blk < kBuildStep / 16; ++blk) {
-          const uint16_t* cb = Sc + (jb + 16 * blk) * kB3Stride;
+          const uint16_t* cb = Sc + ((jb >> 4) + blk) * kB3Block;
           ahs[blk] = *reinterpret_cast<const bf16x8_t*>(cb + col_off);
-          ams[blk] = *reinterpret_cast<const bf16x8_t*>(cb + col_off + 32);
-          if constexpr (!three) als[blk] = *reinterpret_cast<const bf16x8_t*>(cb + col_off + 64);
+          ams[blk] = *reinterpret_cast<const bf16x8_t*>(cb + col_off + kB3Plane);
+          if constexpr (!three) als[blk] = *reinterpret_cast<const bf16x8_t*>(cb + col_off + 2 * kB3Plane);
         }
       } else {
 #pragma unroll
         for (int blk = 0; blk < kBuildStep / 16; ++blk) {
           const int64_t jc = min(jb + 16 * blk + li, n - 1);  // columns past n: any valid point (written as 0)
-          ahs[blk] = *reinterpret_cast<const bf16x8_t*>(Sc + jc * kB3Stride + 8 * lg);
-          ams[blk] = *reinterpret_cast<const bf16x8_t*>(Sc + jc * kB3Stride + 32 + 8 * lg);
-          if constexpr (!three) als[blk] = *reinterpret_cast<const bf16x8_t*>(Sc + jc * kB3Stride + 64 + 8 * lg);
+          const uint16_t* cb = Sc + b3_offset(jc, lg);
+          ahs[blk] = *reinterpret_cast<const bf16x8_t*>(cb);
+          ams[blk] = *reinterpret_cast<const bf16x8_t*>(cb + kB3Plane);
+          if constexpr (!three) als[blk] = *reinterpret_cast<const bf16x8_t*>(cb + 2 * kB3Plane);
         }
       }
       // Gram blocks: the two strips' product chains interleaved, and the next
@@ -1893,17 +1815,17 @@ bool kbuild_mfma(const float* X, const float* q, int64_t n, int p, KernelSpec ks
   const bool aug = p <= 30, bf = dtype == KQR_BF16;
   const float ng = -float(ks.gamma) * kLog2e;
   uint16_t* buf = nullptr;
-  const size_t half_bytes = size_t(n) * kB3Stride * sizeof(uint16_t);
+  const size_t half_bytes = b3_bytes(n);
   KQR_CHECK_HIP(hipMallocAsync(reinterpret_cast<void**>(&buf), 2 * half_bytes + 256, st));
   uint16_t* Pr = buf;                      // row side
-  uint16_t* Sc = buf + size_t(n) * kB3Stride;  // column side (scaled)
-  float* qmax = reinterpret_cast<float*>(buf + 2 * size_t(n) * kB3Stride);
+  uint16_t* Sc = buf + half_bytes / sizeof(uint16_t);  // column side (scaled)
+  float* qmax = reinterpret_cast<float*>(buf + 2 * (half_bytes / sizeof(uint16_t)));
   const float qlim = float(16.0 / (3.0 * ks.gamma));  // three products when max q <= qlim
   if (bf) {
     qmax_kernel<<<1, 1024, 0, st>>>(q, n, qmax);
     KQR_LAUNCH_CHECK();
   }
-  const dim3 sgrid((unsigned)((n * 4 + 255) / 256));
+  const dim3 sgrid((unsigned)(b3_points(n) * 4 / 256));
   if (aug) {
     kotf_split_cols_kernel<true, false><<<sgrid, 256, 0, st>>>(X, q, n, p, ng, Pr);
     kotf_split_cols_kernel<true, true><<<sgrid, 256, 0, st>>>(X, q, n, p, ng, Sc);

@@ -115,6 +115,9 @@ bool kbuild_mfma(const float* X, const float* q, int64_t n, int p, KernelSpec ks
                  int layout, hipStream_t st);
 // Squared row norms of X (FP32).
 void row_sqnorms(const float* X, int64_t n, int p, float* sqn, hipStream_t st);
+// the same for the rows of two matrices of p columns in one launch
+void row_sqnorms2(const float* Xa, int64_t na, float* qa, const float* Xb, int64_t nb, float* qb, int p,
+                  hipStream_t st);
 
 // u = K v (materialised, rows [0, nrows), cols [0, ncols)).  exact: v64 + FP64; else v32.
 // scratch (scratch_doubles long, or null) holds the partial sums when it is
