@@ -263,7 +263,7 @@ static void autotune_otf(const float* X, int64_t n, int p, KernelSpec ks, bool e
   DevBuf xq;
   int shift = -1;
   if (ks.kind == KQR_LAPLACIAN) {
-    xq.alloc(size_t(n) * size_t(p) * sizeof(uint32_t));
+    xq.alloc(quantized_words(n, p) * sizeof(uint32_t));
     shift = quantize_columns(X, n, p, xq.as<uint32_t>(), st);
   }
   const bool sym = (ks.kind == KQR_RBF && p <= 32) || shift >= 20;
@@ -474,26 +474,30 @@ int kqr_kernel_apply(const float* X, int64_t n, int64_t p, int kernel, double ga
       kapply_dense(km, n, n, nullptr, V, U, ldu, mode == KQR_APPLY_EXACT, st);
       return;
     }
-    void* tmp = nullptr;
-    // per column: contiguous FP64 copy (when strided) and its FP32 rounding
-    const size_t bytes = size_t(n) * (sizeof(double) + sizeof(float)) + 256;
-    KQR_CHECK_HIP(hipMallocAsync(&tmp, bytes, st));
-    double* v64 = static_cast<double*>(tmp);
-    float* v32 = reinterpret_cast<float*>(static_cast<char*>(tmp) + ((size_t(n) * sizeof(double) + 255) / 256) * 256);
-    float* sqn = nullptr;
-    double* lscr = nullptr;
-    DevBuf xq;
+    // one allocation: per column a contiguous FP64 copy (when strided) and its FP32 rounding, and on the fly the
+    // norms or fixed-point coordinates and the partial sums
+    auto up = [](size_t b) { return (b + 255) / 256 * 256; };
+    const bool otf = !K && kernel != KQR_LINEAR;
+    const size_t vec_bytes = up(size_t(n) * sizeof(double)) + up(size_t(n) * sizeof(float));
+    const size_t point_bytes =
+        !otf ? 0 : up(kernel == KQR_LAPLACIAN ? quantized_words(n, int(p)) * sizeof(uint32_t) : size_t(n) * sizeof(float));
+    size_t sum_doubles = 0;
+    if (!K && !otf) sum_doubles = lin_scratch_doubles(int(p));
+    else if (otf && kernel == KQR_LAPLACIAN) sum_doubles = otf_sym_scratch_doubles(n);
+    else if (otf) sum_doubles = kapply_otf_scratch_doubles(n, n, int(p), ks, true);
+    char* tmp = nullptr;
+    KQR_CHECK_HIP(hipMallocAsync(reinterpret_cast<void**>(&tmp), vec_bytes + point_bytes + sum_doubles * sizeof(double),
+                                 st));
+    double* v64 = reinterpret_cast<double*>(tmp);
+    float* v32 = reinterpret_cast<float*>(tmp + up(size_t(n) * sizeof(double)));
+    float* sqn = reinterpret_cast<float*>(tmp + vec_bytes);
+    uint32_t* xq = reinterpret_cast<uint32_t*>(tmp + vec_bytes);
+    double* sums = reinterpret_cast<double*>(tmp + vec_bytes + point_bytes);
     int shift = -1;
-    if (!K && kernel == KQR_LINEAR) {
-      KQR_CHECK_HIP(hipMallocAsync(reinterpret_cast<void**>(&lscr), lin_scratch_doubles(int(p)) * sizeof(double), st));
-    } else if (!K) {
-      KQR_CHECK_HIP(hipMallocAsync(reinterpret_cast<void**>(&sqn), size_t(n) * sizeof(float), st));
+    if (otf && kernel == KQR_LAPLACIAN)  // exact integer L1 distances of fixed-point X, as in the fits
+      shift = quantize_columns(X, n, int(p), xq, st);
+    else if (otf)
       row_sqnorms(X, n, int(p), sqn, st);
-      if (kernel == KQR_LAPLACIAN) {  // exact integer L1 distances of fixed-point X, as in the fits
-        xq.alloc(size_t(n) * size_t(p) * sizeof(uint32_t));
-        shift = quantize_columns(X, n, int(p), xq.as<uint32_t>(), st);
-      }
-    }
     if (K && m > 1 && mode == KQR_APPLY_EXACT && k_dtype == KQR_FP32 && m <= kKvMaxExact) {
       // exact columns (FP64 vectors, products and sums) from one pass over K
       double* cols = nullptr;
@@ -548,16 +552,15 @@ int kqr_kernel_apply(const float* X, int64_t n, int64_t p, int kernel, double ga
           to_f32(col, n, 1, 1, v32, 1, st);
           kapply_dense(km, n, n, v32, nullptr, U + j, ldu, false, st);
         }
-      } else if (lscr) {
-        lin_apply(X, n, int(p), col, U + j, ldu, lscr, st);
+      } else if (!otf) {
+        lin_apply(X, n, int(p), col, U + j, ldu, sums, st);
       } else if (shift >= 20) {
-        kapply_otf_l1q(xq.as<uint32_t>(), n, int(p), gamma, shift, col, U + j, ldu, mode == KQR_APPLY_EXACT, st);
+        kapply_otf_l1q(xq, n, int(p), gamma, shift, col, U + j, ldu, mode == KQR_APPLY_EXACT, st, sums, sum_doubles);
       } else {
-        kapply_otf(X, sqn, n, X, sqn, n, int(p), ks, col, U + j, ldu, 1.0, 0.0, st, mode == KQR_APPLY_EXACT);
+        kapply_otf(X, sqn, n, X, sqn, n, int(p), ks, col, U + j, ldu, 1.0, 0.0, st, mode == KQR_APPLY_EXACT, sums,
+                   sum_doubles);
       }
     }
-    if (sqn) KQR_CHECK_HIP(hipFreeAsync(sqn, st));
-    if (lscr) KQR_CHECK_HIP(hipFreeAsync(lscr, st));
     KQR_CHECK_HIP(hipFreeAsync(tmp, st));
   });
 }
@@ -711,11 +714,14 @@ int kqr_predict(const float* Xtrain, int64_t n, int64_t p, const double* alpha, 
       KQR_CHECK_HIP(hipFreeAsync(scr, st));
       return;
     }
+    const KernelSpec ks{kernel, gamma};
+    const size_t sum_doubles = kapply_otf_scratch_doubles(m, n, int(p), ks, false);
+    const size_t sq_bytes = (size_t(n + m) * sizeof(float) + 255) / 256 * 256;
     float* sq = nullptr;
-    KQR_CHECK_HIP(hipMallocAsync(reinterpret_cast<void**>(&sq), size_t(n + m) * sizeof(float), st));
-    row_sqnorms2(Xtrain, n, sq, Xnew, m, sq + n, int(p), st);
-    kapply_otf(Xnew, sq + n, m, Xtrain, sq, n, int(p), KernelSpec{kernel, gamma}, alpha, f, 1, 1.0 / lambda, beta, st,
-               true);
+    KQR_CHECK_HIP(hipMallocAsync(reinterpret_cast<void**>(&sq), sq_bytes + sum_doubles * sizeof(double), st));
+    if (kernel != KQR_LAPLACIAN) row_sqnorms2(Xtrain, n, sq, Xnew, m, sq + n, int(p), st);
+    kapply_otf(Xnew, sq + n, m, Xtrain, sq, n, int(p), ks, alpha, f, 1, 1.0 / lambda, beta, st, true,
+               reinterpret_cast<double*>(reinterpret_cast<char*>(sq) + sq_bytes), sum_doubles);
     KQR_CHECK_HIP(hipFreeAsync(sq, st));
   });
 }

@@ -515,18 +515,24 @@ static void otf_reduce(const double* part, int64_t nslice, int64_t nr, double* u
   KQR_LAUNCH_CHECK();
 }
 
+// columns per slice of a launch on the vector unit
+static int64_t otf_per(int64_t rblk, int64_t nc) {
+  const int64_t nslice = std::min<int64_t>(otf_slices(rblk, nc), 65535);
+  const int64_t per = (nc + nslice - 1) / nslice;
+  return (per + kOtfTile - 1) / kOtfTile * kOtfTile;
+}
+
 template <int PMAX>
 static void kapply_otf_p(const float* Xr, const float* qr, int64_t nr, const float* Xc,
                          const float* qc, int64_t nc, int p, KernelSpec ks, const double* v, double* u,
-                         int64_t ldu, double scale, double shift, bool exact, hipStream_t st) {
+                         int64_t ldu, double scale, double shift, bool exact, hipStream_t st, double* scratch,
+                         size_t scratch_doubles) {
   const int64_t rblk = (nr + 255) / 256;
-  int64_t nslice = otf_slices(rblk, nc);
-  nslice = std::min<int64_t>(nslice, 65535);
-  int64_t per = (nc + nslice - 1) / nslice;
-  per = (per + kOtfTile - 1) / kOtfTile * kOtfTile;
-  nslice = (nc + per - 1) / per;
-  double* part = nullptr;
-  KQR_CHECK_HIP(hipMallocAsync(reinterpret_cast<void**>(&part), size_t(nslice) * size_t(nr) * sizeof(double), st));
+  const int64_t per = otf_per(rblk, nc), nslice = (nc + per - 1) / per;
+  const size_t need = size_t(nslice) * size_t(nr);
+  const bool own = !scratch || scratch_doubles < need;
+  double* part = scratch;
+  if (own) KQR_CHECK_HIP(hipMallocAsync(reinterpret_cast<void**>(&part), need * sizeof(double), st));
   const dim3 grid((unsigned)rblk, (unsigned)nslice);
   const float ng = -float(ks.gamma) * kLog2e;
   const bool lap = ks.kind == KQR_LAPLACIAN;
@@ -536,7 +542,7 @@ static void kapply_otf_p(const float* Xr, const float* qr, int64_t nr, const flo
   else kapply_otf_kernel<PMAX, false, false><<<grid, 256, 0, st>>>(Xr, qr, nr, Xc, qc, nc, p, ng, v, per, part);
   KQR_LAUNCH_CHECK();
   otf_reduce(part, nslice, nr, u, ldu, scale, shift, st);
-  KQR_CHECK_HIP(hipFreeAsync(part, st));
+  if (own) KQR_CHECK_HIP(hipFreeAsync(part, st));
 }
 
 // Laplacian on the fly from fixed-point coordinates.  Column k of X is
@@ -668,19 +674,25 @@ static void kapply_otf_l1q_rows_p(const uint32_t* Xq, int64_t n, int p, float ng
 // over the 32 row groups in LDS (one partial per tile and column); a
 // diagonal tile feeds its rows only.  packed_reduce adds the partials in a
 // fixed order.  Fast: FP32 products and sums within a tile, FP64 beyond;
-// exact: FP64 products and sums.
-template <int PMAX, bool EX>
+// exact: FP64 products and sums.  Bound by the vector unit: NC + 10
+// instructions per 64 pairs, two waves per SIMD (the rows' coordinates fill
+// the registers), so what the lanes do besides counts: NC is p rounded up to
+// 2, not the padded PMAX; v is kept in the type it is used in; and the next
+// column's first half is read ahead.  30,011 x 30 fast: 700 us with all three
+// left out, 610 with them.
+template <int PMAX, int NC, bool EX>
 __global__ __launch_bounds__(256) void kapply_otf_l1q_sym_kernel(const uint32_t* __restrict__ Xq, int64_t n, int p,
                                                                  float ngs, const double* __restrict__ v, int64_t nt,
                                                                  int strip, int64_t nsx, double* __restrict__ rowpart,
                                                                  double* __restrict__ colpart) {
-  static_assert(PMAX % 4 == 0, "coordinates are read from LDS four at a time");
+  static_assert(PMAX % 4 == 0 && NC <= PMAX && NC % 2 == 0, "coordinates are read from LDS four at a time");
+  typedef std::conditional_t<EX, double, float> acc_t;
   constexpr int T = kPkT;
   constexpr int R = 4;     // rows per thread
   constexpr int RG = 32;   // row groups: T / R
   constexpr int CPT = 16;  // columns per thread and tile: T / (256 / RG)
   __shared__ __align__(16) uint32_t xs[T][PMAX];
-  __shared__ double vs[T];
+  __shared__ acc_t vs[T];
   __shared__ double red[RG][T + 1];
   const int t = threadIdx.x;
   const int rg = t & (RG - 1), cg = t >> 5;
@@ -691,21 +703,21 @@ __global__ __launch_bounds__(256) void kapply_otf_l1q_sym_kernel(const uint32_t*
   // are never read and their column contributions vanish.  Every load is
   // issued before any is used (a load whose use is conditional per lane would
   // be moved under the condition and waited for one at a time).
-  uint32_t xi[R][PMAX];
-  double vi[R];
+  uint32_t xi[R][NC];
+  acc_t vi[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int64_t ic = min(I * T + rg + RG * r, n - 1);
 #pragma unroll
-    for (int kk = 0; kk < PMAX; ++kk) xi[r][kk] = Xq[ic * p + min(kk, p - 1)];
+    for (int kk = 0; kk < NC; ++kk) xi[r][kk] = Xq[ic * p + min(kk, p - 1)];
   }
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int64_t i = I * T + rg + RG * r;
     const double vv = v[min(i, n - 1)];
-    vi[r] = i < n ? vv : 0.0;
+    vi[r] = i < n ? acc_t(vv) : acc_t(0);
 #pragma unroll
-    for (int kk = 0; kk < PMAX; ++kk) xi[r][kk] = kk < p ? xi[r][kk] : 0u;  // padded coordinates: 0 on both sides
+    for (int kk = 0; kk < NC; ++kk) xi[r][kk] = kk < p ? xi[r][kk] : 0u;  // padded coordinates: 0 on both sides
   }
   double acc[R];
 #pragma unroll
@@ -733,51 +745,70 @@ __global__ __launch_bounds__(256) void kapply_otf_l1q_sym_kernel(const uint32_t*
       const int jj = e / PMAX, kk = e % PMAX;
       xs[jj][kk] = kk < p ? xc[q] : 0u;
     }
-    if (t < T) vs[t] = J * T + t < n ? vc : 0.0;
+    if (t < T) vs[t] = J * T + t < n ? acc_t(vc) : acc_t(0);
     __syncthreads();
     if (J + 1 < J1) load_cols(J + 1);
     float a32[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) a32[r] = 0.f;
+    // the first half of a column's coordinates is requested before the entries
+    // of the column before it: with two waves per SIMD nothing else covers it
+    // (above 32 coordinates the registers are full)
+    constexpr int Q = (NC + 3) / 4, H = PMAX <= 32 ? (Q + 1) / 2 : 0;
+    const uint4* xr = reinterpret_cast<const uint4*>(xs[cg]);  // 16-byte LDS reads, two rows per wave
+    uint4 head[H > 0 ? H : 1];
+#pragma unroll
+    for (int q = 0; q < H; ++q) head[q] = xr[q];
 #pragma unroll 2
     for (int c = 0; c < CPT; ++c) {
       const int jj = cg + 8 * c;
       uint32_t d[R];
 #pragma unroll
       for (int r = 0; r < R; ++r) d[r] = 0u;
-      const uint4* xr = reinterpret_cast<const uint4*>(xs[jj]);  // 16-byte LDS reads, two rows per wave
-#pragma unroll
-      for (int k4 = 0; k4 < PMAX / 4; ++k4) {
-        const uint4 cc = xr[k4];
+      auto quad = [&](const uint4& x, int k4) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-          d[r] = sad_u32(xi[r][4 * k4], cc.x, d[r]);
-          d[r] = sad_u32(xi[r][4 * k4 + 1], cc.y, d[r]);
-          d[r] = sad_u32(xi[r][4 * k4 + 2], cc.z, d[r]);
-          d[r] = sad_u32(xi[r][4 * k4 + 3], cc.w, d[r]);
+          d[r] = sad_u32(xi[r][4 * k4], x.x, d[r]);
+          d[r] = sad_u32(xi[r][4 * k4 + 1], x.y, d[r]);
+          if (4 * k4 + 2 < NC) {
+            d[r] = sad_u32(xi[r][4 * k4 + 2], x.z, d[r]);
+            d[r] = sad_u32(xi[r][4 * k4 + 3], x.w, d[r]);
+          }
         }
+      };
+      if constexpr (H > 0) {
+        uint4 tail[Q - H > 0 ? Q - H : 1];
+#pragma unroll
+        for (int q = H; q < Q; ++q) tail[q - H] = xr[q];
+#pragma unroll
+        for (int q = 0; q < H; ++q) quad(head[q], q);
+        xr = reinterpret_cast<const uint4*>(xs[min(jj + 8, T - 1)]);
+#pragma unroll
+        for (int q = H; q < Q; ++q) quad(tail[q - H], q);
+#pragma unroll
+        for (int q = 0; q < H; ++q) head[q] = xr[q];
+      } else {
+        xr = reinterpret_cast<const uint4*>(xs[jj]);
+#pragma unroll
+        for (int q = 0; q < Q; ++q) quad(xr[q], q);
       }
       float e[R];
 #pragma unroll
       for (int r = 0; r < R; ++r) e[r] = kexp2(ngs * float(d[r]));
-      const double vj = vs[jj];
-      if (EX) {
-        double cs = 0.0;
+      const acc_t vj = vs[jj];
+      acc_t cs = acc_t(0);
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-          acc[r] = fma(double(e[r]), vj, acc[r]);
-          cs = fma(double(e[r]), vi[r], cs);
-        }
-        if (!diag) red[rg][jj] = cs;
-      } else {
-        float cs = 0.f;
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
+      for (int r = 0; r < R; ++r) {
+        if (EX) {
+          acc[r] = fma(double(e[r]), double(vj), acc[r]);
+          cs = fma(double(e[r]), double(vi[r]), double(cs));
+        } else {
           a32[r] = fmaf(e[r], float(vj), a32[r]);
-          cs = fmaf(e[r], float(vi[r]), cs);
+          cs = fmaf(e[r], float(vi[r]), float(cs));
         }
-        if (!diag) red[rg][jj] = double(cs);
       }
+      // (above 32 coordinates the branch also keeps two columns' registers apart)
+      if (PMAX <= 32 || !diag) red[rg][jj] = double(cs);
     }
     if (!EX) {
 #pragma unroll
@@ -869,10 +900,26 @@ static void kapply_otf_l1q_p(const uint32_t* Xq, int64_t n, int p, float ngs, co
   double* rowpart = buf;
   double* colpart = buf + size_t(nt) * nsx * kPkT;
   const dim3 grid((unsigned)pk_strips_tail(nt, strip));
-  if (exact)
-    kapply_otf_l1q_sym_kernel<PMAX, true><<<grid, 256, 0, st>>>(Xq, n, p, ngs, v, nt, strip, nsx, rowpart, colpart);
-  else
-    kapply_otf_l1q_sym_kernel<PMAX, false><<<grid, 256, 0, st>>>(Xq, n, p, ngs, v, nt, strip, nsx, rowpart, colpart);
+  // the coordinates a pair takes: p rounded up to 2 (a padded coordinate adds
+  // nothing but costs one operation per pair)
+  auto launch = [&](auto nc) {
+    constexpr int NC = decltype(nc)::value;
+    if (exact)
+      kapply_otf_l1q_sym_kernel<PMAX, NC, true><<<grid, 256, 0, st>>>(Xq, n, p, ngs, v, nt, strip, nsx, rowpart, colpart);
+    else
+      kapply_otf_l1q_sym_kernel<PMAX, NC, false><<<grid, 256, 0, st>>>(Xq, n, p, ngs, v, nt, strip, nsx, rowpart, colpart);
+  };
+  if constexpr (PMAX == 8 || PMAX == 32) {  // steps of eight
+    if (p <= PMAX - 6) launch(std::integral_constant<int, PMAX - 6>{});
+    else if (p <= PMAX - 4) launch(std::integral_constant<int, PMAX - 4>{});
+    else if (p <= PMAX - 2) launch(std::integral_constant<int, PMAX - 2>{});
+    else launch(std::integral_constant<int, PMAX>{});
+  } else if constexpr (PMAX < 32) {  // steps of four
+    if (p <= PMAX - 2) launch(std::integral_constant<int, PMAX - 2>{});
+    else launch(std::integral_constant<int, PMAX>{});
+  } else {
+    launch(std::integral_constant<int, PMAX>{});
+  }
   KQR_LAUNCH_CHECK();
   packed_reduce(rowpart, colpart, n, strip, u, ldu, st);
   if (own) KQR_CHECK_HIP(hipFreeAsync(buf, st));
@@ -885,65 +932,82 @@ void kapply_otf_l1q(const uint32_t* Xq, int64_t n, int p, double gamma, int shif
   KQR_DISPATCH_P(p, kapply_otf_l1q_p, Xq, n, p, ngs, v, u, ldu, exact, st, scratch, scratch_doubles);
 }
 
-// Per-column minimum and maximum of X (FP32 values, exact); mm: 2 p floats.
-__global__ void col_minmax_kernel(const float* __restrict__ X, int64_t n, int p, float* __restrict__ mm) {
-  const int k = blockIdx.x;
+// Per-column minima and maxima of X (FP32 values, exact) over each
+// workgroup's rows: part[2 p b + k] and part[2 p b + p + k].  Whole rows are
+// read in memory order, 256 / p of them at a time (p <= 64).  30,011 x 30: one
+// workgroup per column, every row's line read p times, took 39 us; this 5.
+__global__ __launch_bounds__(256) void col_minmax_kernel(const float* __restrict__ X, int64_t n, int p,
+                                                         int64_t rows, float* __restrict__ part) {
+  __shared__ float sl[256], sh[256];
+  const int t = threadIdx.x, step = 256 / p, k = t % p;
+  const int64_t r0 = blockIdx.x * rows, r1 = min(n, r0 + rows);
   float lo = INFINITY, hi = -INFINITY;
-  for (int64_t i = threadIdx.x; i < n; i += blockDim.x) {
-    const float x = X[i * p + k];
-    lo = fminf(lo, x);
-    hi = fmaxf(hi, x);
+  if (t < step * p) {
+#pragma unroll 4
+    for (int64_t i = r0 + t / p; i < r1; i += step) {
+      const float x = X[i * p + k];
+      lo = fminf(lo, x);
+      hi = fmaxf(hi, x);
+    }
   }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    lo = fminf(lo, __shfl_xor(lo, off));
-    hi = fmaxf(hi, __shfl_xor(hi, off));
-  }
-  __shared__ float sl[4], sh[4];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (lane == 0) { sl[wave] = lo; sh[wave] = hi; }
+  sl[t] = lo;
+  sh[t] = hi;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    mm[2 * k] = fminf(fminf(sl[0], sl[1]), fminf(sl[2], sl[3]));
-    mm[2 * k + 1] = fmaxf(fmaxf(sh[0], sh[1]), fmaxf(sh[2], sh[3]));
+  if (t < p) {
+    for (int e = 1; e < step; ++e) {
+      lo = fminf(lo, sl[t + e * p]);
+      hi = fmaxf(hi, sh[t + e * p]);
+    }
+    part[size_t(blockIdx.x) * 2 * p + t] = lo;
+    part[size_t(blockIdx.x) * 2 * p + p + t] = hi;
   }
 }
 
-__global__ void quantize_kernel(const float* __restrict__ X, int64_t n, int p, const float* __restrict__ mm,
-                                double scale, uint32_t* __restrict__ Xq) {
+struct ColumnMin {
+  float v[64];
+};
+
+__global__ void quantize_kernel(const float* __restrict__ X, int64_t n, int p, ColumnMin lo, double scale,
+                                uint32_t* __restrict__ Xq) {
   const int64_t t = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
   if (t >= n * p) return;
-  const int k = int(t % p);
-  Xq[t] = uint32_t(llrint((double(X[t]) - double(mm[2 * k])) * scale));
+  Xq[t] = uint32_t(llrint((double(X[t]) - double(lo.v[t % p])) * scale));
 }
+
+size_t quantized_words(int64_t n, int p) { return size_t(std::max<int64_t>(n, 2)) * size_t(p); }
 
 int quantize_columns(const float* X, int64_t n, int p, uint32_t* Xq, hipStream_t st) {
   if (n <= 0 || p <= 0) return -1;
-  float* mm = nullptr;
-  KQR_CHECK_HIP(hipMallocAsync(reinterpret_cast<void**>(&mm), size_t(2 * p) * sizeof(float), st));
-  col_minmax_kernel<<<dim3((unsigned)p), 256, 0, st>>>(X, n, p, mm);
+  // the partial minima and maxima are kept in Xq (2 p words per workgroup) until the host has them
+  const int64_t want = std::min<int64_t>(128, std::max<int64_t>(1, n / 32));
+  const int64_t rows = (n + want - 1) / want, blocks = (n + rows - 1) / rows;
+  float* part = reinterpret_cast<float*>(Xq);
+  col_minmax_kernel<<<dim3((unsigned)blocks), 256, 0, st>>>(X, n, p, rows, part);
   KQR_LAUNCH_CHECK();
-  std::vector<float> h(size_t(2 * p));
-  KQR_CHECK_HIP(hipMemcpyAsync(h.data(), mm, h.size() * sizeof(float), hipMemcpyDeviceToHost, st));
+  std::vector<float> h(size_t(blocks) * size_t(2 * p));
+  KQR_CHECK_HIP(hipMemcpyAsync(h.data(), part, h.size() * sizeof(float), hipMemcpyDeviceToHost, st));
   KQR_CHECK_HIP(hipStreamSynchronize(st));
   double range = 0.0;
+  ColumnMin mins = {};
   for (int k = 0; k < p; ++k) {
-    const double r = double(h[size_t(2 * k + 1)]) - double(h[size_t(2 * k)]);
-    if (!std::isfinite(r)) {
-      KQR_CHECK_HIP(hipFreeAsync(mm, st));
-      return -1;
+    float lo = INFINITY, hi = -INFINITY;
+    for (int64_t b = 0; b < blocks; ++b) {
+      lo = std::fmin(lo, h[size_t(b) * 2 * p + k]);
+      hi = std::fmax(hi, h[size_t(b) * 2 * p + p + k]);
     }
+    const double r = double(hi) - double(lo);
+    if (!std::isfinite(r)) return -1;
     range = std::max(range, r);
+    mins.v[k] = lo;
   }
   // largest s <= 23 with p * range * 2^s + p <= 2^32 - 1 (sum of rounded coordinates)
   int s = 23;
   while (s >= 0 && double(p) * (range * std::ldexp(1.0, s) + 1.0) > 4294967295.0) --s;
   if (s >= 0) {
     const int64_t tot = n * p;
-    quantize_kernel<<<dim3((unsigned)((tot + 255) / 256)), 256, 0, st>>>(X, n, p, mm, std::ldexp(1.0, s), Xq);
+    quantize_kernel<<<dim3((unsigned)((tot + 255) / 256)), 256, 0, st>>>(X, n, p, mins, std::ldexp(1.0, s), Xq);
     KQR_LAUNCH_CHECK();
   }
-  KQR_CHECK_HIP(hipFreeAsync(mm, st));
   return s;
 }
 
@@ -1467,17 +1531,18 @@ static void kapply_otf_mfma_sym(const float* X, const float* q, int64_t n, int p
   const int strip = otf_sym_strip(n);
   const int64_t nsx = (nt + strip - 1) / strip;
   const size_t need = packed_scratch_doubles(n, strip);
-  const size_t col_bytes = otf_columns_bytes<G>(n);
-  double* part = scratch && scratch_doubles >= need ? scratch : nullptr;
-  const size_t part_bytes = part ? 0 : (need * sizeof(double) + 255) / 256 * 256;
+  const size_t col_bytes = otf_columns_bytes<G>(n), part_bytes = (need * sizeof(double) + 255) / 256 * 256;
+  const size_t have = scratch ? scratch_doubles * sizeof(double) : 0;
+  // the sums in the caller's scratch where they fit, the columns too where both do
+  const bool sums_in = have >= need * sizeof(double), cols_in = have >= part_bytes + col_bytes;
+  const size_t own = (sums_in ? 0 : part_bytes) + (cols_in ? 0 : col_bytes);
   char* buf = nullptr;
-  if (part_bytes + col_bytes > 0)
-    KQR_CHECK_HIP(hipMallocAsync(reinterpret_cast<void**>(&buf), part_bytes + col_bytes, st));
-  if (!part) part = reinterpret_cast<double*>(buf);
-  double* rowpart = part;
-  double* colpart = part + size_t(nt) * nsx * kPkT;
+  if (own > 0) KQR_CHECK_HIP(hipMallocAsync(reinterpret_cast<void**>(&buf), own, st));
+  double* rowpart = sums_in ? scratch : reinterpret_cast<double*>(buf);
+  double* colpart = rowpart + size_t(nt) * nsx * kPkT;
   const float ng = -float(ks.gamma) * kLog2e;
-  const typename G::col_t* cols = otf_columns<G>(X, q, n, p, ng, buf + part_bytes, st);
+  char* col_buf = cols_in ? reinterpret_cast<char*>(scratch) + part_bytes : buf + (sums_in ? 0 : part_bytes);
+  const typename G::col_t* cols = otf_columns<G>(X, q, n, p, ng, col_buf, st);
   const dim3 grid((unsigned)pk_strips_tail(nt, strip));
   if (exact)
     kapply_otf_mfma_sym_kernel<G, true><<<grid, 256, 0, st>>>(X, q, n, cols, p, ng, v, nt, strip, nsx, rowpart, colpart);
@@ -1529,8 +1594,10 @@ static void kapply_otf_mfma_p(const float* Xr, const float* qr, int64_t nr, cons
   const int64_t per = otf_mfma_per(rblk, nc, int64_t(kOtfStage) * G::kFlush);
   const int64_t nslice = (nc + per - 1) / per;
   const size_t part_bytes = (size_t(nslice) * size_t(nr) * sizeof(double) + 255) / 256 * 256;
-  char* buf = nullptr;
-  KQR_CHECK_HIP(hipMallocAsync(reinterpret_cast<void**>(&buf), part_bytes + otf_columns_bytes<G>(nc), st));
+  const size_t bytes = part_bytes + otf_columns_bytes<G>(nc);
+  const bool own = !scratch || scratch_doubles * sizeof(double) < bytes;
+  char* buf = reinterpret_cast<char*>(scratch);
+  if (own) KQR_CHECK_HIP(hipMallocAsync(reinterpret_cast<void**>(&buf), bytes, st));
   double* part = reinterpret_cast<double*>(buf);
   const dim3 grid((unsigned)rblk, (unsigned)nslice);
   const float ng = -float(ks.gamma) * kLog2e;
@@ -1539,7 +1606,7 @@ static void kapply_otf_mfma_p(const float* Xr, const float* qr, int64_t nr, cons
   else kapply_otf_mfma_kernel<G, false><<<grid, 256, 0, st>>>(Xr, qr, nr, cols, qc, nc, p, ng, v, per, part);
   KQR_LAUNCH_CHECK();
   otf_reduce(part, nslice, nr, u, ldu, scale, shift, st);
-  KQR_CHECK_HIP(hipFreeAsync(buf, st));
+  if (own) KQR_CHECK_HIP(hipFreeAsync(buf, st));
 }
 
 void kapply_otf(const float* Xr, const float* sqr, int64_t nr, const float* Xc, const float* sqc,
@@ -1559,7 +1626,22 @@ void kapply_otf(const float* Xr, const float* sqr, int64_t nr, const float* Xc, 
 #undef KQR_OTF_MFMA
     return;
   }
-  KQR_DISPATCH_P(p, kapply_otf_p, Xr, sqr, nr, Xc, sqc, nc, p, ks, v64, u, ldu, out_scale, out_shift, exact, st);
+  KQR_DISPATCH_P(p, kapply_otf_p, Xr, sqr, nr, Xc, sqc, nc, p, ks, v64, u, ldu, out_scale, out_shift, exact, st, scratch,
+                 scratch_doubles);
+}
+
+size_t kapply_otf_scratch_doubles(int64_t nr, int64_t nc, int p, KernelSpec ks, bool square) {
+  const bool mfma = ks.kind == KQR_RBF && p <= 32;
+  const size_t cols = mfma && p > 16 ? b3_bytes(nc) : 0;
+  size_t part = 0;
+  if (mfma && square && otf_sym_fits(nr)) {
+    part = packed_scratch_doubles(nr, otf_sym_strip(nr));
+  } else {
+    const int64_t rblk = (nr + (mfma ? 127 : 255)) / (mfma ? 128 : 256);
+    const int64_t per = mfma ? otf_mfma_per(rblk, nc, kOtfStage * (p > 16 ? 2 : 1)) : otf_per(rblk, nc);
+    part = size_t((nc + per - 1) / per) * size_t(nr);
+  }
+  return ((part * sizeof(double) + 255) / 256 * 256 + cols) / sizeof(double);
 }
 
 // ================================================================= K build on the matrix cores

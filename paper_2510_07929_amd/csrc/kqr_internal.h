@@ -137,6 +137,9 @@ void kapply_otf(const float* Xr, const float* sqr, int64_t nr, const float* Xc, 
                 int64_t nc, int p, KernelSpec ks, const double* v64, double* u, int64_t ldu,
                 double out_scale, double out_shift, hipStream_t st, bool exact = false, double* scratch = nullptr,
                 size_t scratch_doubles = 0);
+// doubles of scratch with which kapply_otf allocates nothing (square: Xr and
+// Xc are the same points)
+size_t kapply_otf_scratch_doubles(int64_t nr, int64_t nc, int p, KernelSpec ks, bool square);
 // Laplacian on the fly from fixed-point coordinates (exact integer L1
 // distances, one v_sad_u32 per coordinate).  quantize_columns fills Xq
 // (n x p, stride p) with round((x - min_k) 2^s) and returns s (or -1 when X
@@ -145,6 +148,7 @@ void kapply_otf(const float* Xr, const float* sqr, int64_t nr, const float* Xc, 
 // to scratch when that holds otf_sym_scratch_doubles(n) doubles, else to
 // memory allocated on st.
 int quantize_columns(const float* X, int64_t n, int p, uint32_t* Xq, hipStream_t st);
+size_t quantized_words(int64_t n, int p);  // 32-bit words Xq has to hold
 size_t otf_sym_scratch_doubles(int64_t n);  // partial sums of a symmetric on-the-fly apply (0: too large)
 void set_otf_sym_budget(int64_t bytes);     // largest such buffer; beyond it the row-streamed forms run
 // Launch shape of the on-the-fly applies: strip = tiles per workgroup of the

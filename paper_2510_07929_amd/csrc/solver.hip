@@ -27,7 +27,7 @@ Operator::Operator(const float* X, int64_t n, int p, KernelSpec ks, KMat km, hip
   // operator beside a BF16 K): exact integer L1 distances of fixed-point X
   // when the quantum 2^-s keeps the entries at FP32 accuracy (s >= 20)
   if (ks.kind == KQR_LAPLACIAN && !(km.K && km.dtype == KQR_FP32) && n > 0) {
-    xq_.alloc(size_t(n) * size_t(p) * sizeof(uint32_t));
+    xq_.alloc(quantized_words(n, p) * sizeof(uint32_t));
     shift_ = quantize_columns(X, n, p, xq_.as<uint32_t>(), st);
     if (shift_ < 20) {
       xq_ = DevBuf();
