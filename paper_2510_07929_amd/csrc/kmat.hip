@@ -554,9 +554,14 @@ static void kapply_otf_p(const float* Xr, const float* qr, int64_t nr, const flo
 // 2^32 - 1.  The entry is exp2(-gamma log2(e) 2^-s float(d)), the rest as in
 // kapply_otf_kernel.
 __device__ __forceinline__ uint32_t sad_u32(uint32_t a, uint32_t b, uint32_t c) {
-  uint32_t r;
-  asm("v_sad_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-  return r;
+  return (max(a, b) - min(a, b)) + c;  // one v_sad_u32 (an asm statement here brought an s_nop per four)
+}
+// a zero the compiler does not know: a sum that starts from a known one costs
+// three instructions for its first coordinate
+__device__ __forceinline__ uint32_t opaque_zero() {
+  uint32_t z = 0;
+  asm("" : "+v"(z));
+  return z;
 }
 
 // Row-streamed form over all n^2 pairs (used when the symmetric form's
@@ -582,6 +587,7 @@ __global__ __launch_bounds__(256) void kapply_otf_l1q_kernel(const uint32_t* __r
   }
   const int64_t c0 = int64_t(blockIdx.y) * cols_per_slice;
   const int64_t c1 = min(n, c0 + cols_per_slice);
+  const uint32_t zero = opaque_zero();
   double acc[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) acc[r] = 0.0;
@@ -605,7 +611,7 @@ __global__ __launch_bounds__(256) void kapply_otf_l1q_kernel(const uint32_t* __r
     for (int jj = 0; jj < cnt; ++jj) {
       uint32_t d[R];
 #pragma unroll
-      for (int r = 0; r < R; ++r) d[r] = 0u;
+      for (int r = 0; r < R; ++r) d[r] = zero;
       const uint4* xr = reinterpret_cast<const uint4*>(xs[jj]);  // broadcast 16-byte LDS reads
 #pragma unroll
       for (int k4 = 0; k4 < PMAX / 4; ++k4) {
@@ -679,7 +685,7 @@ static void kapply_otf_l1q_rows_p(const uint32_t* Xq, int64_t n, int p, float ng
 // the registers), so what the lanes do besides counts: NC is p rounded up to
 // 2, not the padded PMAX; v is kept in the type it is used in; and the next
 // column's first half is read ahead.  30,011 x 30 fast: 700 us with all three
-// left out, 610 with them.
+// left out, 605 with them.
 template <int PMAX, int NC, bool EX>
 __global__ __launch_bounds__(256) void kapply_otf_l1q_sym_kernel(const uint32_t* __restrict__ Xq, int64_t n, int p,
                                                                  float ngs, const double* __restrict__ v, int64_t nt,
@@ -719,6 +725,7 @@ __global__ __launch_bounds__(256) void kapply_otf_l1q_sym_kernel(const uint32_t*
 #pragma unroll
     for (int kk = 0; kk < NC; ++kk) xi[r][kk] = kk < p ? xi[r][kk] : 0u;  // padded coordinates: 0 on both sides
   }
+  const uint32_t zero = opaque_zero();
   double acc[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) acc[r] = 0.0;
@@ -764,8 +771,8 @@ __global__ __launch_bounds__(256) void kapply_otf_l1q_sym_kernel(const uint32_t*
       const int jj = cg + 8 * c;
       uint32_t d[R];
 #pragma unroll
-      for (int r = 0; r < R; ++r) d[r] = 0u;
-      auto quad = [&](const uint4& x, int k4) {
+      for (int r = 0; r < R; ++r) d[r] = zero;
+      auto quad = [&](uint4 x, int k4) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
           d[r] = sad_u32(xi[r][4 * k4], x.x, d[r]);
