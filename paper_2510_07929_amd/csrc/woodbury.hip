@@ -313,87 +313,103 @@ __device__ __forceinline__ double rsqrt_f64(double a) {
   return y;
 }
 
-// Diagonal block (nb <= 64), one wave.  The block sits in LDS column-major
-// (Ac[k][i] = A[i][k]) and lane l owns row l.  Columns go in panels of
-// eight: every lane first subtracts sum_{k<j0} L[l][k] L[j][k] from its row's
-// eight panel entries (per earlier column k: its own L[l][k], a
-// conflict-free read, and the panel rows' L[j0..j0+7][k], contiguous
-// broadcast reads), then finishes the panel in registers column by column:
-// the pivot comes from lane j (readlane), its reciprocal square root from
-// rsqrt_f64, and the multipliers L[j0+c2][j] of the later panel columns from
-// their lanes, so the panel needs no LDS traffic and no barrier until it is
-// written back.  The loop over panels is not unrolled, so the kernel stays
-// small in the instruction cache.
-__global__ __launch_bounds__(64) void chol_diag_kernel(double* __restrict__ C, int64_t ldc, int kb, int nb,
-                                                       int* __restrict__ flag) {
-  __shared__ __align__(16) double Ac[kNb][kNb + 2];  // row stride 528 bytes: 16-byte aligned, banks spread
-  const int l = threadIdx.x;
+// acc - sum over k < kn of a(k) b(k) of one 16 x 16 tile on the matrix cores,
+// k ascending four at a time (bitwise the chain of FMAs): a points at the tile
+// rows' and b at the tile columns' entries of column 0 (column k is `ld`
+// doubles on), both in LDS.
+__device__ __forceinline__ f64x4 chol_tile_sub(f64x4 acc, const double* a, const double* b, int lda, int ldb,
+                                                 int kn, int lane) {
+  const double* ap = a + (lane >> 4) * lda + (lane & 15);
+  const double* bp = b + (lane >> 4) * ldb + (lane & 15);
+#pragma unroll 4
+  for (int k = 0; k < kn; k += 4)
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-ap[k * lda], bp[k * ldb], acc, 0, 0, 0);
+  return acc;
+}
+
+// Diagonal block (nb <= 64), four waves.  The block sits in LDS column-major
+// (Ac[k][i] = A[i][k]).  Columns go in panels of sixteen.  First wave w
+// subtracts the earlier panels' part sum_{k<j0} L[i][k] L[j][k] from the
+// panel's entries of rows 16 w .. 16 w + 15 on the matrix cores; then the
+// first wave, lane l owning row l, finishes the panel in registers column by
+// column: the pivot comes from lane j (readlane), its reciprocal square root
+// from rsqrt_f64, and the multipliers L[j0+c2][j] of the later panel columns
+// from their lanes, so the panel needs no LDS traffic and no barrier until it
+// is written back.  Bound by that chain of 64 pivots.  With the earlier part
+// formed by the one wave too, five LDS reads per column k and panels of
+// eight, the launch took 20.2 us, now 15.1.
+__global__ __launch_bounds__(256) void chol_diag_kernel(double* __restrict__ C, int64_t ldc, int kb, int nb,
+                                                        int* __restrict__ flag) {
+  constexpr int S = kNb + 2;  // row stride 528 bytes: 16-byte aligned, banks spread
+  __shared__ __align__(16) double Ac[kNb][S];
+  const int l = threadIdx.x & 63, wave = threadIdx.x >> 6;
   // 32-bit offsets within the block: a 64-bit product per row for the loads
   // and again for the stores was a tenth of the kernel's time
   double* D = C + int64_t(kb) * ldc + kb;
   const int ld = int(ldc);
   // coalesced: one row of the block per step, lane l reads column l (the
-  // address clamped into the block's lower triangle, so all 64 loads are in
+  // address clamped into the block's lower triangle, so all loads are in
   // flight at once)
   {
-    double t[kNb];
+    double t[16];
 #pragma unroll
-    for (int i = 0; i < kNb; ++i) {
-      const int ic = min(i, nb - 1);
-      t[i] = D[ic * ld + min(l, ic)];
+    for (int e = 0; e < 16; ++e) {
+      const int ic = min(16 * wave + e, nb - 1);
+      t[e] = D[ic * ld + min(l, ic)];
     }
 #pragma unroll
-    for (int i = 0; i < kNb; ++i) Ac[l][i] = (i < nb && l <= i) ? t[i] : (i == l ? 1.0 : 0.0);
+    for (int e = 0; e < 16; ++e) {
+      const int i = 16 * wave + e;
+      Ac[l][i] = (i < nb && l <= i) ? t[e] : (i == l ? 1.0 : 0.0);
+    }
   }
   __syncthreads();
   bool bad = false;
-  constexpr int PW = 8;
+  constexpr int PW = 16;
   for (int j0 = 0; j0 < kNb; j0 += PW) {
-    double v[PW];
+    if (j0 > 0) {
+      if (16 * wave >= j0) {  // (uniform per wave) rows above the panel's diagonal tile are not used
+        double* o = &Ac[j0 + (l & 15)][16 * wave + (l >> 4)];
+        f64x4 acc;
 #pragma unroll
-    for (int c = 0; c < PW; ++c) v[c] = Ac[j0 + c][l];
-#pragma unroll 8
-    for (int k = 0; k < j0; ++k) {
-      const double a = Ac[k][l];
-      const double2 b01 = *reinterpret_cast<const double2*>(&Ac[k][j0]);
-      const double2 b23 = *reinterpret_cast<const double2*>(&Ac[k][j0 + 2]);
-      const double2 b45 = *reinterpret_cast<const double2*>(&Ac[k][j0 + 4]);
-      const double2 b67 = *reinterpret_cast<const double2*>(&Ac[k][j0 + 6]);
-      v[0] = fma(-a, b01.x, v[0]);
-      v[1] = fma(-a, b01.y, v[1]);
-      v[2] = fma(-a, b23.x, v[2]);
-      v[3] = fma(-a, b23.y, v[3]);
-      v[4] = fma(-a, b45.x, v[4]);
-      v[5] = fma(-a, b45.y, v[5]);
-      v[6] = fma(-a, b67.x, v[6]);
-      v[7] = fma(-a, b67.y, v[7]);
-    }
+        for (int v = 0; v < 4; ++v) acc[v] = o[4 * v];
+        acc = chol_tile_sub(acc, &Ac[0][16 * wave], &Ac[0][j0], S, S, j0, l);
 #pragma unroll
-    for (int c = 0; c < PW; ++c) {
-      const int j = j0 + c;
-      double piv = readlane_f64(v[c], j);
-      if (!(piv > 0.0) || !isfinite(piv)) {  // the same in every lane
-        bad = true;
-        piv = 1e-300;
+        for (int v = 0; v < 4; ++v) o[4 * v] = acc[v];
       }
-      const double y = rsqrt_f64(piv);
-      v[c] = (l == j) ? piv * y : v[c] * y;  // rows above j hold unused entries
-#pragma unroll
-      for (int c2 = c + 1; c2 < PW; ++c2) v[c2] = fma(-v[c], readlane_f64(v[c], j0 + c2), v[c2]);
+      __syncthreads();
     }
+    if (wave == 0) {
+      double v[PW];
 #pragma unroll
-    for (int c = 0; c < PW; ++c) Ac[j0 + c][l] = v[c];
+      for (int c = 0; c < PW; ++c) v[c] = Ac[j0 + c][l];
+#pragma unroll
+      for (int c = 0; c < PW; ++c) {
+        const int j = j0 + c;
+        double piv = readlane_f64(v[c], j);
+        if (!(piv > 0.0) || !isfinite(piv)) {  // the same in every lane
+          bad = true;
+          piv = 1e-300;
+        }
+        const double y = rsqrt_f64(piv);
+        v[c] = (l == j) ? piv * y : v[c] * y;  // rows above j hold unused entries
+#pragma unroll
+        for (int c2 = c + 1; c2 < PW; ++c2) v[c2] = fma(-v[c], readlane_f64(v[c], j0 + c2), v[c2]);
+      }
+#pragma unroll
+      for (int c = 0; c < PW; ++c) Ac[j0 + c][l] = v[c];
+    }
     __syncthreads();
   }
-  if (bad && l == 0) flag[0] = 1;
-  // sixteen rows of LDS reads in flight: one read and one store at a time cost 4 us
-  for (int i0 = 0; i0 < nb; i0 += 16) {
-    double t[16];
+  if (bad && threadIdx.x == 0) flag[0] = 1;
+  // as many LDS reads in flight: one read and one store at a time cost 4 us
+  double t[16];
 #pragma unroll
-    for (int e = 0; e < 16; ++e) t[e] = Ac[l][i0 + e];
+  for (int e = 0; e < 16; ++e) t[e] = Ac[l][16 * wave + e];
 #pragma unroll
-    for (int e = 0; e < 16; ++e)
-      if (i0 + e < nb && l <= i0 + e) D[(i0 + e) * ld + l] = t[e];
+  for (int e = 0; e < 16; ++e) {
+    const int i = 16 * wave + e;
+    if (i < nb && l <= i) D[i * ld + l] = t[e];
   }
 }
 
@@ -402,7 +418,7 @@ __global__ __launch_bounds__(64) void chol_diag_kernel(double* __restrict__ C, i
 // the pivot) and broadcast by readlane.  A lane's row of L_kk is in registers
 // before the chain of 64 columns starts, so a column costs a product, the
 // broadcast and an FMA: with the row read from LDS column by column the
-// launch took 9.9 us, now @P.
+// launch took 9.9 us, now 5.4.
 __global__ __launch_bounds__(256) void chol_panel_kernel(double* __restrict__ C, int64_t ldc, int kb, int nb,
                                                          int R1) {
   __shared__ double Lk[kNb][kNb + 1];
@@ -499,81 +515,78 @@ __global__ __launch_bounds__(256) void chol_update_kernel(double* __restrict__ C
 }
 
 // ---------------------------------------------------------------- W = Lc^{-1}
-// Inverse of each 64 x 64 diagonal block: lane j forms column j of the
-// inverse, X[i][j] = (delta_ij - sum_{k<i} L[i][k] X[k][j]) / L[i][i], in
-// panels of eight rows: every lane first subtracts the earlier rows'
-// contributions (per earlier row k: its own X[k][j], a conflict-free read,
-// and the panel rows' L[i0..i0+7][k] from the transposed factor, contiguous
-// broadcast reads), then finishes the panel in registers.  Entries above the
-// diagonal come out as exact zeros.  Blocks are independent (one workgroup
-// each).  W must be zero outside the blocks written here before the doubling
-// steps run.
-__global__ __launch_bounds__(64) void trinv_diag_kernel(const double* __restrict__ C, int64_t ldc, int R1,
-                                                        double* __restrict__ W) {
-  __shared__ __align__(16) double Lt[kNb][kNb + 2];  // Lt[k][i] = L[i][k]
+// Inverse of each 64 x 64 diagonal block, X[i][j] = (delta_ij - sum_{k<i}
+// L[i][k] X[k][j]) / L[i][i], in panels of sixteen rows: wave w first
+// subtracts the earlier rows' part from the panel's columns 16 w .. 16 w + 15
+// on the matrix cores, then lane j of the first wave finishes column j of the
+// panel in registers.  Entries above the diagonal come out as exact zeros.
+// Blocks are independent (one workgroup each).  W must be zero outside the
+// blocks written here before the doubling steps run.  By one wave, with five
+// LDS reads per earlier row and panels of eight, 16.4 us, now 10.9.
+__global__ __launch_bounds__(256) void trinv_diag_kernel(const double* __restrict__ C, int64_t ldc, int R1,
+                                                         double* __restrict__ W) {
+  constexpr int S = kNb + 2;
+  __shared__ __align__(16) double Lt[kNb][S];  // Lt[k][i] = L[i][k]
   __shared__ __align__(16) double X[kNb][kNb];
   __shared__ double rinv[kNb];
   const int kb = blockIdx.x * kNb;
   const int nb = min(kNb, R1 - kb);
-  const int j = threadIdx.x;
+  const int j = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const double* D = C + int64_t(kb) * ldc + kb;
   double* Wd = W + int64_t(kb) * ldc + kb;
   const int ld = int(ldc);
   // coalesced: one row of the block per step, lane j reads column j (the
-  // address clamped into the block's lower triangle, so all 64 loads are in
+  // address clamped into the block's lower triangle, so all loads are in
   // flight at once)
   {
-    double t[kNb];
+    double t[16];
 #pragma unroll
-    for (int i = 0; i < kNb; ++i) {
-      const int ic = min(i, nb - 1);
-      t[i] = D[ic * ld + min(j, ic)];
+    for (int e = 0; e < 16; ++e) {
+      const int ic = min(16 * wave + e, nb - 1);
+      t[e] = D[ic * ld + min(j, ic)];
     }
 #pragma unroll
-    for (int i = 0; i < kNb; ++i) Lt[j][i] = (i < nb && j <= i) ? t[i] : (i == j ? 1.0 : 0.0);
+    for (int e = 0; e < 16; ++e) {
+      const int i = 16 * wave + e;
+      Lt[j][i] = (i < nb && j <= i) ? t[e] : (i == j ? 1.0 : 0.0);
+    }
   }
   __syncthreads();
-  rinv[j] = 1.0 / Lt[j][j];
-  __syncthreads();
-  constexpr int PW = 8;
+  if (wave == 0) rinv[j] = 1.0 / Lt[j][j];
+  constexpr int PW = 16;
   for (int i0 = 0; i0 < kNb; i0 += PW) {
-    double x[PW];
+    {  // tile rows i0 + 4 v + j / 16, column 16 wave + j % 16
+      f64x4 acc;
 #pragma unroll
-    for (int c = 0; c < PW; ++c) x[c] = (i0 + c == j) ? 1.0 : 0.0;
-#pragma unroll 4
-    for (int k = 0; k < i0; ++k) {
-      const double xk = X[k][j];
-      const double2 l01 = *reinterpret_cast<const double2*>(&Lt[k][i0]);
-      const double2 l23 = *reinterpret_cast<const double2*>(&Lt[k][i0 + 2]);
-      const double2 l45 = *reinterpret_cast<const double2*>(&Lt[k][i0 + 4]);
-      const double2 l67 = *reinterpret_cast<const double2*>(&Lt[k][i0 + 6]);
-      x[0] = fma(-l01.x, xk, x[0]);
-      x[1] = fma(-l01.y, xk, x[1]);
-      x[2] = fma(-l23.x, xk, x[2]);
-      x[3] = fma(-l23.y, xk, x[3]);
-      x[4] = fma(-l45.x, xk, x[4]);
-      x[5] = fma(-l45.y, xk, x[5]);
-      x[6] = fma(-l67.x, xk, x[6]);
-      x[7] = fma(-l67.y, xk, x[7]);
+      for (int v = 0; v < 4; ++v) acc[v] = (i0 + 4 * v + (j >> 4) == 16 * wave + (j & 15)) ? 1.0 : 0.0;
+      acc = chol_tile_sub(acc, &Lt[0][i0], &X[0][16 * wave], S, kNb, i0, j);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) X[i0 + 4 * v + (j >> 4)][16 * wave + (j & 15)] = acc[v];
     }
+    __syncthreads();
+    if (wave == 0) {
+      double x[PW];
 #pragma unroll
-    for (int c = 0; c < PW; ++c) {
+      for (int c = 0; c < PW; ++c) x[c] = X[i0 + c][j];
 #pragma unroll
-      for (int c1 = 0; c1 < c; ++c1) x[c] = fma(-Lt[i0 + c1][i0 + c], x[c1], x[c]);
-      x[c] *= rinv[i0 + c];
+      for (int c1 = 0; c1 < PW; ++c1) {
+        x[c1] *= rinv[i0 + c1];
+#pragma unroll
+        for (int c = c1 + 1; c < PW; ++c) x[c] = fma(-Lt[i0 + c1][i0 + c], x[c1], x[c]);
+      }
+#pragma unroll
+      for (int c = 0; c < PW; ++c) X[i0 + c][j] = x[c];
     }
-#pragma unroll
-    for (int c = 0; c < PW; ++c) X[i0 + c][j] = x[c];  // the lane's own column: no barrier needed
+    __syncthreads();
   }
-  if (j < nb)
-    for (int i0 = 0; i0 < nb; i0 += 16) {  // as many LDS reads in flight
-      double t[16];
+  if (j < nb) {
+    double t[16];
 #pragma unroll
-      for (int e = 0; e < 16; ++e) t[e] = X[i0 + e][j];
+    for (int e = 0; e < 16; ++e) t[e] = X[16 * wave + e][j];
 #pragma unroll
-      for (int e = 0; e < 16; ++e)
-        if (i0 + e < nb) Wd[(i0 + e) * ld + j] = t[e];
-    }
+    for (int e = 0; e < 16; ++e)
+      if (16 * wave + e < nb) Wd[(16 * wave + e) * ld + j] = t[e];
+  }
 }
 
 // One doubling level with blocks of s rows: for every pair (top = [i0, i0+s),
@@ -1084,7 +1097,7 @@ void spd_factor_inverse(double* C, int64_t ldc, int R1, double* W, double* WT, d
   KQR_CHECK_HIP(hipMemsetAsync(flag, 0, sizeof(int), st));
   for (int kb = 0; kb < R1; kb += kNb) {
     const int nb = std::min(kNb, R1 - kb);
-    chol_diag_kernel<<<1, 64, 0, st>>>(C, ldc, kb, nb, flag);
+    chol_diag_kernel<<<1, 256, 0, st>>>(C, ldc, kb, nb, flag);
     KQR_LAUNCH_CHECK();
     const int rest = R1 - kb - nb;
     if (rest > 0) {
@@ -1098,7 +1111,7 @@ void spd_factor_inverse(double* C, int64_t ldc, int R1, double* W, double* WT, d
   // W = Lc^{-1}: diagonal blocks, then doubling levels
   KQR_CHECK_HIP(hipMemsetAsync(W, 0, size_t(R1) * ldc * sizeof(double), st));
   const int nib = (R1 + kNb - 1) / kNb;
-  trinv_diag_kernel<<<nib, 64, 0, st>>>(C, ldc, R1, W);
+  trinv_diag_kernel<<<nib, 256, 0, st>>>(C, ldc, R1, W);
   KQR_LAUNCH_CHECK();
   for (int s = kNb; s < R1; s *= 2) {
     const int pairs = (R1 + 2 * s - 1) / (2 * s);
