@@ -474,15 +474,19 @@ int kqr_kernel_apply(const float* X, int64_t n, int64_t p, int kernel, double ga
       kapply_dense(km, n, n, nullptr, V, U, ldu, mode == KQR_APPLY_EXACT, st);
       return;
     }
-    // one allocation: per column a contiguous FP64 copy (when strided) and its FP32 rounding, and on the fly the
-    // norms or fixed-point coordinates and the partial sums
+    // one allocation (a free costs the host 16 us): per column a contiguous FP64 copy (when strided) and its FP32
+    // rounding, or all columns as the matrix cores read them; on the fly the norms or fixed-point coordinates; and the
+    // partial sums
     auto up = [](size_t b) { return (b + 255) / 256 * 256; };
     const bool otf = !K && kernel != KQR_LINEAR;
-    const size_t vec_bytes = up(size_t(n) * sizeof(double)) + up(size_t(n) * sizeof(float));
+    const bool kv = K && m > 1 && mode == KQR_APPLY_FAST;  // all columns, padded to 16 FP32 per row
+    const size_t vec_bytes = kv ? up(size_t(n) * 16 * sizeof(float))
+                                : up(size_t(n) * sizeof(double)) + up(size_t(n) * sizeof(float));
     const size_t point_bytes =
         !otf ? 0 : up(kernel == KQR_LAPLACIAN ? quantized_words(n, int(p)) * sizeof(uint32_t) : size_t(n) * sizeof(float));
     size_t sum_doubles = 0;
-    if (!K && !otf) sum_doubles = lin_scratch_doubles(int(p));
+    if (kv) sum_doubles = kv_scratch_doubles(n);
+    else if (!K && !otf) sum_doubles = lin_scratch_doubles(int(p));
     else if (otf && kernel == KQR_LAPLACIAN) sum_doubles = otf_sym_scratch_doubles(n);
     else if (otf) sum_doubles = kapply_otf_scratch_doubles(n, n, int(p), ks, true);
     char* tmp = nullptr;
@@ -526,16 +530,10 @@ int kqr_kernel_apply(const float* X, int64_t n, int64_t p, int kernel, double ga
       KQR_CHECK_HIP(hipFreeAsync(cols, st));
       m = 0;  // done
     }
-    if (K && m > 1 && mode == KQR_APPLY_FAST) {  // all columns in one pass over K on the matrix cores
-      float* V16 = nullptr;
-      double* part = nullptr;
-      KQR_CHECK_HIP(hipMallocAsync(reinterpret_cast<void**>(&V16), size_t(n) * 16 * sizeof(float), st));
-      KQR_CHECK_HIP(
-          hipMallocAsync(reinterpret_cast<void**>(&part), kv_scratch_doubles(n) * sizeof(double), st));
+    if (kv) {  // all columns in one pass over K on the matrix cores
+      float* V16 = reinterpret_cast<float*>(tmp);
       kv_gather_strided(V, ldv, int(m), n, n, V16, st);
-      kapply_kv(km, n, V16, int(m), U, ldu, part, st);
-      KQR_CHECK_HIP(hipFreeAsync(part, st));
-      KQR_CHECK_HIP(hipFreeAsync(V16, st));
+      kapply_kv(km, n, V16, int(m), U, ldu, sums, st);
       m = 0;  // done
     }
     for (int64_t j = 0; j < m; ++j) {
@@ -618,11 +616,16 @@ int kqr_kernel_apply_packed(const void* K, int k_dtype, int64_t n, const double*
     if (mode == KQR_APPLY_EXACT) {
       kapply_packed(km, n, nullptr, v, u, 1, true, st);
     } else {
-      float* v32 = nullptr;
-      KQR_CHECK_HIP(hipMallocAsync(reinterpret_cast<void**>(&v32), size_t(n) * sizeof(float), st));
+      // v in FP32 and the partial sums in one allocation
+      const PackedShape sh = default_packed_shape(k_dtype, false);
+      const size_t v_bytes = (size_t(n) * sizeof(float) + 255) / 256 * 256;
+      char* tmp = nullptr;
+      KQR_CHECK_HIP(hipMallocAsync(reinterpret_cast<void**>(&tmp),
+                                   v_bytes + packed_shape_scratch_doubles(n, sh) * sizeof(double), st));
+      float* v32 = reinterpret_cast<float*>(tmp);
       to_f32(v, n, 1, 1, v32, 1, st);
-      kapply_packed(km, n, v32, nullptr, u, 1, false, st);
-      KQR_CHECK_HIP(hipFreeAsync(v32, st));
+      kapply_packed(km, n, v32, nullptr, u, 1, false, st, &sh, reinterpret_cast<double*>(tmp + v_bytes));
+      KQR_CHECK_HIP(hipFreeAsync(tmp, st));
     }
   });
 }

@@ -429,7 +429,7 @@ constexpr int kOtfTile = 64;
 // Column slices of an on-the-fly launch: about 8192 workgroups in all (many
 // rounds of the blocks the chip holds at once, so the last round is a small
 // tail), each slice at least 1024 columns.  Every slice writes one partial
-// per row, added in slice order by otf_reduce_kernel.
+// per row, added in a fixed order by otf_reduce_kernel.
 std::atomic<int64_t> g_otf_wgs{8192};  // target workgroups of a sliced launch (kqr_set_otf_shape)
 
 static int64_t otf_slices(int64_t rblk, int64_t nc) {
