@@ -274,6 +274,7 @@ int kqr_kernel_apply_packed(const void* K, int k_dtype, int64_t n, const double*
  *         FP32 K and m <= 4 forms all columns in FP64 (vectors, products, sums)
  *         from one pass over K; every other EXACT case runs column by column in
  *         FP64 (so EXACT never drops to FP32 products).
+ *  U may be V itself (ldu = ldv), and one column may overlap V in any way.
  *  Needs 1 <= m <= 16.  Asynchronous on `stream`; allocates its device
  *  workspace on `stream` (stream-ordered) and frees it before returning. */
 int kqr_kernel_apply(const float* X, int64_t n, int64_t p, int kernel, double gamma,

@@ -469,12 +469,15 @@ int kqr_kernel_apply(const float* X, int64_t n, int64_t p, int kernel, double ga
     hipStream_t st = static_cast<hipStream_t>(stream);
     const KernelSpec ks{kernel, gamma};
     const KMat km{K, k_dtype, ldk};
-    const bool strided = ldv != 1 || (reinterpret_cast<uintptr_t>(V) & 15) != 0;  // kernels read 16-byte vectors
-    if (K && m == 1 && !strided) {  // v is rounded as it is read: no FP32 copy, no memory for one
+    // V is read where it lies when the kernels can (they read 16-byte vectors), except by a stored K's kernel that
+    // writes U while other workgroups still read V: there an overlapping V is copied first
+    const bool copied = ldv != 1 || (reinterpret_cast<uintptr_t>(V) & 15) != 0 ||
+                        (K && ranges_overlap(V, size_t(n - 1) * ldv + 1, U, size_t(n - 1) * ldu + 1));
+    if (K && m == 1 && !copied) {  // v is rounded as it is read: no FP32 copy, no memory for one
       kapply_dense(km, n, n, nullptr, V, U, ldu, mode == KQR_APPLY_EXACT, st);
       return;
     }
-    // one allocation (a free costs the host 16 us): per column a contiguous FP64 copy (when strided) and its FP32
+    // one allocation (a free costs the host 16 us): per column a contiguous FP64 copy (when copied) and its FP32
     // rounding, or all columns as the matrix cores read them; on the fly the norms or fixed-point coordinates; and the
     // partial sums
     auto up = [](size_t b) { return (b + 255) / 256 * 256; };
@@ -538,7 +541,7 @@ int kqr_kernel_apply(const float* X, int64_t n, int64_t p, int kernel, double ga
     }
     for (int64_t j = 0; j < m; ++j) {
       const double* col = V + j;
-      if (ldv != 1 || (reinterpret_cast<uintptr_t>(col) & 15) != 0) {  // kernels read 16-byte vectors
+      if (copied) {  // (always with several columns: ldv is at least two then)
         KQR_CHECK_HIP(hipMemcpy2DAsync(v64, sizeof(double), V + j, size_t(ldv) * sizeof(double), sizeof(double),
                                        size_t(n), hipMemcpyDeviceToDevice, st));
         col = v64;

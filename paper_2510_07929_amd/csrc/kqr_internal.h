@@ -119,6 +119,12 @@ void row_sqnorms(const float* X, int64_t n, int p, float* sqn, hipStream_t st);
 void row_sqnorms2(const float* Xa, int64_t na, float* qa, const float* Xb, int64_t nb, float* qb, int p,
                   hipStream_t st);
 
+// whether the na doubles at a and the nb at b share memory
+inline bool ranges_overlap(const double* a, size_t na, const double* b, size_t nb) {
+  const uintptr_t ia = reinterpret_cast<uintptr_t>(a), ib = reinterpret_cast<uintptr_t>(b);
+  return ia < ib + nb * sizeof(double) && ib < ia + na * sizeof(double);
+}
+
 // u = K v (materialised, rows [0, nrows), cols [0, ncols)).  exact: v64 + FP64; else v32.
 // scratch (scratch_doubles long, or null) holds the partial sums when it is
 // large enough (kapply_scratch_doubles); otherwise they are allocated on st.
