@@ -286,9 +286,10 @@ int kqr_kernel_apply(const float* X, int64_t n, int64_t p, int kernel, double ga
  * allocates nothing.  For callers that cannot allocate device memory: code
  * under HIP graph capture, serving loops, harnesses that forbid allocation.
  *  K      device n x ldk, type k_dtype (ldk >= n, a multiple of 8, 16-byte aligned).
- *  v      device n FP64, element i at v[i * incv];  u device n FP64 at u[i * incu].
- *  Its scratch (the FP32 copy of v, an aligned FP64 copy when incv != 1, the
- *  partial sums of the column segments) lives in one fixed device array of
+ *  v      device n FP64, element i at v[i * incv];  u device n FP64 at u[i * incu]
+ *         (u may overlap v).
+ *  Its scratch (the FP32 copy of v, an aligned FP64 copy when incv != 1 or u
+ *  overlaps v, the partial sums of the column segments) lives in one fixed device array of
  *  64 MiB per device, held from the first call on that device until the
  *  process ends; n needs 20 n bytes of it plus alignment (n up to about
  *  3.3 million), else KQR_EINVAL.  The launch shape is kqr_kernel_apply's, with

@@ -1,6 +1,6 @@
 // K-apply that allocates nothing: the materialised single-vector K v of
 // kqr_kernel_apply with its scratch (the FP32 copy of v, an aligned FP64 copy
-// when v is strided, the column-segment partial sums) in a fixed device array
+// when v is strided or u overlaps it, the column-segment partial sums) in a fixed device array
 // instead of stream-ordered allocations.  For callers that cannot allocate
 // (code under HIP graph capture, serving loops, harnesses that forbid it).
 //
@@ -67,7 +67,9 @@ void kapply_static(const KMat& km, int64_t n, const double* v, int64_t incv, dou
   s.segs = int(std::max<int64_t>(1, std::min<int64_t>(s.segs, int64_t(part_doubles / size_t(n)))));
   if (exact) {
     const double* col = v;
-    if (incv != 1 || (reinterpret_cast<uintptr_t>(v) & 15) != 0) {  // the kernel reads 16-byte pieces of v
+    // the kernel reads 16-byte pieces of v, and may write u while other workgroups still read v
+    if (incv != 1 || (reinterpret_cast<uintptr_t>(v) & 15) != 0 ||
+        ranges_overlap(v, size_t(n - 1) * incv + 1, u, size_t(n - 1) * incu + 1)) {
       KQR_CHECK_HIP(hipMemcpy2DAsync(v64, sizeof(double), v, size_t(incv) * sizeof(double), sizeof(double),
                                      size_t(n), hipMemcpyDeviceToDevice, st));
       col = v64;

@@ -43,10 +43,11 @@ def test_apply_of_one_column_at_rule_edges(n, kd):
         assert torch.equal(kqr.kqr_kernel_apply(w[1:], K=K, mode=mode), u)
 
 
+@pytest.mark.parametrize("static", [False, True])
 @pytest.mark.parametrize("mode", [kqr.KQR_APPLY_FAST, kqr.KQR_APPLY_EXACT])
 @pytest.mark.parametrize("kd", ["fp32", "bf16"])
 @pytest.mark.parametrize("n", [1, 130, 6251, 12501, 16384])
-def test_apply_of_one_column_into_its_own_vector(n, kd, mode):
+def test_apply_of_one_column_into_its_own_vector(n, kd, mode, static):
     """K v written over v, over part of v from either side, and beside v: the bits of a call with its own output."""
     dev = torch.device("cuda:0")
     g = torch.Generator(device=dev)
@@ -54,15 +55,21 @@ def test_apply_of_one_column_into_its_own_vector(n, kd, mode):
     X = torch.randn((n, 4), generator=g, device=dev)
     K = kqr.kqr_kernel_build(X, "rbf", 0.5, kd)
     v = torch.randn(n, generator=g, device=dev, dtype=torch.float64)
-    want = kqr.kqr_kernel_apply(v, K=K, mode=mode)
-    say("apply in place", kd, n, mode)
+
+    def apply(x, out=None):
+        if static:
+            return kqr.kqr_kernel_apply_static(x, K, mode, u=out)
+        return kqr.kqr_kernel_apply(x, K=K, mode=mode, U=out)
+
+    want = apply(v)
+    say("apply in place", kd, n, mode, static)
     at = 2 * n  # (even: v is 16-byte aligned)
     for off in (0, 1, -1, 64, -64, n - 1, 1 - n, n, -n):
         if abs(off) > n:
             continue
         w = torch.full((5 * n,), float("nan"), device=dev, dtype=torch.float64)
         w[at:at + n] = v
-        u = kqr.kqr_kernel_apply(w[at:at + n], K=K, mode=mode, U=w[at + off:at + off + n])
+        u = apply(w[at:at + n], w[at + off:at + off + n])
         assert torch.equal(u, want), off
         if abs(off) == n:
             assert torch.equal(w[at:at + n], v)
