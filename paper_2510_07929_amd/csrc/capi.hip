@@ -38,6 +38,25 @@ void DevBuf::alloc(size_t b) {
   bytes = b;
 }
 
+bool StreamBuf::try_alloc(size_t b) {
+  release();
+  const hipError_t e = hipMallocAsync(&ptr_, b, st_);
+  if (e == hipSuccess) return true;
+  ptr_ = nullptr;
+  (void)hipGetLastError();
+  if (e != hipErrorOutOfMemory) fail(KQR_EHIP, "hipMallocAsync(%zu bytes): %s", b, hipGetErrorString(e));
+  return false;
+}
+
+void StreamBuf::alloc(size_t b) {
+  if (!try_alloc(b)) fail(KQR_ENOMEM, "hipMallocAsync(%zu bytes): out of memory", b);
+}
+
+void StreamBuf::release() {
+  if (ptr_) (void)hipFreeAsync(ptr_, st_);
+  ptr_ = nullptr;
+}
+
 // hipFree waits for the whole device; inside a DeferFrees scope the frees
 // wait for the scope's end instead, so a batch of fits running side by side
 // does not drain the GPU whenever one of them releases a buffer.
@@ -442,11 +461,9 @@ int kqr_kernel_build(const float* X, int64_t n, int64_t p, int kernel, double ga
     check_kmat(K, k_dtype, ldk, n);
     ensure_device();
     hipStream_t st = static_cast<hipStream_t>(stream);
-    float* sqn = nullptr;
-    KQR_CHECK_HIP(hipMallocAsync(reinterpret_cast<void**>(&sqn), size_t(n) * sizeof(float), st));
-    row_sqnorms(X, n, int(p), sqn, st);
-    kbuild(X, sqn, n, int(p), KernelSpec{kernel, gamma}, k_dtype, K, ldk, st);
-    KQR_CHECK_HIP(hipFreeAsync(sqn, st));
+    const StreamBuf sqn(size_t(n) * sizeof(float), st);
+    row_sqnorms(X, n, int(p), sqn.as<float>(), st);
+    kbuild(X, sqn.as<float>(), n, int(p), KernelSpec{kernel, gamma}, k_dtype, K, ldk, st);
   });
 }
 
@@ -481,40 +498,59 @@ int kqr_kernel_apply(const float* X, int64_t n, int64_t p, int kernel, double ga
     // rounding, or all columns as the matrix cores read them; on the fly the norms or fixed-point coordinates; and the
     // partial sums
     auto up = [](size_t b) { return (b + 255) / 256 * 256; };
-    const bool otf = !K && kernel != KQR_LINEAR;
+    const bool otf = !K && kernel != KQR_LINEAR, lap = otf && kernel == KQR_LAPLACIAN;
     const bool kv = K && m > 1 && mode == KQR_APPLY_FAST;  // all columns, padded to 16 FP32 per row
     const size_t vec_bytes = kv ? up(size_t(n) * 16 * sizeof(float))
                                 : up(size_t(n) * sizeof(double)) + up(size_t(n) * sizeof(float));
     const size_t point_bytes =
-        !otf ? 0 : up(kernel == KQR_LAPLACIAN ? quantized_words(n, int(p)) * sizeof(uint32_t) : size_t(n) * sizeof(float));
+        !otf ? 0 : up(lap ? quantized_words(n, int(p)) * sizeof(uint32_t) : size_t(n) * sizeof(float));
     size_t sum_doubles = 0;
     if (kv) sum_doubles = kv_scratch_doubles(n);
     else if (!K && !otf) sum_doubles = lin_scratch_doubles(int(p));
-    else if (otf && kernel == KQR_LAPLACIAN) sum_doubles = otf_sym_scratch_doubles(n);
+    else if (lap) sum_doubles = otf_sym_scratch_doubles(n);
     else if (otf) sum_doubles = kapply_otf_scratch_doubles(n, n, int(p), ks, true);
-    char* tmp = nullptr;
-    KQR_CHECK_HIP(hipMallocAsync(reinterpret_cast<void**>(&tmp), vec_bytes + point_bytes + sum_doubles * sizeof(double),
-                                 st));
-    double* v64 = reinterpret_cast<double*>(tmp);
-    float* v32 = reinterpret_cast<float*>(tmp + up(size_t(n) * sizeof(double)));
-    float* sqn = reinterpret_cast<float*>(tmp + vec_bytes);
-    uint32_t* xq = reinterpret_cast<uint32_t*>(tmp + vec_bytes);
-    double* sums = reinterpret_cast<double*>(tmp + vec_bytes + point_bytes);
+    StreamBuf tmp(st), sum_buf(st);
+    auto ptr = [&](size_t off) { return tmp.as<char>() + off; };
+    double* sums = nullptr;
     int shift = -1;
-    if (otf && kernel == KQR_LAPLACIAN)  // exact integer L1 distances of fixed-point X, as in the fits
-      shift = quantize_columns(X, n, int(p), xq, st);
-    else if (otf)
-      row_sqnorms(X, n, int(p), sqn, st);
+    if (lap) {
+      // Exact integer L1 distances of fixed-point X, as in the fits, where its ranges allow them (shift >= 20); which
+      // sums are needed is known only then.  Those of the fixed-point form, about n^2 / 32 bytes, are taken with the
+      // rest where memory allows: the pool gives back what is free when the ranges are waited for, so taken afterwards
+      // they are mapped anew in every call (n = 60,000: 2.24 ms, 2.52 that way).  Where memory is short, or the float
+      // form with its O(n) sums runs, the sums are taken (again) by what is needed, a surplus below 64 MiB kept.
+      if (!tmp.try_alloc(vec_bytes + point_bytes + sum_doubles * sizeof(double))) {
+        sum_doubles = 0;
+        tmp.alloc(vec_bytes + point_bytes);
+      }
+      shift = quantize_columns(X, n, int(p), reinterpret_cast<uint32_t*>(ptr(vec_bytes)), st);
+      const size_t need = shift >= 20 ? otf_sym_scratch_doubles(n) : kapply_otf_scratch_doubles(n, n, int(p), ks, true);
+      if (shift < 20 && sum_doubles * sizeof(double) > need * sizeof(double) + (size_t(64) << 20)) {
+        sum_doubles = 0;
+        tmp.alloc(vec_bytes + point_bytes);  // (the float form reads X itself)
+      }
+      sums = reinterpret_cast<double*>(ptr(vec_bytes + point_bytes));
+      if (sum_doubles < need) {
+        sum_buf.alloc(need * sizeof(double));
+        sums = sum_buf.as<double>();
+        sum_doubles = need;
+      }
+    } else {
+      tmp.alloc(vec_bytes + point_bytes + sum_doubles * sizeof(double));
+      sums = reinterpret_cast<double*>(ptr(vec_bytes + point_bytes));
+    }
+    double* v64 = reinterpret_cast<double*>(ptr(0));
+    float* v32 = reinterpret_cast<float*>(ptr(up(size_t(n) * sizeof(double))));
+    float* sqn = reinterpret_cast<float*>(ptr(vec_bytes));
+    const uint32_t* xq = reinterpret_cast<const uint32_t*>(ptr(vec_bytes));
+    if (otf && !lap) row_sqnorms(X, n, int(p), sqn, st);
     if (K && m > 1 && mode == KQR_APPLY_EXACT && k_dtype == KQR_FP32 && m <= kKvMaxExact) {
       // exact columns (FP64 vectors, products and sums) from one pass over K
-      double* cols = nullptr;
-      double* part = nullptr;
-      KQR_CHECK_HIP(hipMallocAsync(reinterpret_cast<void**>(&cols), size_t(2 * m) * size_t(n) * sizeof(double), st));
-      KQR_CHECK_HIP(
-          hipMallocAsync(reinterpret_cast<void**>(&part), kv_scratch_doubles(n) * sizeof(double), st));
-      float* V16 = nullptr;  // no fast columns: zeros for the matrix-core half of the pass
-      KQR_CHECK_HIP(hipMallocAsync(reinterpret_cast<void**>(&V16), size_t(n) * 16 * sizeof(float), st));
-      fill(n * 8, 0.0, reinterpret_cast<double*>(V16), st);  // 16 FP32 zeros per row, by a kernel (capturable)
+      const StreamBuf col_buf(size_t(2 * m) * size_t(n) * sizeof(double), st);
+      const StreamBuf part(kv_scratch_doubles(n) * sizeof(double), st);
+      const StreamBuf V16(size_t(n) * 16 * sizeof(float), st);  // no fast columns: zeros for the matrix-core half of the pass
+      double* cols = col_buf.as<double>();
+      fill(n * 8, 0.0, V16.as<double>(), st);  // 16 FP32 zeros per row, by a kernel (capturable)
       SrcTable16 xs{};
       DstTable16 xd{};
       for (int64_t j = 0; j < m; ++j) {
@@ -524,17 +560,14 @@ int kqr_kernel_apply(const float* X, int64_t n, int64_t p, int kernel, double ga
         xs.p[j] = cj;
         xd.p[j] = cols + size_t(m + j) * size_t(n);
       }
-      kapply_kv_mixed(km, n, V16, 0, nullptr, 16, xs, int(m), xd, part, st);
+      kapply_kv_mixed(km, n, V16.as<float>(), 0, nullptr, 16, xs, int(m), xd, part.as<double>(), st);
       for (int64_t j = 0; j < m; ++j)
         KQR_CHECK_HIP(hipMemcpy2DAsync(U + j, size_t(ldu) * sizeof(double), xd.p[j], sizeof(double), sizeof(double),
                                        size_t(n), hipMemcpyDeviceToDevice, st));
-      KQR_CHECK_HIP(hipFreeAsync(V16, st));
-      KQR_CHECK_HIP(hipFreeAsync(part, st));
-      KQR_CHECK_HIP(hipFreeAsync(cols, st));
       m = 0;  // done
     }
     if (kv) {  // all columns in one pass over K on the matrix cores
-      float* V16 = reinterpret_cast<float*>(tmp);
+      float* V16 = tmp.as<float>();
       kv_gather_strided(V, ldv, int(m), n, n, V16, st);
       kapply_kv(km, n, V16, int(m), U, ldu, sums, st);
       m = 0;  // done
@@ -562,7 +595,6 @@ int kqr_kernel_apply(const float* X, int64_t n, int64_t p, int kernel, double ga
                    sum_doubles);
       }
     }
-    KQR_CHECK_HIP(hipFreeAsync(tmp, st));
   });
 }
 
@@ -597,11 +629,9 @@ int kqr_kernel_build_packed(const float* X, int64_t n, int64_t p, int kernel, do
     check_kernel(kernel, gamma, false);
     ensure_device();
     hipStream_t st = static_cast<hipStream_t>(stream);
-    float* sqn = nullptr;
-    KQR_CHECK_HIP(hipMallocAsync(reinterpret_cast<void**>(&sqn), size_t(n) * sizeof(float), st));
-    row_sqnorms(X, n, int(p), sqn, st);
-    kbuild_packed(X, sqn, n, int(p), KernelSpec{kernel, gamma}, k_dtype, K, st);
-    KQR_CHECK_HIP(hipFreeAsync(sqn, st));
+    const StreamBuf sqn(size_t(n) * sizeof(float), st);
+    row_sqnorms(X, n, int(p), sqn.as<float>(), st);
+    kbuild_packed(X, sqn.as<float>(), n, int(p), KernelSpec{kernel, gamma}, k_dtype, K, st);
   });
 }
 
@@ -622,13 +652,10 @@ int kqr_kernel_apply_packed(const void* K, int k_dtype, int64_t n, const double*
       // v in FP32 and the partial sums in one allocation
       const PackedShape sh = default_packed_shape(k_dtype, false);
       const size_t v_bytes = (size_t(n) * sizeof(float) + 255) / 256 * 256;
-      char* tmp = nullptr;
-      KQR_CHECK_HIP(hipMallocAsync(reinterpret_cast<void**>(&tmp),
-                                   v_bytes + packed_shape_scratch_doubles(n, sh) * sizeof(double), st));
-      float* v32 = reinterpret_cast<float*>(tmp);
+      const StreamBuf tmp(v_bytes + packed_shape_scratch_doubles(n, sh) * sizeof(double), st);
+      float* v32 = tmp.as<float>();
       to_f32(v, n, 1, 1, v32, 1, st);
-      kapply_packed(km, n, v32, nullptr, u, 1, false, st, &sh, reinterpret_cast<double*>(tmp + v_bytes));
-      KQR_CHECK_HIP(hipFreeAsync(tmp, st));
+      kapply_packed(km, n, v32, nullptr, u, 1, false, st, &sh, reinterpret_cast<double*>(tmp.as<char>() + v_bytes));
     }
   });
 }
@@ -714,21 +741,18 @@ int kqr_predict(const float* Xtrain, int64_t n, int64_t p, const double* alpha, 
     ensure_device();
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (kernel == KQR_LINEAR) {  // f = beta + Xnew (Xtrain^T alpha) / lambda
-      double* scr = nullptr;
-      KQR_CHECK_HIP(hipMallocAsync(reinterpret_cast<void**>(&scr), lin_scratch_doubles(int(p)) * sizeof(double), st));
-      lin_predict(Xtrain, n, int(p), alpha, Xnew, m, 1.0 / lambda, beta, f, scr, st);
-      KQR_CHECK_HIP(hipFreeAsync(scr, st));
+      const StreamBuf scr(lin_scratch_doubles(int(p)) * sizeof(double), st);
+      lin_predict(Xtrain, n, int(p), alpha, Xnew, m, 1.0 / lambda, beta, f, scr.as<double>(), st);
       return;
     }
     const KernelSpec ks{kernel, gamma};
     const size_t sum_doubles = kapply_otf_scratch_doubles(m, n, int(p), ks, false);
     const size_t sq_bytes = (size_t(n + m) * sizeof(float) + 255) / 256 * 256;
-    float* sq = nullptr;
-    KQR_CHECK_HIP(hipMallocAsync(reinterpret_cast<void**>(&sq), sq_bytes + sum_doubles * sizeof(double), st));
+    const StreamBuf buf(sq_bytes + sum_doubles * sizeof(double), st);
+    float* sq = buf.as<float>();
     if (kernel != KQR_LAPLACIAN) row_sqnorms2(Xtrain, n, sq, Xnew, m, sq + n, int(p), st);
     kapply_otf(Xnew, sq + n, m, Xtrain, sq, n, int(p), ks, alpha, f, 1, 1.0 / lambda, beta, st, true,
-               reinterpret_cast<double*>(reinterpret_cast<char*>(sq) + sq_bytes), sum_doubles);
-    KQR_CHECK_HIP(hipFreeAsync(sq, st));
+               reinterpret_cast<double*>(buf.as<char>() + sq_bytes), sum_doubles);
   });
 }
 

@@ -52,6 +52,25 @@ struct DevBuf {
   template <typename T> T* as() const { return static_cast<T*>(ptr); }
 };
 
+// Buffer in stream order: taken and given back on st, also when the call that
+// owns it fails in between.
+class StreamBuf {
+ public:
+  explicit StreamBuf(hipStream_t st) : st_(st) {}
+  StreamBuf(size_t b, hipStream_t st) : st_(st) { alloc(b); }
+  ~StreamBuf() { release(); }
+  StreamBuf(const StreamBuf&) = delete;
+  StreamBuf& operator=(const StreamBuf&) = delete;
+  bool try_alloc(size_t b);  // false when memory is short
+  void alloc(size_t b);
+  void release();
+  template <typename T> T* as() const { return static_cast<T*>(ptr_); }
+
+ private:
+  void* ptr_ = nullptr;
+  hipStream_t st_;
+};
+
 // While alive on a thread, DevBuf releases on that thread are collected and
 // freed when the scope ends (hipFree synchronises the device).
 class DeferFrees {
