@@ -209,11 +209,22 @@ def padded_ld(n: int) -> int:
     return (int(n) + 63) // 64 * 64
 
 
-def _pivot_uniforms(uniforms):
-    """Host copy for kqr_options.pivot_uniforms, which the library reads up to the rank it
-    arrives at (at most 1024): fewer values start again from the first."""
+def _seed_uniforms(seed, first, count):
+    """Values first .. count - 1 of the uniforms the library draws from kqr_options.seed: SplitMix64
+    (Steele, Lea, Flood 2014) on seed + step, top 53 bits."""
+    z = np.uint64(int(seed)) + np.uint64(0x9E3779B97F4A7C15) * np.arange(first + 1, count + 1, dtype=np.uint64)
+    z = (z ^ (z >> np.uint64(30))) * np.uint64(0xBF58476D1CE4E5B9)
+    z = (z ^ (z >> np.uint64(27))) * np.uint64(0x94D049BB133111EB)
+    return ((z ^ (z >> np.uint64(31))) >> np.uint64(11)).astype(np.float64) * 2.0 ** -53
+
+
+def _pivot_uniforms(uniforms, o, kernel):
+    """Host copy for kqr_options.pivot_uniforms.  The library reads one value per pivot up to the rank it
+    arrives at (at most 1024); pivots past the caller's values are drawn as with none given, from o.seed."""
     u = np.ascontiguousarray(np.asarray(uniforms, dtype=np.float64)).reshape(-1)
-    return np.resize(u, 1024) if 0 < u.size < 1024 else u
+    if u.size == 0 and o.rank >= 0 and _kernel_id(kernel) != KQR_LINEAR:
+        raise ValueError("need at least one pivot uniform")
+    return u if u.size >= 1024 else np.concatenate([u, _seed_uniforms(o.seed, u.size, 1024)])
 
 
 # ----------------------------------------------------------------------- entry points
@@ -544,7 +555,7 @@ def kqr_fit(X, y, tau, lam, kernel="rbf", gamma=1.0, options: KqrOptions | None 
         o.v_out, o.z_out = vz[0].data_ptr(), vz[1].data_ptr()
     keep = None
     if uniforms is not None:
-        keep = _pivot_uniforms(uniforms)
+        keep = _pivot_uniforms(uniforms, o, kernel)
         o.pivot_uniforms = keep.ctypes.data_as(C.POINTER(C.c_double))
     tbuf = None
     if trace > 0:
@@ -571,13 +582,13 @@ def kqr_fit(X, y, tau, lam, kernel="rbf", gamma=1.0, options: KqrOptions | None 
     return alpha, float(beta.value), out, st
 
 
-def _options(options, uniforms, overrides):
+def _options(options, uniforms, overrides, kernel):
     o = options if options is not None else kqr_default_options()
     for k, v in overrides.items():
         setattr(o, k, v)
     keep = None
     if uniforms is not None:
-        keep = _pivot_uniforms(uniforms)
+        keep = _pivot_uniforms(uniforms, o, kernel)
         o.pivot_uniforms = keep.ctypes.data_as(C.POINTER(C.c_double))
     return o, keep
 
@@ -589,7 +600,7 @@ def kqr_fit_multi_tau(X, y, taus, lam, kernel="rbf", gamma=1.0, options: KqrOpti
     n, p = X.shape
     taus = np.ascontiguousarray(np.asarray(taus, dtype=np.float64))
     m = int(taus.size)
-    o, keep = _options(options, uniforms, overrides)
+    o, keep = _options(options, uniforms, overrides, kernel)
     alpha = torch.empty((m, n), dtype=torch.float64, device=X.device)
     beta = np.zeros(m)
     info = (KqrInfo * m)()
@@ -609,7 +620,7 @@ def kqr_fit_path(X, y, tau, lams, kernel="rbf", gamma=1.0, options: KqrOptions |
     n, p = X.shape
     lams = np.ascontiguousarray(np.asarray(lams, dtype=np.float64))
     m = int(lams.size)
-    o, keep = _options(options, uniforms, overrides)
+    o, keep = _options(options, uniforms, overrides, kernel)
     alpha = torch.empty((m, n), dtype=torch.float64, device=X.device)
     beta = np.zeros(m)
     info = (KqrInfo * m)()
@@ -636,7 +647,7 @@ def kqr_fit_batch(Xs, ys, taus, lams, gammas, kernel="rbf", options: KqrOptions 
     taus = np.ascontiguousarray(np.asarray(taus, dtype=np.float64))
     lams = np.ascontiguousarray(np.asarray(lams, dtype=np.float64))
     gammas = np.ascontiguousarray(np.asarray(gammas, dtype=np.float64))
-    o, keep = _options(options, uniforms, overrides)
+    o, keep = _options(options, uniforms, overrides, kernel)
     beta = np.zeros(k)
     info = (KqrInfo * k)()
     status = np.zeros(k, dtype=np.int32)
@@ -659,7 +670,7 @@ def kqr_fit_grad(X, y, tau, lam, kernel, gamma, Xval, yval, options: KqrOptions 
     nv = Xval.shape[0]
     if Xval.shape[1] != p:
         raise ValueError("Xval must have the columns of X")
-    o, keep = _options(options, uniforms, overrides)
+    o, keep = _options(options, uniforms, overrides, kernel)
     alpha = torch.empty(n, dtype=torch.float64, device=X.device)
     beta = C.c_double(0.0)
     loss = C.c_double(0.0)

@@ -198,3 +198,36 @@ def test_traffic_summaries_are_tied_to_kernel_sources():
         val, recorded = got
         assert recorded == dig, f"{name} was measured on another version of the {layout} K-apply"
         assert 1e9 < val < 2e10
+
+
+def _splitmix(seed, step):
+    m = (1 << 64) - 1
+    z = (seed + 0x9E3779B97F4A7C15 * (step + 1)) & m
+    z = ((z ^ (z >> 30)) * 0xBF58476D1CE4E5B9) & m
+    z = ((z ^ (z >> 27)) * 0x94D049BB133111EB) & m
+    return ((z ^ (z >> 31)) >> 11) / 2.0 ** 53
+
+
+@pytest.mark.parametrize("seed", [0, 7, 2 ** 64 - 1])
+@pytest.mark.parametrize("size", [1, 64, 1023])
+def test_short_pivot_uniforms_go_on_with_the_seeds_own(size, seed):
+    """A fit reads up to 1024 uniforms: past the caller's come fresh draws, the ones the library makes from the
+    seed, never the caller's again."""
+    o = kqr.kqr_default_options(seed=seed)
+    u = np.random.default_rng(size).uniform(size=size)
+    full = kqr._pivot_uniforms(u, o, "rbf")
+    assert full.size == 1024 and np.array_equal(full[:size], u)
+    assert full[size:].tolist() == [_splitmix(seed, i) for i in range(size, 1024)]
+    assert ((full >= 0.0) & (full < 1.0)).all()
+
+
+def test_pivot_uniforms_at_their_limits():
+    o = kqr.kqr_default_options()
+    u = np.random.default_rng(1).uniform(size=1025)
+    assert np.array_equal(kqr._pivot_uniforms(u, o, "rbf"), u)
+    assert np.array_equal(kqr._pivot_uniforms(u[:1024].reshape(32, 32), o, "rbf"), u[:1024])
+    with pytest.raises(ValueError):
+        kqr._pivot_uniforms([], o, "rbf")
+    # no pivot is drawn without a preconditioner, and for the linear kernel
+    assert kqr._pivot_uniforms([], o, "linear").size == 1024
+    assert kqr._pivot_uniforms([], kqr.kqr_default_options(rank=-1), "rbf").size == 1024
