@@ -253,7 +253,9 @@ int kqr_set_otf_symmetric_limit(int64_t bytes);
  * (2 tiles below 64 tile-rows, 8 from 64, 16 from 256, 32 from 1024); the
  * partial-sum buffer grows as the strip shrinks.  wgs: workgroups a
  * row-streamed launch (rectangles: prediction; squares beyond the symmetric
- * limit) aims for by slicing its columns, 256..2^20, or 0 = 8192.
+ * limit) aims for by slicing its columns, 256..2^20, or 0 = by size (whole
+ * rounds of the CUs for RBF with p <= 32 up to 32 workgroups per CU, else
+ * 8192).
  * Host-only; KQR_EINVAL outside those ranges. */
 int kqr_set_otf_shape(int strip, int64_t wgs);
 int kqr_kernel_build_packed(const float* X, int64_t n, int64_t p, int kernel, double gamma, int k_dtype, void* K,
@@ -366,8 +368,8 @@ int kqr_set_kv_shape(int k_dtype, int64_t n, int nld, int prefetch, int segs);
  * per workgroup, where the partial sums fit the symmetric limit), keeping
  * the fastest for n's size class (as kqr_set_otf_shape would, for that class
  * only), then the column-slice target of the row-streamed form on the
- * rectangle K(X[0:n/4], X) v over 2048 .. 32768 workgroups, keeping the
- * fastest.  JSON report into `report` (host, cap bytes, or NULL).
+ * rectangle K(X[0:n/4], X) v by size (reported as 0) and over 2048 .. 32768
+ * workgroups, keeping the fastest.  JSON report into `report` (host, cap bytes, or NULL).
  * Synchronises. */
 int kqr_autotune_otf(const float* X, int64_t n, int64_t p, int kernel, double gamma, int mode, int reps,
                      char* report, int64_t cap, void* stream);

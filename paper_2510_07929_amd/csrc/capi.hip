@@ -273,7 +273,7 @@ static void autotune_packed(const KMat& km, int64_t n, bool exact, int reps, cha
 // symmetric form {1, 2, 4, 8, 16, 32} (those whose partial sums fit the
 // budget) and installs the fastest for n's size class; then the column-slice
 // target of the row-streamed form on a rectangle K(X[0:n/4], X) v, over
-// {2048, 4096, 8192, 16384, 32768} workgroups.  JSON report.
+// {by size (0), 2048, 4096, 8192, 16384, 32768} workgroups.  JSON report.
 static void autotune_otf(const float* X, int64_t n, int p, KernelSpec ks, bool exact, int reps, char* report,
                          int64_t cap, hipStream_t st) {
   DevBuf sqn(size_t(n) * sizeof(float)), v(size_t(n) * sizeof(double)), u(size_t(n) * sizeof(double));
@@ -334,7 +334,7 @@ static void autotune_otf(const float* X, int64_t n, int p, KernelSpec ks, bool e
     int64_t best_wgs = keep_wgs;
     double best_wus = 1e300;
     first = true;
-    for (int64_t w : {int64_t(2048), int64_t(4096), int64_t(8192), int64_t(16384), int64_t(32768)}) {
+    for (int64_t w : {int64_t(0), int64_t(2048), int64_t(4096), int64_t(8192), int64_t(16384), int64_t(32768)}) {
       set_otf_wgs(w);
       const double us = time_us([&] {
         kapply_otf(X, sqn.as<float>(), nr, X, sqn.as<float>(), n, p, ks, v.as<double>(), u.as<double>(), 1, 1.0, 0.0,

@@ -428,12 +428,12 @@ constexpr int kOtfTile = 64;
 
 // Column slices of an on-the-fly launch: about 8192 workgroups in all (many
 // rounds of the blocks the chip holds at once, so the last round is a small
-// tail), each slice at least 1024 columns.  Every slice writes one partial
-// per row, added in a fixed order by otf_reduce_kernel.
-std::atomic<int64_t> g_otf_wgs{8192};  // target workgroups of a sliced launch (kqr_set_otf_shape)
+// tail) unless a target is set, each slice at least 1024 columns.  Every slice
+// writes one partial per row, added in a fixed order by otf_reduce_kernel.
+std::atomic<int64_t> g_otf_wgs{0};  // target workgroups of a sliced launch (kqr_set_otf_shape); 0: by size
 
 static int64_t otf_slices(int64_t rblk, int64_t nc) {
-  const int64_t wgs = g_otf_wgs.load();
+  const int64_t set = g_otf_wgs.load(), wgs = set > 0 ? set : 8192;
   const int64_t want = (wgs + std::max<int64_t>(rblk, 1) - 1) / std::max<int64_t>(rblk, 1);
   return std::max<int64_t>(1, std::min<int64_t>(want, (nc + 1023) / 1024));
 }
@@ -863,14 +863,14 @@ static int otf_sym_strip(int64_t n) {
 
 void set_otf_shape(int strip, int64_t wgs) {
   for (auto& a : g_otf_strip) a.store(strip);
-  g_otf_wgs.store(wgs > 0 ? wgs : 8192);
+  g_otf_wgs.store(wgs);
 }
 
 void set_otf_strip_for(int64_t n, int strip) { g_otf_strip[otf_class(n)].store(strip); }
 
 int64_t otf_wgs() { return g_otf_wgs.load(); }
 
-void set_otf_wgs(int64_t wgs) { g_otf_wgs.store(wgs > 0 ? wgs : 8192); }
+void set_otf_wgs(int64_t wgs) { g_otf_wgs.store(wgs); }
 
 int otf_strip_for(int64_t n) { return otf_sym_strip(n); }
 
@@ -1561,8 +1561,8 @@ static void kapply_otf_mfma_sym(const float* X, const float* q, int64_t n, int p
 }
 
 // Column slices of a rectangular launch on the matrix cores, in stages of
-// `stage` columns: where the launch is more than 32 workgroups per CU, as
-// otf_slices; below that, so that the workgroups come out in whole rounds of
+// `stage` columns: where a target is set, or the launch is more than 32
+// workgroups per CU, as otf_slices; below that, so that the workgroups come out in whole rounds of
 // the CUs (a CU with one more workgroup than the others is what the launch
 // waits for), the time taken as that of the busiest CU, two stages' time for
 // a workgroup's start and a half or a fifth more where one or two
@@ -1571,7 +1571,7 @@ static void kapply_otf_mfma_sym(const float* X, const float* q, int64_t n, int p
 static int64_t otf_mfma_per(int64_t rblk, int64_t nc, int64_t stage) {
   const int64_t cus = 256, ns = (nc + stage - 1) / stage;
   const int64_t big = std::min<int64_t>(otf_slices(rblk, nc), 65535);
-  if (rblk * std::min<int64_t>(ns, big) > 32 * cus || g_otf_wgs.load() != 8192)
+  if (rblk * std::min<int64_t>(ns, big) > 32 * cus || g_otf_wgs.load() > 0)
     return ((nc + big - 1) / big + stage - 1) / stage * stage;
   int64_t best = ns;
   double best_t = 0.0;

@@ -178,12 +178,12 @@ size_t otf_sym_scratch_doubles(int64_t n);  // partial sums of a symmetric on-th
 void set_otf_sym_budget(int64_t bytes);     // largest such buffer; beyond it the row-streamed forms run
 // Launch shape of the on-the-fly applies: strip = tiles per workgroup of the
 // symmetric square applies (0: by size), wgs = workgroups a sliced
-// rectangular launch aims for (0: 8192).
+// rectangular launch aims for (0: by size).
 void set_otf_shape(int strip, int64_t wgs);
 void set_otf_strip_for(int64_t n, int strip);  // the strip for n's size class only (0: by size)
 int otf_strip_for(int64_t n);                  // the strip the symmetric applies use at n
 int64_t otf_wgs();
-void set_otf_wgs(int64_t wgs);  // 0: 8192
+void set_otf_wgs(int64_t wgs);  // 0: by size
 
 // Launch-shape registry: every shape installed by an autotuner or a
 // kqr_set_* call, as the entries of the tuning file (kqr_tune_save /

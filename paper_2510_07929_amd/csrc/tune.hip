@@ -10,7 +10,8 @@
 //   {"kind": "apply", "k_dtype": 0, "mode": 0, "n": 50000, "m": 1, "a": 4, "b": 2, "c": 4, "wgs": 0, "us": 1440.1},
 //   ...]}
 // with (a, b, c) = apply: (rows, unroll, segments); kv: (nld, prefetch,
-// segments); packed: (map, strip, -); otf: (strip, -, -) plus wgs.
+// segments); packed: (map, strip, -); otf: (strip, -, -) plus wgs, where 0
+// (by size) leaves a target that is set as it is.
 #include "kernel_entry.h"
 #include "kmulti.h"
 #include "kqr_internal.h"

@@ -323,7 +323,7 @@ def kqr_set_otf_symmetric_limit(nbytes):
 
 def kqr_set_otf_shape(strip=0, wgs=0):
     """Launch shape of the on-the-fly applies (strip: tiles per workgroup of the symmetric
-    square applies, 0 = by size; wgs: target workgroups of sliced launches, 0 = 8192)."""
+    square applies, 0 = by size; wgs: target workgroups of sliced launches, 0 = by size)."""
     _check(lib().kqr_set_otf_shape(int(strip), int(wgs)), "kqr_set_otf_shape")
 
 

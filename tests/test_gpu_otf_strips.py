@@ -54,6 +54,26 @@ def _reference(kind, n, p):
     return _REF[key]
 
 
+@pytest.mark.parametrize("p", [10, 20])
+def test_slice_target_of_8192_is_a_target(dev, p):
+    """40 row blocks over 20,000 columns: 8191 and 8192 workgroups make the same slices of at least 1024 columns, so
+    the same bits; the rule by size cuts them elsewhere."""
+    n, m = 20000, 5000
+    X, _ = inputs.additive(n, p, (911, n, p))
+    Xt = torch.from_numpy(X).to(dev)
+    alpha = torch.from_numpy(np.random.default_rng(p).standard_normal(n)).to(dev)
+    say("slice target", p)
+    f = {}
+    try:
+        for wgs in (8191, 8192, 0):
+            kqr.kqr_set_otf_shape(0, wgs)
+            f[wgs] = kqr.kqr_predict(Xt, alpha, 0.1, 1.0, "rbf", 1.0 / p, Xt[:m] + 0.01)
+    finally:
+        kqr.kqr_set_otf_shape(0, 0)
+    assert torch.equal(f[8191], f[8192])
+    assert not torch.equal(f[0], f[8192])
+
+
 # 33 tile-rows: strips of 8, 16 and 32 leave ragged last strips; the last tile is ragged too
 @pytest.mark.parametrize("strip", [1, 2, 8, 16, 32])
 @pytest.mark.parametrize("kind,p", [("laplacian", 30), ("rbf", 8), ("rbf", 20), ("rbf", 30), ("rbf", 32)])
