@@ -1354,35 +1354,13 @@ __global__ __launch_bounds__(256, 4) void kapply_otf_mfma_kernel(
   }
 }
 
-// the sums of four per-lane values over the four lane groups of 16: group k
-// returns the total of value k
-__device__ __forceinline__ double groups4_sum_f64(const double (&x)[4]) {
-  auto pair = [](double a, double b, auto wide) {
-    const uint64_t ua = __builtin_bit_cast(uint64_t, a), ub = __builtin_bit_cast(uint64_t, b);
-    uint32_t l0, l1, h0, h1;
-    if constexpr (decltype(wide)::value) {
-      const auto lo = __builtin_amdgcn_permlane32_swap(uint32_t(ua), uint32_t(ub), false, false);
-      const auto hi = __builtin_amdgcn_permlane32_swap(uint32_t(ua >> 32), uint32_t(ub >> 32), false, false);
-      l0 = lo[0]; l1 = lo[1]; h0 = hi[0]; h1 = hi[1];
-    } else {
-      const auto lo = __builtin_amdgcn_permlane16_swap(uint32_t(ua), uint32_t(ub), false, false);
-      const auto hi = __builtin_amdgcn_permlane16_swap(uint32_t(ua >> 32), uint32_t(ub >> 32), false, false);
-      l0 = lo[0]; l1 = lo[1]; h0 = hi[0]; h1 = hi[1];
-    }
-    return __builtin_bit_cast(double, (uint64_t(h0) << 32) | l0) +
-           __builtin_bit_cast(double, (uint64_t(h1) << 32) | l1);
-  };
-  return pair(pair(x[0], x[1], std::false_type{}), pair(x[2], x[3], std::false_type{}), std::true_type{});
-}
-
 // Symmetric form for the square K(X, X): each distinct pair once, over the
 // upper-triangle 128 x 128 tiles of the packed geometry.  A workgroup takes a
 // strip of tiles of tile-row I, two 64-column stages per tile.  Every entry
 // feeds the row sum (times v_j) and, off the diagonal tile, the column sum
-// (times v_i): a lane adds its eight rows of each of the stage's four
-// 16-column tiles, the four lane groups are added across lanes (one exchange
-// for the four tiles: lane l ends with column l of the stage) and the four
-// waves in LDS.  Row sums are added over the 16 column lanes at the end of
+// (times v_i): of each of the stage's four 16-column tiles a lane adds its
+// eight rows, two exchanges add the four lane groups (all four end with the
+// sum and store it to the same LDS word), and the four waves are added in LDS.  Row sums are added over the 16 column lanes at the end of
 // the strip.  packed_reduce adds the partials in a fixed order.
 template <class G, bool EX>
 __global__ __launch_bounds__(256, 4) void kapply_otf_mfma_sym_kernel(

@@ -10,8 +10,9 @@
 //    (1/l_in - 1/l_out) U_E^T U_E with G_all = U^T U formed once per fit; a
 //    Newton step then only sums over the |E| interior rows.
 //  * C = Lc Lc^T by a blocked right-looking Cholesky (64-column panels; the
-//    diagonal block is factored by one wave, one row per lane, with the
-//    panel columns finished in registers);
+//    diagonal block is factored by four waves in panels of sixteen columns:
+//    the earlier panels' part on the matrix cores, the panel itself by one
+//    wave in registers, one row per lane);
 //    W = Lc^{-1} is formed explicitly by recursive doubling
 //    (W21 = -W22 L21 W11), so an application needs two triangular mat-vecs
 //    over many workgroups instead of sequential substitutions, and
@@ -68,6 +69,8 @@ __device__ __forceinline__ double load_or_zero(const double* p, bool ok) {
 // Bound by the FP64 matrix rate (66 TFLOP/s in a large library product here):
 // n = 50,000, r = 500, general L: 811 us as VALU FMAs from LDS tiles with
 // barriers every 32 rows, 299 us now; r = 224, no L: 368 us, 136 us now.
+// (The weighted form needs seven registers more than the 128 of four waves per
+// SIMD and spills them.)
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 // w = 1 / L, once per launch of the weighted SYRK: its waves read a row's weight
