@@ -6,7 +6,7 @@ import pytest
 
 torch = pytest.importorskip("torch")
 
-from paper_2510_07929_amd import kqr
+from paper_2510_07929_amd import inputs, kqr
 
 pytestmark = pytest.mark.gpu
 
@@ -114,3 +114,73 @@ def test_rpcholesky_steps_at_chunk_edges(dev, n, rank, stored):
         G[:, i] = F[:, i]
         d = np.maximum(d - G[:, i] ** 2, 0.0)
         d[s] = 0.0
+
+
+def _rpc_inputs(dev, X, gamma, form):
+    """(kernel, K): entries from X, or a stored K."""
+    Xt = torch.from_numpy(X).to(dev)
+    if form in ("rbf", "laplacian"):
+        return Xt, form, None
+    return Xt, "rbf", kqr.kqr_kernel_build(Xt, "rbf", gamma, form)
+
+
+@pytest.mark.parametrize("form", ["rbf", "laplacian", "fp32", "bf16"])
+@pytest.mark.parametrize("n,rank", [(7, 7), (300, 12), (70001, 9)])
+def test_rpcholesky_stops_at_the_rank_of_k(dev, n, rank, form):
+    """Seven places whose kernel values underflow between them: K is a 0-1 block matrix, every step is exact, and
+    the residual is zero after seven pivots, one per place; the columns from there on are zero."""
+    places = np.zeros((7, 3), dtype=np.float32)
+    for k in range(3):
+        places[2 * k + 1, k], places[2 * k + 2, k] = 16.0, -16.0
+    rng = np.random.default_rng((n, rank))
+    at = rng.permutation(np.arange(n) % 7)
+    gamma = 16.0  # exp(-16 * 16) and below: zero in FP32
+    say("rpcholesky rank", n, rank, form)
+    Xt, kernel, K = _rpc_inputs(dev, places[at], gamma, form)
+    F, piv, r = kqr.kqr_rpcholesky(rank, rng.uniform(0.0, 1.0, rank), X=Xt, kernel=kernel, gamma=gamma, K=K)
+    assert r == 7 and sorted(at[piv].tolist()) == list(range(7))
+    want = np.zeros((n, F.shape[1]), dtype=np.float32)
+    want[:, :7] = at[:, None] == at[piv][None, :]
+    assert np.array_equal(F.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("form", ["laplacian", "bf16"])
+@pytest.mark.parametrize("n,rank", [(257, 70), (2049, 45)])
+def test_rpcholesky_columns_of_other_kernels(dev, n, rank, form):
+    """The columns at the pivots drawn, against the steps in FP64 on the host on the same entries."""
+    rng = np.random.default_rng((n, rank, 1))
+    X = rng.uniform(-1.0, 1.0, (n, 3)).astype(np.float32)
+    gamma = 2.0
+    say("rpcholesky columns", n, rank, form)
+    Xt, kernel, K = _rpc_inputs(dev, X, gamma, form)
+    F, piv, r = kqr.kqr_rpcholesky(rank, rng.uniform(0.0, 1.0, rank), X=Xt, kernel=kernel, gamma=gamma, K=K)
+    F = F.cpu().numpy().astype(np.float64)
+    assert r == rank and len(set(piv.tolist())) == rank
+    x = X.astype(np.float64)
+    for i, s in enumerate(piv):
+        if K is None:
+            col = np.exp(-gamma * np.abs(x - x[s]).sum(1))
+        else:
+            col = K[s, :n].double().cpu().numpy()
+        g = col - F[:, :i] @ F[s, :i]
+        # FP32 roundings of an entry from X and of F's column, magnified by 1 / sqrt(g_s) as g_s carries them too
+        tol = 64 * (i + 1) * 2.0 ** -24 / g[s]
+        assert np.max(np.abs(F[:, i] - g / np.sqrt(g[s]))) <= tol, i
+
+
+@pytest.mark.parametrize("kd", ["fp32", "bf16"])
+def test_preconditioner_from_a_packed_k(dev, kd):
+    """A fit on the packed layout draws its pivots from the tiles: the same entries as the full layout's, so the rank
+    rule keeps the same columns, and Phase I needs about as many iterations."""
+    prob = inputs.workload("c0", n=1500)
+    X, y = torch.from_numpy(prob.X).to(dev), torch.from_numpy(prob.y).to(dev)
+    got = []
+    for layout in (0, 1):
+        say("packed preconditioner", kd, layout)
+        _, _, info, st = kqr.kqr_fit(X, y, prob.tau, prob.lam, prob.kernel, prob.gamma, k_layout=layout,
+                                     k_dtype=kqr.KDTYPES[kd], xi=1e-4, uniforms=inputs.pivot_uniforms(64, (1500, 1)))
+        assert st == kqr.KQR_OK
+        got.append((info["rank_used"], info["admm_pcg_iters"]))
+    (r0, it0), (r1, it1) = got
+    assert r0 == r1 == 39  # ceil(sqrt n): the rule keeps them all
+    assert abs(it0 - it1) <= 0.2 * it0
