@@ -1039,9 +1039,10 @@ int quantize_columns(const float* X, int64_t n, int p, uint32_t* Xq, hipStream_t
 // MFMAs are issued ahead of this tile's entries, and the MFMA results stay in
 // ordinary registers (the second launch bound; without it each is copied from
 // the accumulation registers first).  Loading each stage where it was needed,
-// a load at a time: 100,000 x 20,011 at p = 30 exact 690 us, now 612; the
-// square form at 40,000 x 30 exact 400, now 335; 20,000 x 5,000 at p = 10 63,
-// now 48.
+// a load at a time, against this form, whole calls timed in turn: 100,000 x
+// 20,011 at p = 30 exact 755 and 628 us; the square form at 40,000 x 30 exact
+// 430 and 346; 20,000 x 5,000 at p = 10 77 and 56.  (The same kernel moves by
+// 8 % from run to run with the clock.)
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef uint16_t u16x8_t __attribute__((ext_vector_type(8)));
