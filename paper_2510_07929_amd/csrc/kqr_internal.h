@@ -144,7 +144,8 @@ inline bool ranges_overlap(const double* a, size_t na, const double* b, size_t n
   return ia < ib + nb * sizeof(double) && ib < ia + na * sizeof(double);
 }
 
-// u = K v (materialised, rows [0, nrows), cols [0, ncols)).  exact: v64 + FP64; else v32.
+// u = K v (materialised, rows [0, nrows), cols [0, ncols)).  exact: v64 + FP64; else v32, or v64
+// rounded to FP32 as it is read where v32 is null.  v64 is 16-byte aligned and apart from u.
 // scratch (scratch_doubles long, or null) holds the partial sums when it is
 // large enough (kapply_scratch_doubles); otherwise they are allocated on st.
 void kapply_dense(const KMat& km, int64_t nrows, int64_t ncols, const float* v32, const double* v64,
